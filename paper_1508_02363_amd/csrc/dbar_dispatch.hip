@@ -68,12 +68,17 @@ int line_tiles(int N, bool cols, bool fp64) {
   return line_tiles_variant(N, cols, fp64, cols ? tile_variant(N, fp64) : 0);
 }
 
+int box_row_align(int N) {
+  return std::max(kBoxCols, std::max(N / line_tiles(N, false, true), N / line_tiles(N, false, false)));
+}
+
 // Algorithmic HBM bytes of one stage (each array read or written once): per batch entry, and once per launch for the
 // potential when all entries share it (Q_bs = 0: one array read at stride 0 by every entry).
 static double line_bytes_once(int N, LineOp op, const LineArgs& a, size_t es) {
   const bool reads_q = op == LineOp::ColsInvTailFwd || op == LineOp::RowsInvTailEpilogue ||
                        op == LineOp::ColsFwdPotential;
-  return reads_q && a.Q_bs == 0 ? (double)N * N * es : 0.0;
+  const double in = op == LineOp::RowsInvTailEpilogue ? a.box_fr * a.box_fc : 1.0;
+  return reads_q && a.Q_bs == 0 ? in * N * N * es : 0.0;
 }
 static double line_bytes(int N, LineOp op, const LineArgs& a, size_t es) {
   const double P = (double)N * N * es;
@@ -90,13 +95,18 @@ static double line_bytes(int N, LineOp op, const LineArgs& a, size_t es) {
     case LineOp::ColsFwdPotential: return P + PQ;
     case LineOp::ColsFwdPlain: return 2 * P;
     case LineOp::ColsInvPlain: return 2 * P;
-    case LineOp::RowsFwdMoments: return 2 * P + (a.upd_coef ? P + a.upd_nv * (a.upd_v32 ? P / 2 : P) : 0.0);
-    case LineOp::ColsFwdRegularInv: return 2 * P + (a.sout ? P : 0.0);
+    // x-space stages: s, the basis, Q and the result live on the box, the transform array on its rows (all rows where h
+    // is wanted on the whole grid)
+    case LineOp::RowsFwdMoments:
+      return a.box_fr * (P + a.box_fc * (P + (a.upd_coef ? P + a.upd_nv * (a.upd_v32 ? P / 2 : P) : 0.0)));
+    case LineOp::ColsFwdRegularInv: return (a.box_fr + (a.box_full ? 1.0 : a.box_fr)) * P + (a.sout ? P : 0.0);
     case LineOp::RowsInvTailEpilogue:  // in, Q (per entry unless shared), out, S, Y (unless formed from q_k), h, the
                                        // FP32 copy, earlier basis
-      return P + PQ + (a.out ? P : 0.0) + (a.out32 ? P / 2 : 0.0) + (a.alpha != 0.0 ? P : 0.0) +
-             (a.gamma != 0.0 && !a.y_rhs ? P : 0.0) + (a.hout ? P : 0.0) +
-             (a.dot_nv > 0 ? (a.dot_nv - (a.alpha != 0.0 ? 1 : 0)) * P : 0.0);
+      return (a.box_full ? 1.0 : a.box_fr) * P + (a.hout ? P : 0.0) +
+             a.box_fr * a.box_fc *
+                 (PQ + (a.out ? P : 0.0) + (a.out32 ? P / 2 : 0.0) + (a.alpha != 0.0 ? P : 0.0) +
+                  (a.gamma != 0.0 && !a.y_rhs ? P : 0.0) +
+                  (a.dot_nv > 0 ? (a.dot_nv - (a.alpha != 0.0 ? 1 : 0)) * P : 0.0));
   }
   return 0.0;
 }

@@ -79,7 +79,30 @@ struct LineArgs {
   int upd_zero = 0;            // the input counts as zero (its loaded values are ignored)
   void* upd_out = nullptr;
   double* upd_part = nullptr;
+  // x-space stages: the index box {row0, row1, col0, col1} that holds the potential (k_box_cut), one per entry at
+  // box + b * box_bs (0: shared).  s, the basis, the result and the products live on it: nothing outside is read or
+  // written, and the transform array's rows outside [row0, row1) count as zero.  Null: the whole grid.
+  const int* box = nullptr;    int box_bs = 0;
+  int box_rows = 0;            // rows the launch covers (at least every entry's row1 - row0)
+  int box_full = 0;            // ColsFwdRegularInv, RowsInvTailEpilogue: the h that comes out is wanted on the whole grid
+  double box_fr = 1.0, box_fc = 1.0;  // rows and columns of the box over N (byte accounting)
 };
+
+// Tiles (partial sums) of a row launch, per entry: all of them, or those of the entry's box.
+struct TileSpan {
+  int stride = 0;              // tiles of the whole grid: the stride between the partials of one value
+  int rows = 1;                // rows per tile
+  const int* box = nullptr;    int box_bs = 0;
+  DBAR_HD int count(int b) const {
+    return box ? (box[(size_t)b * box_bs + 1] - box[(size_t)b * box_bs]) / rows : stride;
+  }
+};
+// Rows of a box are whole tiles of the row launches (of either precision) and its columns whole kBoxCols groups.
+constexpr int kBoxCols = 8;
+// Smallest grid on which x-space solves keep to the potential's index box: on smaller ones a row tile is most of the
+// grid and the launches are bound by latency, not by the rows they cover.
+constexpr int kBoxMinN = 128;
+int box_row_align(int N);
 
 // Number of blocks (tiles) per batch entry used by a line stage with the current tile choice; partial buffers are
 // sized for the default (narrowest, most tiles) choice.
@@ -137,7 +160,13 @@ template <typename TO, typename TI> void launch_convert(const void* in, size_t i
 int vec_blocks(size_t n);
 
 // Deterministic reduction of partial sums: out[b][v] = scale * sum_blk part[b][v][blk]
-void launch_reduce(const double* part, int nval, int nblk, double* out, int B, const int* act, hipStream_t s);
+void launch_reduce(const double* part, int nval, const TileSpan& span, double* out, int B, const int* act,
+                   hipStream_t s);
+
+// The box of each potential Q (B of them, stride Q_bs) on an N x N grid: the rows and columns outside hold at most
+// 2^-56 of its 2-norm.  tmp: box_scratch(N, B) doubles.  box: 4 B ints.
+size_t box_scratch(int N, int B);
+void launch_box(const c64* Q, size_t Q_bs, int N, double* tmp, int* box, int B, const int* act, hipStream_t s);
 
 // ------------------------------------------------------------------------------------------------------------
 // Optional measurement: HIP events around every launch, grouped by stage, with the number of active batch entries

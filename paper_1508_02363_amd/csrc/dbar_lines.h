@@ -16,6 +16,15 @@
 //   RowsFwdMoments      moments d_n = F(z^n s)(0), dt = F(conj(z) s)(0) of the input, first pass of F s
 //   ColsFwdRegularInv   second pass of F s (= S), R = (S - G)/xi, first pass of F^{-1} R
 //   RowsInvTailEpilogue second pass of F^{-1} R, h, and F^{-1} A(S) = s + i q_k conj(h)
+//
+// Every vector of that iteration is q_k times something (the right-hand side is -i q_k, the operator's second term
+// i q_k conj(h)), so it lives where the potential does.  The three launches keep to the potential's index box
+// (LineArgs::box): the row launches run its rows only and touch its columns only, the column launch reads and writes its
+// rows of the transform array (rows outside are zero going in, and h is not needed there coming out, unless the caller
+// wants h itself).  They are bound by memory, so they shorten with the box.  Measured at N = 1024, L = 5, a Gaussian
+// potential (44% of the rows and columns), 8 FP32 entries per launch beside a second lane: RowsFwdMoments 69 -> 25 us,
+// ColsFwdRegularInv 67 -> 40 us, RowsInvTailEpilogue 76 -> 27 us; the 16-k mixed solve 7.1 -> 3.8 ms.  At N = 512, 45
+// entries, FP64, a sum of three Gaussians: 134 -> 47, 93 -> 73, 153 -> 85 us; 11.4 -> 7.7 ms.
 #pragma once
 
 #include "dbar_fft.h"
@@ -288,6 +297,48 @@ struct LdsSize {
 };
 
 // ------------------------------------------------------------------------------------------------------------
+// Reads and writes on an index box: buffer accesses whose offset is moved out of the buffer outside the box, where the
+// hardware returns zero or drops the store without memory traffic, so that the box costs no branch around each access
+// ------------------------------------------------------------------------------------------------------------
+using Rsrc = __amdgpu_buffer_rsrc_t;
+constexpr uint32_t kOutside = 0x80000000u;  // beyond every array here (N <= 4096: at most 2^28 bytes per entry)
+
+// the N x N array of one entry at p (the same for every lane of the wave)
+template <typename T, int N>
+DBAR_D Rsrc entry_rsrc(const cx<T>* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<cx<T>*>(p), 0, N * N * (int)sizeof(cx<T>), 0x00020000);
+}
+// element idx, or zero / nothing when !in
+template <typename T>
+DBAR_D cx<T> box_load(Rsrc r, uint32_t idx, bool in) {
+  const uint32_t off = in ? idx * (uint32_t)sizeof(cx<T>) : kOutside;
+  if constexpr (sizeof(T) == 4) return __builtin_bit_cast(cx<T>, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+  else return __builtin_bit_cast(cx<T>, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+template <typename T>
+DBAR_D void box_store(Rsrc r, uint32_t idx, bool in, cx<T> v) {
+  using V2 = unsigned __attribute__((ext_vector_type(2)));
+  using V4 = unsigned __attribute__((ext_vector_type(4)));
+  const uint32_t off = in ? idx * (uint32_t)sizeof(cx<T>) : kOutside;
+  if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V2, v), r, off, 0, 0);
+  else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(V4, v), r, off, 0, 0);
+}
+
+// an entry's box (uniform over the block); always the whole grid below kBoxMinN
+template <int N>
+struct Box {
+  int r0, r1, c0, c1;
+  DBAR_D bool row(int i) const { return N < kBoxMinN || (i >= r0 && i < r1); }
+  DBAR_D bool col(int j) const { return N < kBoxMinN || (j >= c0 && j < c1); }
+};
+template <int N>
+DBAR_D Box<N> entry_box(const LineArgs& a, int b) {
+  if (N < kBoxMinN || !a.box) return Box<N>{0, N, 0, N};
+  const int* x = a.box + (size_t)b * a.box_bs;
+  return Box<N>{x[0], x[1], x[2], x[3]};
+}
+
+// ------------------------------------------------------------------------------------------------------------
 // Operations
 // ------------------------------------------------------------------------------------------------------------
 struct NoAcc {};
@@ -303,7 +354,8 @@ struct OpBase {
   DBAR_D const cx<T>* inp(int b) const { return static_cast<const cx<T>*>(a.in) + (size_t)b * a.in_bs; }
   DBAR_D cx<T>* outp(int b) const { return static_cast<cx<T>*>(a.out) + (size_t)b * a.out_bs; }
   template <class Acc> DBAR_D void mid(int, int, int, cx<T>&) const {}
-  template <int NT, class Acc> DBAR_D void finish(Acc&, int, int, int, double*) const {}
+  // finish (and dots): the tile's partials go to slot `slot` of ntiles
+  template <int NT, class Acc> DBAR_D void finish(Acc&, int, int, int, int, double*) const {}
   // after the stores: dots over the values the stores left in the thread's registers (ops that define DOTS)
   static constexpr bool DOTS = false;
   // the op works on its loaded values before the first transform (loaded(acc, b, line, jt, v, tile, ntiles, scratch)
@@ -311,6 +363,8 @@ struct OpBase {
   static constexpr bool LOADACC = false;
   // ROLLED stores: > 1: the op's store_all stores the thread's elements GROUP at a time, else store one at a time
   static constexpr int GROUP = 1;
+  // the op works on the entry's box (row launches cover its rows only); its load and loaded take the Pre
+  static constexpr bool BOXED = false;
   // per-block data read once at kernel start, before any store (ops that need it define PRE and a Pre type)
   static constexpr bool PRE = false;
   struct Pre {};
@@ -440,18 +494,18 @@ struct MomentsBase : OpBase<T, N> {
   }
 
   template <int NT>
-  DBAR_D void finish(Acc& acc, int b, int tile, int ntiles, double* scratch) const {
-    if (this->a.M == 11) finish_kk<NT, 11>(acc, b, tile, ntiles, scratch);
-    else finish_kk<NT, kMaxM>(acc, b, tile, ntiles, scratch);
+  DBAR_D void finish(Acc& acc, int b, int tile, int slot, int ntiles, double* scratch) const {
+    if (this->a.M == 11) finish_kk<NT, 11>(acc, b, tile, slot, ntiles, scratch);
+    else finish_kk<NT, kMaxM>(acc, b, tile, slot, ntiles, scratch);
   }
   // Block reduction: 1) each line's mu_k summed over its threads within a wave by shuffles (a column tile
   // interleaves its lines, so a column's lanes differ by multiples of LN; a row's lanes are contiguous), parked in
   // LDS per reduction group; 2) summed over the line's groups (one thread per line and value); 3) combined into the
   // moments (one thread per line and moment); 4) the tile's partials: sum over its lines.
   template <int NT, int KK>
-  DBAR_D void finish_kk(Acc& acc, int b, int tile, int ntiles, double* scratch) const {
+  DBAR_D void finish_kk(Acc& acc, int b, int tile, int slot, int ntiles, double* scratch) const {
     constexpr int NU = 2 * (KK + 1);  // mu values in use
-    double* dst = this->a.part + (size_t)b * NV * ntiles + tile;
+    double* dst = this->a.part + (size_t)b * NV * ntiles + slot;
     constexpr int TPL = LineGeom<N>::TPL;
     constexpr int LN = NT / TPL;  // lines per tile
     // reduction groups: runs of GS consecutive lanes on a row tile; (wave, column) pairs on a column tile of fewer
@@ -558,15 +612,21 @@ struct OpRowsFwdMoments : MomentsBase<T, N, true> {
   static constexpr int DIR1 = -1;
   static constexpr bool TWO = false;
   static constexpr bool LOADACC = true;
+  static constexpr bool BOXED = true;
+  static constexpr bool PRE = true;
+  using Pre = Box<N>;
   using Acc = typename MomentsBase<T, N, true>::Acc;
-  DBAR_D cx<T> load(int b, int row, int pos) const { return this->inp(b)[(size_t)row * N + pos]; }
+  DBAR_D void prologue(int b, Pre& p) const { p = entry_box<N>(this->a, b); }
+  DBAR_D cx<T> load(int b, int row, int pos, const Pre& p) const {
+    return box_load<T>(entry_rsrc<T, N>(this->inp(b)), row * N + pos, p.col(pos));
+  }
   template <int NT>
-  DBAR_D void loaded(Acc& acc, int b, int row, int jt, cx<T>* v, int tile, int ntiles, double* scratch) const {
+  DBAR_D void loaded(Acc& acc, int b, int row, int jt, cx<T>* v, int slot, int ntiles, double* scratch,
+                     const Pre& p) const {
     using G = LineGeom<N>;
     const LineArgs& a = this->a;
     if (a.upd_coef) {
       const double* coef = a.upd_coef + (size_t)b * a.upd_coef_bs;
-      const cx<T>* V = static_cast<const cx<T>*>(a.dotV) + (size_t)b * a.dotV_bs + (size_t)row * N;
       c64 w[G::RMAX];
 #pragma unroll
       for (int s = 0; s < G::RMAX; ++s) w[s] = a.upd_zero ? c64{0.0, 0.0} : cvt<double>(v[s]);
@@ -575,31 +635,40 @@ struct OpRowsFwdMoments : MomentsBase<T, N, true> {
         const double c = a.upd_sign * coef[i];
         if (c == 0.0) continue;  // also keeps never-written basis slots (any bit pattern) out of the sum
         if (sizeof(T) == 8 && a.upd_v32) {
-          const c32* Vi = static_cast<const c32*>(a.dotV) + (size_t)b * a.dotV_bs + (size_t)row * N + (size_t)i * N * N;
+          const Rsrc Vi = entry_rsrc<float, N>(static_cast<const c32*>(a.dotV) + (size_t)b * a.dotV_bs +
+                                               (size_t)i * N * N);
 #pragma unroll
-          for (int s = 0; s < G::RMAX; ++s) w[s] = w[s] - c * cvt<double>(Vi[jt + s * G::TPL]);
+          for (int s = 0; s < G::RMAX; ++s) {
+            const int pos = jt + s * G::TPL;
+            w[s] = w[s] - c * cvt<double>(box_load<float>(Vi, row * N + pos, p.col(pos)));
+          }
         } else {
-          const cx<T>* Vi = V + (size_t)i * N * N;
+          const Rsrc Vi = entry_rsrc<T, N>(static_cast<const cx<T>*>(a.dotV) + (size_t)b * a.dotV_bs +
+                                           (size_t)i * N * N);
 #pragma unroll
-          for (int s = 0; s < G::RMAX; ++s) w[s] = w[s] - c * cvt<double>(Vi[jt + s * G::TPL]);
+          for (int s = 0; s < G::RMAX; ++s) {
+            const int pos = jt + s * G::TPL;
+            w[s] = w[s] - c * cvt<double>(box_load<T>(Vi, row * N + pos, p.col(pos)));
+          }
         }
       }
-      cx<T>* out = static_cast<cx<T>*>(a.upd_out) + (size_t)b * a.in_bs + (size_t)row * N;
+      const Rsrc out = entry_rsrc<T, N>(static_cast<const cx<T>*>(a.upd_out) + (size_t)b * a.in_bs);
       double nrm[1] = {0.0};
 #pragma unroll
       for (int s = 0; s < G::RMAX; ++s) {
+        const int pos = jt + s * G::TPL;
         v[s] = cvt<T>(w[s]);
-        out[jt + s * G::TPL] = v[s];
+        box_store<T>(out, row * N + pos, p.col(pos), v[s]);
         nrm[0] += rdot(v[s], v[s]);
       }
       if (a.upd_part) {
-        block_reduce_store<NT, 1>(nrm, a.upd_part + (size_t)b * ntiles + tile, 0, scratch);
+        block_reduce_store<NT, 1>(nrm, a.upd_part + (size_t)b * ntiles + slot, 0, scratch);
         __syncthreads();  // the scratch aliases the LDS the transform's first exchange writes
       }
     }
     this->add_loaded(acc, b, row, jt, v);
   }
-  DBAR_D void store(Acc&, int b, int row, int pos, cx<T> v) const {
+  DBAR_D void store(Acc&, int b, int row, int pos, cx<T> v, const Pre&) const {
     this->outp(b)[t_index<T, N>(row, pos)] = v;
   }
 };
@@ -696,19 +765,28 @@ struct OpColsFwdRegInv : OpBase<T, N> {
   static constexpr bool TWO = true;
   static constexpr bool ROLLED = true;
   using Acc = NoAcc;
-  DBAR_D cx<T> load(int b, int col, int pos) const { return this->inp(b)[t_index<T, N>(pos, col)]; }
+  static constexpr bool BOXED = true;
   static constexpr bool PRE = true;
-  using Pre = RegPre;
-  DBAR_D void prologue(int b, Pre& p) const { regularised_pre(this->a, b, p); }
+  struct Pre {
+    RegPre g;
+    Box<N> x;
+  };
+  DBAR_D void prologue(int b, Pre& p) const {
+    regularised_pre(this->a, b, p.g);
+    p.x = entry_box<N>(this->a, b);
+  }
+  DBAR_D cx<T> load(int b, int col, int pos, const Pre& p) const {
+    return box_load<T>(entry_rsrc<T, N>(this->inp(b)), t_index<T, N>(pos, col), p.x.row(pos));
+  }
   template <class A>
   DBAR_D void mid(int b, int col, int pos, cx<T>& v, const Pre& p) const {
     const T f = static_cast<T>(((col + pos) & 1) ? -this->a.cf : this->a.cf);
     const cx<T> S = f * v;
     if (this->a.sout) (static_cast<cx<T>*>(this->a.sout) + (size_t)b * this->a.sout_bs)[(size_t)pos * N + col] = S;
-    v = regularised<T, N>(this->a, p, pos, col, S);  // row = xi2 index (pos), position = xi1 index (col)
+    v = regularised<T, N>(this->a, p.g, pos, col, S);  // row = xi2 index (pos), position = xi1 index (col)
   }
-  DBAR_D void store(Acc&, int b, int col, int pos, cx<T> v, const Pre&) const {
-    this->outp(b)[t_index<T, N>(pos, col)] = v;
+  DBAR_D void store(Acc&, int b, int col, int pos, cx<T> v, const Pre& p) const {
+    box_store<T>(entry_rsrc<T, N>(this->outp(b)), t_index<T, N>(pos, col), this->a.box_full || p.x.row(pos), v);
   }
 };
 
@@ -797,9 +875,9 @@ struct OpRowsFwdEpilogue : OpBase<T, N> {
     acc.sdot += sv.re * od.re + sv.im * od.im;
   }
   template <int NT>
-  DBAR_D void finish(Acc& acc, int b, int tile, int ntiles, double* scratch) const {
+  DBAR_D void finish(Acc& acc, int b, int, int slot, int ntiles, double* scratch) const {
     if (!this->a.want_norm) return;
-    block_reduce_store<NT, 1>(acc.v, this->a.part + (size_t)b * ntiles + tile, 0, scratch);
+    block_reduce_store<NT, 1>(acc.v, this->a.part + (size_t)b * ntiles + slot, 0, scratch);
   }
   // Re<V_i, out> over this tile for i < dot_nv, from the output values in registers (FP64 accumulation, the order
   // fixed): the multi-dot of the first classical Gram-Schmidt pass without reading the new vector back.  The last
@@ -844,15 +922,22 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
   // otherwise fetched again for most entries (measured 3-7% off the launch); at N = 1024 the tile-major order
   // measured 2-4% slower per launch, and the entry-major order stays
   static constexpr bool TILE_MAJOR = N >= 4096;
-  using Pre = typename OpColsInvTail<T, N, false>::Pre;
+  static constexpr bool BOXED = true;
+  struct Pre : OpColsInvTail<T, N, false>::Pre {
+    Box<N> x;
+  };
+  DBAR_D void prologue(int b, Pre& p) const {
+    OpColsInvTail<T, N, false>::prologue(b, p);
+    p.x = entry_box<N>(this->a, b);
+  }
   struct Acc {
     double v[1];
     double sdot;  // Re<S, out> over this thread's elements (S is the last vector of the fused products)
   };
-  DBAR_D cx<T> load(int b, int row, int pos) const { return this->inp(b)[t_index<T, N>(row, pos)]; }
+  DBAR_D cx<T> load(int b, int row, int pos, const Pre&) const { return this->inp(b)[t_index<T, N>(row, pos)]; }
   // The stores run GROUP elements at a time: the group's global reads (q, the x factor of e_k, S, Y) are issued
   // together ahead of its tails.  The LDS slot of each element (the row transform's output r) is replaced by the
-  // stored value, for the Gram-Schmidt products.
+  // stored value, for the Gram-Schmidt products (zero outside the box).
   // four at a time: wider groups hold more registers than the loads in flight repay (the FP32 launch drops to three
   // waves per SIMD at eight)
   static constexpr int GROUP_W = 4;
@@ -860,21 +945,21 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
   struct GroupIn {
     cx<T> q[GROUP], s[GROUP], y[GROUP], ex[GROUP];
   };
-  // the group's q (times the x factor of e_k on the plain operator), S and Y
-  DBAR_D void group_load(GroupIn& g, int b, int row, int jt, int s0) const {
+  // the group's q (times the x factor of e_k on the plain operator), S and Y (zero outside the box)
+  DBAR_D void group_load(GroupIn& g, int b, int row, int jt, int s0, const bool (&in)[GROUP]) const {
     using G = LineGeom<N>;
     const LineArgs& a = this->a;
-    const size_t base = (size_t)row * N;
-    const cx<T>* Qb = static_cast<const cx<T>*>(a.Q) + (size_t)b * a.Q_bs + base;
-    const cx<T>* Sb = static_cast<const cx<T>*>(a.S) + (size_t)b * a.S_bs + base;
-    const cx<T>* Yb = static_cast<const cx<T>*>(a.Y) + (size_t)b * a.Y_bs + base;
+    const Rsrc Qb = entry_rsrc<T, N>(static_cast<const cx<T>*>(a.Q) + (size_t)b * a.Q_bs);
+    const Rsrc Sb = entry_rsrc<T, N>(static_cast<const cx<T>*>(a.S) + (size_t)b * a.S_bs);
+    const Rsrc Yb = entry_rsrc<T, N>(static_cast<const cx<T>*>(a.Y) + (size_t)b * a.Y_bs);
     const size_t eo = (size_t)b * a.e_bs;
 #pragma unroll
     for (int u = 0; u < GROUP; ++u) {
       const int pos = jt + (s0 + u) * G::TPL;
-      g.q[u] = Qb[pos];
-      g.s[u] = a.alpha != 0.0 ? Sb[pos] : cx<T>{T(0), T(0)};
-      g.y[u] = (a.gamma != 0.0 && !a.y_rhs) ? Yb[pos] : cx<T>{T(0), T(0)};
+      const uint32_t idx = row * N + pos;
+      g.q[u] = box_load<T>(Qb, idx, in[u]);
+      g.s[u] = a.alpha != 0.0 ? box_load<T>(Sb, idx, in[u]) : cx<T>{T(0), T(0)};
+      g.y[u] = (a.gamma != 0.0 && !a.y_rhs) ? box_load<T>(Yb, idx, in[u]) : cx<T>{T(0), T(0)};
       if (a.shv) g.ex[u] = cx<T>{T(1), T(0)};
       else if constexpr (sizeof(T) == 8) g.ex[u] = a.ex[eo + pos];
       else g.ex[u] = a.ex32[eo + pos];
@@ -892,14 +977,24 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
       if constexpr (sizeof(T) == 8) ey = a.ey[(size_t)b * a.e_bs + row];
       else ey = a.ey32[(size_t)b * a.e_bs + row];
     }
+    const bool row_in = p.x.row(row);
+    const Rsrc outb = entry_rsrc<T, N>(this->outp(b));
+    const Rsrc out32 = entry_rsrc<float, N>(static_cast<const c32*>(a.out32) + (size_t)b * a.out32_bs);
 #pragma unroll 1
     for (int s0 = 0; s0 < G::RMAX; s0 += GROUP) {
+      bool in[GROUP];
+#pragma unroll
+      for (int u = 0; u < GROUP; ++u) in[u] = row_in && p.x.col(jt + (s0 + u) * G::TPL);
       GroupIn cur;
-      group_load(cur, b, row, jt, s0);
+      group_load(cur, b, row, jt, s0, in);
 #pragma unroll
       for (int u = 0; u < GROUP; ++u) {
         const int pos = jt + (s0 + u) * G::TPL;
         cx<T>& slot = my[G::padded(pos) * LS];
+        if (!in[u] && !a.hout) {  // outside the box only h is formed
+          slot = cx<T>{T(0), T(0)};
+          continue;
+        }
         const cx<T> h = this->h_at(b, pos, row, slot, p);  // x index pos, y index row
         if (a.hout) (static_cast<cx<T>*>(a.hout) + (size_t)b * a.hout_bs)[base + pos] = h;
         const cx<T> qk = cur.q[u] * (cur.ex[u] * ey);
@@ -911,9 +1006,11 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
         } else {  // the FP32 operator's result is FP32: form it in FP32
           ot = cvt<T>(a.beta) * w + static_cast<T>(a.alpha) * cur.s[u] + static_cast<T>(a.gamma) * yv;
         }
-        if (a.out) this->outp(b)[base + pos] = ot;
+        if (!in[u]) ot = cx<T>{T(0), T(0)};  // (q is zero there, but h may not be finite)
+        const uint32_t idx = row * N + pos;
+        if (a.out) box_store<T>(outb, idx, in[u], ot);
         if constexpr (sizeof(T) == 8) {
-          if (a.out32) (static_cast<c32*>(a.out32) + (size_t)b * a.out32_bs)[base + pos] = cvt<float>(ot);
+          if (a.out32) box_store<float>(out32, idx, in[u], cvt<float>(ot));
         }
         slot = ot;
         acc.v[0] += rdot(ot, ot);
@@ -922,9 +1019,9 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
     }
   }
   template <int NT>
-  DBAR_D void finish(Acc& acc, int b, int tile, int ntiles, double* scratch) const {
+  DBAR_D void finish(Acc& acc, int b, int, int slot, int ntiles, double* scratch) const {
     if (!this->a.want_norm) return;
-    block_reduce_store<NT, 1>(acc.v, this->a.part + (size_t)b * ntiles + tile, 0, scratch);
+    block_reduce_store<NT, 1>(acc.v, this->a.part + (size_t)b * ntiles + slot, 0, scratch);
   }
   // Re<V_i, out> over this tile for i < dot_nv (FP64 accumulation, the order fixed); V_{dot_nv - 1} is S, whose
   // products the stores accumulated, as they did |out|^2 (value dot_nv with dot_self).  Each wave reduces its
@@ -932,7 +1029,7 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
   // then serves all of them (the waves read their next V_i while others still compute).
   template <int NT>
   DBAR_D void dots(const Acc& acc, const cx<T>* v, int b, int row, int jt, int tile, int ntiles,
-                   double* scratch) const {
+                   double* scratch, const Pre& p) const {
     using G = LineGeom<N>;
     const LineArgs& a = this->a;
     const int nv = a.dot_nv;
@@ -940,13 +1037,17 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
     const int nval = nv + (a.dot_self ? 1 : 0);
     // vectors below the entry's Gram-Schmidt window (never V_{nv - 1}, the input itself)
     const int skip = (a.dot_full && !a.dot_full[b]) ? a.dot_skip : 0;
-    const cx<T>* V = static_cast<const cx<T>*>(a.dotV) + (size_t)b * a.dotV_bs + (size_t)row * N;
+    const cx<T>* V = static_cast<const cx<T>*>(a.dotV) + (size_t)b * a.dotV_bs;
     double* dst = a.dot_part + (size_t)b * nval * ntiles + tile;
+    const bool row_in = p.x.row(row);
     auto partial = [&](int i) {
-      const cx<T>* Vi = V + (size_t)i * N * N;
+      const Rsrc Vi = entry_rsrc<T, N>(V + (size_t)i * N * N);
       double p4[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int s = 0; s < G::RMAX; ++s) p4[s & 3] += rdot(Vi[jt + s * G::TPL], v[s]);
+      for (int s = 0; s < G::RMAX; ++s) {
+        const int pos = jt + s * G::TPL;
+        p4[s & 3] += rdot(box_load<T>(Vi, row * N + pos, row_in && p.x.col(pos)), v[s]);
+      }
       return (p4[0] + p4[1]) + (p4[2] + p4[3]);
     };
     if constexpr (NT >= 64) {
@@ -1018,6 +1119,10 @@ DBAR_D int xcd_swizzle(int bid, int nblk) {
 }
 
 
+// Boxed row launches with at least this many tiles give each XCD a contiguous range of them; with fewer, consecutive
+// blocks (tiles, then entries) simply go round the XCDs, which keeps all of them busy however few tiles a box has.
+constexpr int kSpreadTiles = 128;
+
 // Occupancy floor: at least 4 waves per SIMD (<= 128 VGPRs) for the wide column tiles, whose LDS allows two
 // blocks per CU only if the registers do too.
 template <int NT>
@@ -1034,24 +1139,42 @@ __global__ void __launch_bounds__(LINES * LineGeom<N>::TPL, MinWaves<LINES * Lin
   // pass-1 twiddle table: column stages only (their element work makes them arithmetic-bound)
   __shared__ cx<T> lds_t1[COLS ? Pass1Table<N>::SIZE : 1];
   constexpr int NTILES = N / LINES;
-  int b, tile;
-  if constexpr (Op::TILE_MAJOR) {
-    // one-dimensional grid of NTILES x B blocks; block i goes to XCD i mod 8, whose k-th block (k = i / 8) is entry
-    // k mod B of tile k / B within the XCD's contiguous range of tiles
-    const int i = blockIdx.x, nb = gridDim.x / NTILES;
-    if constexpr ((NTILES & 7) == 0) {
-      const int k = i >> 3;
-      tile = (i & 7) * (NTILES >> 3) + k / nb;
+  int b, tile, slot;
+  if constexpr (Op::BOXED && !COLS) {
+    // rows of the entry's box only: its cnt tiles from t0 on, partials in slots 0 .. cnt - 1; the launch covers the
+    // largest box of the batch.  With many tiles, block i of an entry goes to XCD i mod 8, which takes a contiguous
+    // eighth of them (neighbouring tiles share lines of the tiled array).  TILE_MAJOR: the entries of a tile follow one
+    // another on its XCD, i / 8 = (tile's place on the XCD) * entries + entry.
+    constexpr bool SPREAD = NTILES >= kSpreadTiles;
+    static_assert(SPREAD || !Op::TILE_MAJOR, "tile-major launches spread their tiles over the XCDs");
+    int k = SPREAD ? blockIdx.x >> 3 : blockIdx.x;
+    if constexpr (Op::TILE_MAJOR) {
+      const int nb = op.a.B;
       b = k % nb;
+      k /= nb;
     } else {
-      tile = i / nb;
-      b = i % nb;
+      b = blockIdx.y;
     }
+    if (!op.active(b)) return;
+    int t0 = 0, cnt = NTILES;
+    if (N >= kBoxMinN && op.a.box && !op.a.box_full) {
+      const Box<N> x = entry_box<N>(op.a, b);
+      t0 = x.r0 / LINES;
+      cnt = x.r1 / LINES - t0;
+    }
+    slot = k;
+    if constexpr (SPREAD) {
+      const int per = (cnt + 7) >> 3;
+      slot = (blockIdx.x & 7) * per + k;
+      if (k >= per) return;
+    }
+    if (slot >= cnt) return;
+    tile = t0 + slot;
   } else {
     b = blockIdx.y;
-    tile = xcd_swizzle(blockIdx.x, gridDim.x);
+    tile = slot = xcd_swizzle(blockIdx.x, gridDim.x);
+    if (!op.active(b)) return;
   }
-  if (!op.active(b)) return;
   typename Op::Pre pre;
   op.prologue(b, pre);
   const int tid = threadIdx.x;
@@ -1064,8 +1187,12 @@ __global__ void __launch_bounds__(LINES * LineGeom<N>::TPL, MinWaves<LINES * Lin
   typename Op::Acc acc{};
   cx<T> v[G::RMAX];
 #pragma unroll
-  for (int s = 0; s < G::RMAX; ++s) v[s] = op.load(b, line, jt + s * G::TPL);
-  if constexpr (Op::LOADACC) op.template loaded<NT>(acc, b, line, jt, v, tile, NTILES, reinterpret_cast<double*>(lds));
+  for (int s = 0; s < G::RMAX; ++s) {
+    if constexpr (Op::BOXED) v[s] = op.load(b, line, jt + s * G::TPL, pre);
+    else v[s] = op.load(b, line, jt + s * G::TPL);
+  }
+  if constexpr (Op::LOADACC)
+    op.template loaded<NT>(acc, b, line, jt, v, slot, NTILES, reinterpret_cast<double*>(lds), pre);
   // LDS: a row tile keeps each line contiguous (one line per wave or less); a column tile interleaves its lines
   // element by element, so that the lanes of a wave (consecutive columns) hit consecutive banks
   constexpr int LS = COLS ? LINES : 1;
@@ -1123,8 +1250,11 @@ __global__ void __launch_bounds__(LINES * LineGeom<N>::TPL, MinWaves<LINES * Lin
       else op.store(acc, b, line, jt + s * G::TPL, v[s]);
     }
   }
-  op.template finish<NT>(acc, b, tile, NTILES, reinterpret_cast<double*>(lds));
-  if constexpr (Op::DOTS) op.template dots<NT>(acc, v, b, line, jt, tile, NTILES, reinterpret_cast<double*>(lds));
+  op.template finish<NT>(acc, b, tile, slot, NTILES, reinterpret_cast<double*>(lds));
+  if constexpr (Op::DOTS && Op::BOXED)
+    op.template dots<NT>(acc, v, b, line, jt, slot, NTILES, reinterpret_cast<double*>(lds), pre);
+  else if constexpr (Op::DOTS)
+    op.template dots<NT>(acc, v, b, line, jt, slot, NTILES, reinterpret_cast<double*>(lds));
 }
 
 template <typename T, int N, bool COLS, class Op, int V = 0>
@@ -1133,7 +1263,15 @@ void launch_op(const LineArgs& a, hipStream_t s) {
   constexpr int NT = LINES * LineGeom<N>::TPL;
   Op op;
   op.a = a;
-  const dim3 grid = Op::TILE_MAJOR ? dim3((N / LINES) * a.B) : dim3(N / LINES, a.B);
+  int tiles = N / LINES;
+  if constexpr (Op::BOXED && !COLS) {
+    // the tiles of the largest box, rounded up to a sixteenth of the grid (captured graphs are kept per launch size):
+    // whole rounds of the eight XCDs where the tiles are spread over them
+    constexpr int STEP = N / LINES > 16 ? N / LINES / 16 : 1;
+    static_assert(N / LINES < kSpreadTiles || STEP % 8 == 0, "whole rounds");
+    if (a.box && !a.box_full) tiles = (a.box_rows / LINES + STEP - 1) / STEP * STEP;
+  }
+  const dim3 grid = Op::TILE_MAJOR ? dim3(tiles * a.B) : dim3(tiles, a.B);
   hipLaunchKernelGGL((k_lines<T, N, LINES, COLS, Op>), grid, dim3(NT), 0, s, op);
 }
 

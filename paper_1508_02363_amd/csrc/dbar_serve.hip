@@ -388,8 +388,10 @@ static void worker(dbar_session* s, SClass* cp) {
       (void)hipMemcpyAsync(c.tolv.p, c.h_tol.data(), c.cap * sizeof(double), hipMemcpyHostToDevice, c.stream);
       if (mixed) launch_convert<float, double>(w.Q64.p, n, w.Q32.p, n, n, c.cap, nm, 1.0, c.stream);
       c.P.rhs_x(w.Q64.p, n, w.V.p, V_bs, mixed, c.cap, nm, 0u, c.stream);  // the first basis vector
-      launch_reduce(static_cast<double*>(w.part_vec.p), 1, c.P.rhs_blocks(),
-                    static_cast<double*>(w.nred.p), c.cap, nm, c.stream);
+      TileSpan rhs_span;
+      rhs_span.stride = c.P.rhs_blocks();
+      launch_reduce(static_cast<double*>(w.part_vec.p), 1, rhs_span, static_cast<double*>(w.nred.p), c.cap, nm,
+                    c.stream);
       launch_ctl_check(w, 0.0, 1, nm, static_cast<const double*>(c.tolv.p), c.stream);
       launch_zero_done(w, nm, false, c.stream);  // admitted requests with b = 0: S = m = 0
     }

@@ -137,6 +137,11 @@ struct Work {
   // solve starts); this host mirror, updated from the flags the host reads anyway, tells whether a cycle's launches
   // must cover the whole basis.  Other entries keep their window inside such launches.
   std::vector<int> full_host;
+  // x-space solves: the potentials' index boxes (k_box_cut; one, or one per entry in serving) and their partial sums;
+  // host_box: the host's copy
+  DevBuf box, boxtmp;
+  PinnedInts host_box;
+  int setup_box();
   void* S_dst(int method) { return outS ? outS : method == 1 ? Fx.p : Sx.p; }
   void* m_dst() { return outm ? outm : mx.p; }
   PinnedInts host_act, host_live;
@@ -219,10 +224,17 @@ struct Pipeline {
   double* part_vec = nullptr;
   // apply / rhs act on s = F^{-1} S (the plain method's x-space form) instead of S
   bool xspace = false;
+  // x-space: the entries' boxes (LineArgs::box; null: the whole grid), the rows of the largest and its share of the grid
+  const int* box = nullptr;
+  int box_bs = 0, box_rows = 0;
+  double box_fr = 1.0, box_fc = 1.0;
+  // from the host's copy of the boxes (cnt of them, 4 ints each; use: which of them count, null: all)
+  void set_box(const int* dev, int bs, const int* host, int cnt, const int* use);
 
   LineArgs base(int B, const int* act, unsigned flags) const;
-  // tiles (blocks per entry) of the launch whose partials (norms, Gram-Schmidt products) apply leaves
-  int apply_tiles(bool fp64) const;
+  // tiles (blocks per entry) of the launch whose partials (norms, Gram-Schmidt products) apply leaves; full: it covered
+  // the whole grid (h wanted there)
+  TileSpan apply_tiles(bool fp64, bool full = false) const;
   // blocks per entry of rhs's norm partials
   int rhs_blocks() const;
   template <typename T>
@@ -305,7 +317,7 @@ int make_pipeline(const dbar_grid* g, Work& w, Pipeline* p);
 // e_k tables of B entries: FP64 ex/ey and their FP32 roundings ex32/ey32 (per-entry stride N)
 void launch_phase_tables(const c64* kv_dev, int N, double L, c64* ex, c64* ey, c32* ex32, c32* ey32, int B,
                          hipStream_t s);
-int run_batch(const Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vector<int>& iters_out);
+int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vector<int>& iters_out);
 // x-space: the residual evaluation's outputs (w.Sx, w.mx; with iterated also w.Fx, w.Ax) = 0 for entries that are
 // not live (and in mask, if given): those no residual evaluation writes
 void launch_zero_done(Work& w, const int* mask, bool iterated, hipStream_t s);

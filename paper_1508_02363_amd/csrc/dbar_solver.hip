@@ -53,14 +53,14 @@ DBAR_D double wsum(double x) {
 // Deterministic block reduction of one entry's partials: red[v] = sum_blk part[v * nblk + blk] for v < nval
 // (wave w sums the values v = w, w + NW, ...; lanes stride over the partials).  1024 threads.
 constexpr int kCtlThreads = 1024;
-// Values v >= nv1 come from part2 (v - nv1 of it, same nblk) when part2 is given.
+// Values v >= nv1 come from part2 (v - nv1 of it, same nblk) when part2 is given.  stride: between values' partials.
 template <int NT = kCtlThreads>
-DBAR_D void reduce_entry(const double* __restrict__ part, int nval, int nblk, double* red,
+DBAR_D void reduce_entry(const double* __restrict__ part, int nval, int nblk, int stride, double* red,
                          const double* __restrict__ part2 = nullptr, int nv1 = 0) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int v = wave; v < nval; v += NW) {
-    const double* p = (part2 && v >= nv1) ? part2 + (size_t)(v - nv1) * nblk : part + (size_t)v * nblk;
+    const double* p = (part2 && v >= nv1) ? part2 + (size_t)(v - nv1) * stride : part + (size_t)v * stride;
     // eight independent partial sums per lane: the loads of a chunk are in flight together
     double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     int i = lane;
@@ -99,20 +99,20 @@ DBAR_D void moments_combine(int b, const double* tot, double wscale, int M, c64*
 }
 
 // All kCtlThreads threads of the block.
-DBAR_D void moments_entry(int b, const double* part, int ntiles, double wscale, int M, c64* coefG, c64* dmom,
-                          c32* dmom32) {
+DBAR_D void moments_entry(int b, const double* part, const TileSpan& span, double wscale, int M, c64* coefG,
+                          c64* dmom, c32* dmom32) {
   constexpr int NV = 2 * kNMom;
   __shared__ double tot[NV];
-  reduce_entry(part + (size_t)b * NV * ntiles, NV, ntiles, tot);
+  reduce_entry(part + (size_t)b * NV * span.stride, NV, span.count(b), span.stride, tot);
   moments_combine(b, tot, wscale, M, coefG, dmom, dmom32);
 }
 
 // One block of kCtlThreads per entry.
-__global__ void __launch_bounds__(kCtlThreads) k_moments(const double* part, int ntiles, const int* act,
+__global__ void __launch_bounds__(kCtlThreads) k_moments(const double* part, TileSpan span, const int* act,
                                                          double wscale, int M, c64* coefG, c64* dmom, c32* dmom32) {
   const int b = blockIdx.x;
   if (act && !act[b]) return;
-  moments_entry(b, part, ntiles, wscale, M, coefG, dmom, dmom32);
+  moments_entry(b, part, span, wscale, M, coefG, dmom, dmom32);
 }
 
 // Column j of the Hessenberg matrix from hsum and beta = ||v_{j+1}|| (unnormalised basis: column j is sigma_j times the
@@ -154,12 +154,12 @@ DBAR_D void givens_commit(Ctl& c, int j, double beta) {
 // NT threads per entry: 256 while the step has at most 4 values (a windowed step), 1024 otherwise (a smaller block
 // starts sooner when another stream's line kernels hold most of every CU; the sums are the same either way)
 template <int NT>
-__global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, int nval, int nblk, int* act, int j,
+__global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, int nval, TileSpan span, int* act, int j,
                                                  int pass, int early, int m, int lo, int skip, const int* full) {
   const int b = blockIdx.x;
   if (!act[b]) return;
   __shared__ double red[kMaxRestart + 2];
-  reduce_entry<NT>(part + (size_t)b * nval * nblk, nval, nblk, red);
+  reduce_entry<NT>(part + (size_t)b * nval * span.stride, nval, span.count(b), span.stride, red);
   if (threadIdx.x == 0) {
     Ctl& c = ctl[b];
     double p2 = 0.0;
@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, i
 // threads of entry b's block.
 DBAR_D void givens_entry(int b, Ctl* ctl, const double* pnorm, int nblk, int* act, int j, int m) {
   __shared__ double red[1];
-  reduce_entry(pnorm + (size_t)b * nblk, 1, nblk, red);
+  reduce_entry(pnorm + (size_t)b * nblk, 1, nblk, nblk, red);
   if (threadIdx.x != 0) return;
   Ctl& c = ctl[b];
   const double beta = sqrt(fmax(red[0], 0.0));
@@ -216,16 +216,16 @@ __global__ void __launch_bounds__(kCtlThreads) k_ctl_givens(Ctl* ctl, const doub
 // 512 threads (a windowed step's moment sums take three rounds of its eight waves): a block of half a CU starts sooner
 // than one of kCtlThreads beside another stream's line kernels (same sums; measured 0.6% off the two-lane step)
 constexpr int kMomGivensThreads = 512;
-__global__ void __launch_bounds__(kMomGivensThreads) k_moments_givens(const double* part, int ntiles, double wscale,
-                                                                      int M,
-                                                                c64* coefG, c64* dmom, c32* dmom32, Ctl* ctl,
-                                                                const double* pnorm, int nblk, int* act, int j,
-                                                                int m) {
+__global__ void __launch_bounds__(kMomGivensThreads) k_moments_givens(const double* part, TileSpan span,
+                                                                      double wscale, int M, c64* coefG, c64* dmom,
+                                                                      c32* dmom32, Ctl* ctl, const double* pnorm,
+                                                                      int* act, int j, int m) {
   const int b = blockIdx.x;
   if (!act[b]) return;
   constexpr int NV = 2 * kNMom;
   __shared__ double tot[NV + 1];  // the moment sums, then |v_{j+1}|^2
-  reduce_entry<kMomGivensThreads>(part + (size_t)b * NV * ntiles, NV + 1, ntiles, tot, pnorm + (size_t)b * nblk, NV);
+  reduce_entry<kMomGivensThreads>(part + (size_t)b * NV * span.stride, NV + 1, span.count(b), span.stride, tot,
+                                  pnorm + (size_t)b * span.stride, NV);
   moments_combine(b, tot, wscale, M, coefG, dmom, dmom32);  // wave 0
   if (threadIdx.x == 64) {                                   // wave 1
     Ctl& c = ctl[b];
@@ -532,6 +532,7 @@ Work& Work::operator=(Work&& o) noexcept {
   live = std::move(o.live); kvals = std::move(o.kvals); results = std::move(o.results);
   shv = std::move(o.shv); unit = std::move(o.unit); Hbuf = std::move(o.Hbuf);
   Sx = std::move(o.Sx); mx = std::move(o.mx); Fx = std::move(o.Fx); Ax = std::move(o.Ax);
+  box = std::move(o.box); boxtmp = std::move(o.boxtmp); host_box = std::move(o.host_box);
   outS = o.outS; outm = o.outm; x_zero = o.x_zero;
   full_host = std::move(o.full_host);
   host_act = std::move(o.host_act); host_live = std::move(o.host_live);
@@ -608,6 +609,14 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   return DBAR_OK;
 }
 
+int Work::setup_box() {
+  const int cnt = Q_bs ? B : 1;
+  int rc;
+  if ((rc = box.ensure((size_t)cnt * 4 * sizeof(int)))) return rc;
+  if ((rc = boxtmp.ensure(box_scratch(N, cnt) * sizeof(double)))) return rc;
+  return host_box.ensure((size_t)cnt * 4);
+}
+
 static Work g_work;
 
 // ------------------------------------------------------------------------------------------------------------
@@ -639,7 +648,26 @@ LineArgs Pipeline::base(int B, const int* act, unsigned flags) const {
   a.coefG = coefG;
   a.dmom = dmom;
   a.dmom32 = dmom32;
+  a.box = box;
+  a.box_bs = box_bs;
+  a.box_rows = box_rows;
+  a.box_fr = box_fr;
+  a.box_fc = box_fc;
   return a;
+}
+
+void Pipeline::set_box(const int* dev, int bs, const int* host, int cnt, const int* use) {
+  box = dev;
+  box_bs = bs;
+  int rows = 0, cols = 0;
+  for (int b = 0; b < cnt; ++b) {
+    if (use && !use[b]) continue;
+    rows = std::max(rows, host[4 * b + 1] - host[4 * b]);
+    cols = std::max(cols, host[4 * b + 3] - host[4 * b + 2]);
+  }
+  box_rows = rows;
+  box_fr = (double)rows / N;
+  box_fc = (double)cols / N;
 }
 
 template <typename T>
@@ -664,8 +692,10 @@ void Pipeline::moments(const void* in, size_t in_bs, void* Tbuf, int B, const in
   launch_lines_any<T>(N, LineOp::ColsInvMoments, a, s);
   const double dx = 2.0 * kPi * L / N;
   TimerScope ts(kStageMoments, 0.0, B, act, s);
-  hipLaunchKernelGGL(k_moments, dim3(B), dim3(kCtlThreads), 0, s, part_mom, line_tiles(N, true, sizeof(T) == 8), act,
-                     dx * dx / (2.0 * kPi), M, coefG, dmom, dmom32);
+  TileSpan span;
+  span.stride = line_tiles(N, true, sizeof(T) == 8);
+  hipLaunchKernelGGL(k_moments, dim3(B), dim3(kCtlThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M, coefG,
+                     dmom, dmom32);
 }
 
 // out = alpha S_ep + beta i F(q conj(hh(in))) + gamma Y, with hh the regularised inverse of in/xi (or of in/(xi - a)
@@ -719,7 +749,14 @@ void Pipeline::apply(const void* in, size_t in_bs, void* out, size_t out_bs, con
                 dr);
 }
 
-int Pipeline::apply_tiles(bool fp64) const { return line_tiles(N, false, fp64); }  // both forms end on rows
+TileSpan Pipeline::apply_tiles(bool fp64, bool full) const {  // both forms end on rows
+  TileSpan t;
+  t.stride = line_tiles(N, false, fp64);
+  t.rows = N / t.stride;
+  t.box = full ? nullptr : box;
+  t.box_bs = box_bs;
+  return t;
+}
 int Pipeline::rhs_blocks() const { return xspace ? vec_blocks(n) : line_tiles(N, false, true); }
 
 // The operator on s = F^{-1} S.  With S = F s (F: cf phase FFT2, F^{-1}: ci phase IFFT2, F^{-1} F = identity),
@@ -750,13 +787,13 @@ void Pipeline::apply_x_first(const void* in, size_t in_bs, void* Tbuf, int B, co
   }
   launch_lines_any<T>(N, LineOp::RowsFwdMoments, a, s);
   const double dx = 2.0 * kPi * L / N;
-  const int tiles = line_tiles(N, false, sizeof(T) == 8);
+  const TileSpan span = apply_tiles(sizeof(T) == 8);
   TimerScope ts(kStageMoments, 0.0, B, act, s);
   if (u && u->ctl)
-    hipLaunchKernelGGL(k_moments_givens, dim3(B), dim3(kMomGivensThreads), 0, s, part_mom, tiles, dx * dx / (2.0 * kPi),
-                       M, coefG, dmom, dmom32, u->ctl, u->part, tiles, const_cast<int*>(act), u->j, u->m);
+    hipLaunchKernelGGL(k_moments_givens, dim3(B), dim3(kMomGivensThreads), 0, s, part_mom, span, dx * dx / (2.0 * kPi),
+                       M, coefG, dmom, dmom32, u->ctl, u->part, const_cast<int*>(act), u->j, u->m);
   else
-    hipLaunchKernelGGL(k_moments, dim3(B), dim3(kCtlThreads), 0, s, part_mom, tiles, act, dx * dx / (2.0 * kPi), M,
+    hipLaunchKernelGGL(k_moments, dim3(B), dim3(kCtlThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M,
                        coefG, dmom, dmom32);
 }
 
@@ -773,6 +810,7 @@ void Pipeline::apply_x_rest(const void* in, size_t in_bs, void* out, size_t out_
   a.out_bs = n;
   a.sout = xo ? xo->S : nullptr;
   a.sout_bs = n;
+  a.box_full = xo && xo->h ? 1 : 0;
   launch_lines_any<T>(N, LineOp::ColsFwdRegularInv, a, s);
   a.sout = nullptr;
   a.hout = xo ? xo->h : nullptr;
@@ -819,13 +857,19 @@ void Pipeline::apply_x(const void* in, size_t in_bs, void* out, size_t out_bs, c
 template <typename TO>
 __global__ void __launch_bounds__(256) k_rhs_x(const c64* Q, size_t Q_bs, const c64* ex, const c64* ey, size_t e_bs,
                                                int N, cx<TO>* out, size_t out_bs, double* part, int B,
-                                               const int* act) {
+                                               const int* act, const int* box, int box_bs) {
   const int b = blockIdx.y;
   if (b >= B || (act && !act[b])) return;
-  const size_t n = (size_t)N * N;
+  int r0 = 0, c0 = 0;
+  unsigned nr = N, nc = N;  // the box (a shared or per-entry one), else the whole grid
+  if (box) {
+    const int* x = box + (size_t)b * box_bs;
+    r0 = x[0], nr = x[1] - x[0], c0 = x[2], nc = x[3] - x[2];
+  }
   double acc = 0.0;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int pos = (int)(i / N), col = (int)(i % N);
+  for (unsigned e = blockIdx.x * blockDim.x + threadIdx.x; e < nr * nc; e += gridDim.x * blockDim.x) {
+    const int pos = r0 + (int)(e / nc), col = c0 + (int)(e % nc);
+    const size_t i = (size_t)pos * N + col;
     const c64 q = Q[(size_t)b * Q_bs + i] * (ex[(size_t)b * e_bs + col] * ey[(size_t)b * e_bs + pos]);
     const c64 v{q.im, -q.re};
     out[(size_t)b * out_bs + i] = cvt<TO>(v);
@@ -842,16 +886,17 @@ void Pipeline::rhs_x(const void* Q64p, size_t Q_bs, void* out, size_t out_bs, bo
                      unsigned flags, hipStream_t s) const {
   const LineArgs a = base(B, act, flags & kUnitPhase);
   // the potential counted once when the entries share it (Q_bs = 0)
-  TimerScope ts(kStageConvert, (double)n * ((Q_bs ? sizeof(c64) : 0) + (out32 ? sizeof(c32) : sizeof(c64))), B, act, s,
-                Q_bs ? 0.0 : (double)n * sizeof(c64));
+  const double nb = box_fr * box_fc * n;
+  TimerScope ts(kStageConvert, nb * ((Q_bs ? sizeof(c64) : 0) + (out32 ? sizeof(c32) : sizeof(c64))), B, act, s,
+                Q_bs ? 0.0 : nb * sizeof(c64));
   const dim3 grid(rhs_blocks(), B);
   const c64* Q = static_cast<const c64*>(Q64p);
   if (out32)
     hipLaunchKernelGGL(k_rhs_x<float>, grid, dim3(256), 0, s, Q, Q_bs, a.ex, a.ey, a.e_bs, N, static_cast<c32*>(out),
-                       out_bs, part_vec, B, act);
+                       out_bs, part_vec, B, act, box, box_bs);
   else
     hipLaunchKernelGGL(k_rhs_x<double>, grid, dim3(256), 0, s, Q, Q_bs, a.ex, a.ey, a.e_bs, N, static_cast<c64*>(out),
-                       out_bs, part_vec, B, act);
+                       out_bs, part_vec, B, act, box, box_bs);
 }
 
 // H(h) = -i F(Q conj(F^{-1}(h/(xi - a)))) (equation eqh2), into Hout
@@ -1177,14 +1222,15 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
       va.w_bs = V_bs;
       va.part = part;
       va.want_self = 0;
-      int nblk = P.apply_tiles(sizeof(T) == 8);  // pass 0: partials of the operator's last kernel
+      TileSpan span = P.apply_tiles(sizeof(T) == 8);  // pass 0: partials of the operator's last kernel
       if (pass > 0) {
         launch_dots<T>(va, s);
-        nblk = nvb;
+        span = TileSpan{};
+        span.stride = nvb;
       }
       {
         TimerScope ts(kStageControl, 0.0, B, nullptr, s);
-        launch_ctl_coef(j + 1, B, s, ctl, part, j + 1, nblk, act, j, pass, 0, w.m, 0, 0, nullptr);
+        launch_ctl_coef(j + 1, B, s, ctl, part, j + 1, span, act, j, pass, 0, w.m, 0, 0, nullptr);
       }
       va.coef = &ctl[0].coef[0];
       va.coef_bs = sizeof(Ctl) / sizeof(double);
@@ -1213,8 +1259,9 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
       uint64_t Lbits = 0;
       std::memcpy(&Lbits, &P.L, sizeof(Lbits));
       const Work::GraphKey key((int)sizeof(T) + 16 * cfg.method + 64 * (P.xspace ? 1 : 0), j * 1024 + j1,
-                               cfg.reorth + 16 * (fused ? window : 0) + 4096 * (any_full ? 1 : 0), B, P.N, P.M,
-                               Lbits);
+                               cfg.reorth + 16 * (fused ? window : 0) + 4096 * (any_full ? 1 : 0) +
+                                   8192 * (P.box ? 1 + (16 * P.box_rows + P.N - 1) / P.N : 0),
+                               B, P.N, P.M, Lbits);
       auto it = w.graphs.find(key);
       if (it != w.graphs.end()) {
         done = hipGraphLaunch(it->second, s) == hipSuccess;
@@ -1324,8 +1371,8 @@ void end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t s, i
     P.apply_x_rest<double>(w.x.p, n, sizeof(T) == 4 ? nullptr : r_out, r_bs, w.Q64.p, w.Q_bs, w.T64.p, B, live, -1.0,
                            -1.0, kYRhs, 0, true, s, nullptr, &xo, 0u, nullptr, 0);
   }
-  launch_reduce(static_cast<double*>(w.part_vec.p), 1, P.apply_tiles(true), static_cast<double*>(w.nred.p), B, live,
-                s);
+  launch_reduce(static_cast<double*>(w.part_vec.p), 1, P.apply_tiles(true, P.xspace && outputs),
+                static_cast<double*>(w.nred.p), B, live, s);
 }
 
 template int krylov_cycle<float>(const Pipeline&, Work&, const BatchCfg&, int, hipStream_t);
@@ -1372,7 +1419,7 @@ void launch_zero_done(Work& w, const int* mask, bool iterated, hipStream_t s) {
                      static_cast<const int*>(w.live.p), mask, w.n);
 }
 
-int run_batch(const Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vector<int>& iters_out) {
+int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vector<int>& iters_out) {
   const int B = w.B;
   const size_t n = w.n;
   const bool mixed = w.prec == DBAR_MIXED;
@@ -1388,7 +1435,11 @@ int run_batch(const Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, st
     P.rhs_x(w.Q64.p, w.Q_bs, w.V.p, n * (w.m + 1), mixed, B, nullptr, rhs_flags, s);
   else
     P.rhs(w.Q64.p, w.Q_bs, w.T64.p, static_cast<c64*>(w.bvec.p), B, nullptr, rhs_flags, s);
-  launch_reduce(static_cast<double*>(w.part_vec.p), 1, P.rhs_blocks(), nred, B, nullptr, s);
+  TileSpan rhs_span;
+  rhs_span.stride = P.rhs_blocks();
+  launch_reduce(static_cast<double*>(w.part_vec.p), 1, rhs_span, nred, B, nullptr, s);
+  if (P.box && hipMemcpyAsync(w.host_box.data(), P.box, 4 * sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess)
+    return fail(DBAR_EDEVICE, "hipMemcpyAsync failed");
   // x = 0: the x-space residual's first launch writes x = sum y_i V_i on the first update (no memset)
   w.x_zero = P.xspace;
   w.full_host.assign(B, 0);  // device flags: cleared by the first residual check below
@@ -1414,6 +1465,7 @@ int run_batch(const Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, st
     if (hipStreamSynchronize(s) != hipSuccess) return fail(DBAR_EDEVICE, "stream synchronize failed");
     bool any = false;
     for (int b = 0; b < B; ++b) any |= w.host_live[b] != 0;
+    if (P.box && total == 0) P.set_box(P.box, 0, w.host_box.data(), 1, nullptr);  // (read with the first flags)
     if (!any || total >= cfg.max_iter) break;
     const double rel = mixed ? cfg.inner_tol : 0.0;
     const double abs_tol = mixed ? 0.3 * cfg.tol : 0.5 * cfg.tol;
@@ -1679,6 +1731,12 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
         return fail(DBAR_EDEVICE, "Q upload failed");
     }
     if (o.precision == DBAR_MIXED) launch_convert<float, double>(w.Q64.p, 0, w.Q32.p, 0, n, 1, nullptr, 1.0, s);
+    if (cfg.xspace && cfg.reorth == 1 && N >= kBoxMinN) {
+      if ((rc = w.setup_box())) return rc;
+      launch_box(static_cast<const c64*>(w.Q64.p), 0, N, static_cast<double*>(w.boxtmp.p), static_cast<int*>(w.box.p),
+                 1, nullptr, s);
+      ln[l].P.box = static_cast<const int*>(w.box.p);
+    }
     if (cfg.method == 1 && (rc = w.Hbuf.ensure((size_t)Bl * n * sizeof(c64)))) return rc;
     if (cfg.xspace &&
         ((rc = w.Sx.ensure((size_t)Bl * n * sizeof(c64))) || (rc = w.mx.ensure((size_t)Bl * n * sizeof(c64)))))
@@ -1693,7 +1751,7 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
   auto run_lane = [&](int l) -> int {
     Work& w = *ln[l].w;
     const hipStream_t s = ln[l].s;
-    const Pipeline& P = ln[l].P;
+    Pipeline& P = ln[l].P;
     std::vector<EntryResult> hres(Bl);
     std::vector<int> shifts(2 * (size_t)Bl);
     int result = DBAR_OK;

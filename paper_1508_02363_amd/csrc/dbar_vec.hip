@@ -165,11 +165,13 @@ __global__ void __launch_bounds__(kVecBlock) k_convert(const TI* in, size_t in_b
 }
 
 // out[b][v] = sum_blk part[b][v][blk], fixed order
-__global__ void __launch_bounds__(256) k_reduce(const double* part, int nval, int nblk, double* out, const int* act) {
+__global__ void __launch_bounds__(256) k_reduce(const double* part, int nval, TileSpan span, double* out,
+                                                const int* act) {
   const int b = blockIdx.y, v = blockIdx.x;
   if (act && !act[b]) return;
   __shared__ double red[4];
-  const double* p = part + ((size_t)b * nval + v) * nblk;
+  const int nblk = span.count(b);
+  const double* p = part + ((size_t)b * nval + v) * span.stride;
   double s = 0.0;
   for (int i = threadIdx.x; i < nblk; i += 256) s += p[i];
   s = wave_sum(s);
@@ -203,9 +205,114 @@ void launch_convert(const void* in, size_t in_bs, void* out, size_t out_bs, size
   hipLaunchKernelGGL((k_convert<TO, TI>), dim3(blocks, B), dim3(kVecBlock), 0, s, static_cast<const TI*>(in), in_bs,
                      static_cast<TO*>(out), out_bs, n, act, scale);
 }
-void launch_reduce(const double* part, int nval, int nblk, double* out, int B, const int* act, hipStream_t s) {
-  TimerScope ts(kStageReduce, (double)nval * nblk * sizeof(double), B, act, s);
-  hipLaunchKernelGGL(k_reduce, dim3(nval, B), dim3(256), 0, s, part, nval, nblk, out, act);
+void launch_reduce(const double* part, int nval, const TileSpan& span, double* out, int B, const int* act,
+                   hipStream_t s) {
+  TimerScope ts(kStageReduce, (double)nval * span.stride * sizeof(double), B, act, s);
+  hipLaunchKernelGGL(k_reduce, dim3(nval, B), dim3(256), 0, s, part, nval, span, out, act);
+}
+
+// ------------------------------------------------------------------------------------------------------------
+// The index box of a potential
+// ------------------------------------------------------------------------------------------------------------
+// Energies |Q|^2 of 64 x 64 tiles, per row and per column of the tile: rowp[b][tile column][row],
+// colp[b][tile row][column] (grids below N = 64: one tile, its rows and columns beyond N empty).
+constexpr int kBoxTile = 64;
+__global__ void __launch_bounds__(256) k_box_sums(const c64* Q, size_t Q_bs, int N, double* tmp, const int* act) {
+  const int b = blockIdx.y;
+  if (act && !act[b]) return;
+  const int nt = (N + kBoxTile - 1) / kBoxTile;
+  const int tx = blockIdx.x % nt, ty = blockIdx.x / nt;
+  double* rowp = tmp + (size_t)b * 2 * nt * N;
+  double* colp = rowp + (size_t)nt * N;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = tx * kBoxTile + lane;
+  __shared__ double cs[4][kBoxTile];
+  double e[kBoxTile / 4], ce = 0.0;
+#pragma unroll
+  for (int i = 0; i < kBoxTile / 4; ++i) {
+    const int row = ty * kBoxTile + wave + 4 * i;
+    e[i] = col < N && row < N ? norm2(Q[(size_t)b * Q_bs + (size_t)row * N + col]) : 0.0;
+  }
+#pragma unroll
+  for (int i = 0; i < kBoxTile / 4; ++i) {
+    const int row = ty * kBoxTile + wave + 4 * i;
+    ce += e[i];
+    const double r = wave_sum(e[i]);
+    if (lane == 0 && row < N) rowp[(size_t)tx * N + row] = r;
+  }
+  cs[wave][lane] = ce;
+  __syncthreads();
+  if (wave == 0 && col < N)
+    colp[(size_t)ty * N + col] = (cs[0][lane] + cs[1][lane]) + (cs[2][lane] + cs[3][lane]);
+}
+
+// Rows (blockIdx.x = 0) or columns (1): the first and last whose removal from the edge inwards would leave out more
+// than kBoxCut of the energy on that side.  All four sides together leave out at most 4 kBoxCut = 2^-112 of |Q|^2,
+// 2^-56 of the 2-norm: an eighth of the rounding unit, below what rounding the values of Q to FP64 has left out
+// already.  A potential whose energy is not finite, or underflows, keeps the whole grid.
+constexpr double kBoxCut = 0x1p-114;
+__global__ void __launch_bounds__(1024) k_box_cut(const double* tmp, int N, int align, int* box, const int* act) {
+  const int b = blockIdx.y;
+  if (act && !act[b]) return;
+  const bool cols = blockIdx.x == 1;
+  const int nt = (N + kBoxTile - 1) / kBoxTile;
+  const double* p = tmp + (size_t)b * 2 * nt * N + (cols ? (size_t)nt * N : 0);
+  // thread t: lines t * per .. ; inclusive sums over the threads from both ends, then the lines of the thread where
+  // the sum passes the limit
+  constexpr int NT = 1024, PER = 4;
+  __shared__ double fw[NT], bw[NT];
+  __shared__ int lo, hi;
+  const int t = threadIdx.x, per = (N + NT - 1) / NT;
+  double e[PER] = {0.0, 0.0, 0.0, 0.0}, own = 0.0;
+  for (int i = 0; i < per; ++i) {
+    const int line = t * per + i;
+    if (line < N)
+      for (int k = 0; k < nt; ++k) e[i] += p[(size_t)k * N + line];
+    own += e[i];
+  }
+  fw[t] = own;
+  bw[t] = own;
+  if (t == 0) lo = 0, hi = N;
+  __syncthreads();
+  for (int off = 1; off < NT; off <<= 1) {
+    const double x = t >= off ? fw[t - off] : 0.0, y = t + off < NT ? bw[t + off] : 0.0;
+    __syncthreads();
+    fw[t] += x;
+    bw[t] += y;
+    __syncthreads();
+  }
+  const double total = fw[NT - 1], cut = kBoxCut * total;
+  if (total > 0x1p-900 && total < 0x1p900) {
+    // the thread that holds the first line beyond the cut, from either side
+    if (fw[t] > cut && (t == 0 || !(fw[t - 1] > cut))) {
+      double s = t == 0 ? 0.0 : fw[t - 1];
+      int i = 0;
+      while (i < per - 1 && s + e[i] <= cut) s += e[i++];
+      lo = t * per + i;
+    }
+    if (bw[t] > cut && (t == NT - 1 || !(bw[t + 1] > cut))) {
+      double s = t == NT - 1 ? 0.0 : bw[t + 1];
+      int i = per - 1;
+      while (i > 0 && s + e[i] <= cut) s += e[i--];
+      hi = t * per + i + 1;
+    }
+  }
+  __syncthreads();
+  if (t == 0) {
+    const int al = cols ? kBoxCols : align;
+    const int a = lo / al * al, z = hi < a + 1 ? a + 1 : hi;
+    int* dst = box + (size_t)b * 4 + (cols ? 2 : 0);
+    dst[0] = a;
+    dst[1] = (z + al - 1) / al * al < N ? (z + al - 1) / al * al : N;
+  }
+}
+
+size_t box_scratch(int N, int B) { return (size_t)B * 2 * ((N + kBoxTile - 1) / kBoxTile) * N; }
+void launch_box(const c64* Q, size_t Q_bs, int N, double* tmp, int* box, int B, const int* act, hipStream_t s) {
+  const int nt = (N + kBoxTile - 1) / kBoxTile;
+  TimerScope ts(kStageConvert, (double)N * N * sizeof(c64), B, act, s);
+  hipLaunchKernelGGL(k_box_sums, dim3(nt * nt, B), dim3(256), 0, s, Q, Q_bs, N, tmp, act);
+  hipLaunchKernelGGL(k_box_cut, dim3(2, B), dim3(1024), 0, s, tmp, N, box_row_align(N), box, act);
 }
 
 template void launch_dots<double>(const VecArgs&, hipStream_t);
