@@ -45,6 +45,28 @@ static int tile_cols(int variant) {
   }
 }
 
+// tiles of the column stage that leaves moment partials (its threads may limit its columns below the variant's)
+template <typename T, int N>
+static int moment_cols(int variant) {
+  using Tl = Tiling<T, N>;
+  constexpr int E = Ept<T, N>::MOMENT_COLS;
+  switch (variant) {
+    case 1: return Tl::template cols_of<E, 1, true>();
+    case 2: return Tl::template cols_of<E, 2, true>();
+    case 3: return Tl::template cols_of<E, 3, true>();
+    default: return Tl::template cols_of<E, 0, true>();
+  }
+}
+
+int moment_tiles(int N, bool fp64) {
+  const int v = tile_variant(N, fp64);
+#define DBAR_TILES(NN) \
+  if (N == NN) return NN / (fp64 ? moment_cols<double, NN>(v) : moment_cols<float, NN>(v));
+  DBAR_FOR_EACH_N(DBAR_TILES)
+#undef DBAR_TILES
+  return 0;
+}
+
 int line_tiles_variant(int N, bool cols, bool fp64, int variant) {
 #define DBAR_TILES(NN)                                                                               \
   if (N == NN) {                                                                                     \

@@ -1,7 +1,7 @@
-// Line FFTs for gfx950: Stockham autosort radix-16 passes with LDS exchanges.
+// Line FFTs for gfx950: Stockham autosort radix-4/8/16 passes with LDS exchanges.
 //
 // A "line" is one row or one column of an N x N complex array.  TPL = N / RMAX threads cooperate on a line
-// (RMAX = 16, or N when N < 16).  Thread jt of a line always holds, in registers, the elements at positions
+// (RMAX = 4, 8 or 16 elements per thread, by stage).  Thread jt of a line always holds, in registers, the elements at positions
 //     jt + s * TPL,   s = 0 .. RMAX-1
 // before and after every pass.  Consequently the first pass loads straight from global memory and the last pass
 // leaves the transformed line in registers in the same position pattern; only the exchanges between passes go
@@ -10,7 +10,7 @@
 //
 // Pass (R, NS): butterfly j (0 <= j < N/R) reads positions j + r N/R, multiplies element r by W^{r (j mod NS)} with
 // W = exp(DIR 2 pi i / (NS R)), does an R-point DFT and writes element r to (j / NS) NS R + (j mod NS) + r NS.
-// Radix sequence: 16, 16, ..., then 2/4/8 for the remainder (N = 2^p, 8 <= N <= 4096).
+// Radix sequence: RMAX, RMAX, ..., then the remainder (N = 2^p, 8 <= N <= 4096).
 // DIR = -1 is the forward transform sum_j x_j e^{-2 pi i jm/N}; DIR = +1 the unnormalised inverse.
 #pragma once
 
@@ -151,70 +151,64 @@ DBAR_D void dft(cx<T>* x) {
 // Line geometry
 // ------------------------------------------------------------------------------------------------------------
 
-template <int N>
+// E: elements per thread (the largest radix), 4, 8 or 16
+template <int N, int E>
 struct LineGeom {
   static_assert(N >= 8 && N <= 4096 && (N & (N - 1)) == 0, "N must be a power of two in [8, 4096]");
-  static constexpr int RMAX = N < 16 ? N : 16;
+  static_assert(E == 4 || E == 8 || E == 16, "radix 4, 8 or 16");
+  static constexpr int log2(int n) { return n <= 1 ? 0 : 1 + log2(n / 2); }
+  static constexpr int RMAX = N < E ? N : E;
   static constexpr int TPL = N / RMAX;  // threads per line
-  static constexpr int LOG = (N >= 4096)   ? 12
-                             : (N >= 2048) ? 11
-                             : (N >= 1024) ? 10
-                             : (N >= 512)  ? 9
-                             : (N >= 256)  ? 8
-                             : (N >= 128)  ? 7
-                             : (N >= 64)   ? 6
-                             : (N >= 32)   ? 5
-                             : (N >= 16)   ? 4
-                                           : 3;
-  static constexpr int P16 = N < 16 ? 0 : LOG / 4;             // number of radix-16 passes
-  static constexpr int REM = N < 16 ? N : (1 << (LOG % 4));    // last radix (1 = none)
-  static constexpr int NPASS = P16 + (REM > 1 ? 1 : 0);
+  static constexpr int LOG = log2(N), LOGR = log2(RMAX);
+  static constexpr int PFULL = LOG / LOGR;          // number of radix-RMAX passes
+  static constexpr int REM = 1 << (LOG % LOGR);     // last radix (1 = none)
+  static constexpr int NPASS = PFULL + (REM > 1 ? 1 : 0);
   // LDS padding: one element every 16 keeps strided Stockham writes from piling onto the same banks
   static constexpr int padded(int n) { return n + (n >> 4); }
   static constexpr int LDS_LINE = padded(N);
+  static constexpr int size() { return N; }
 };
 
 // radix and NS of pass number `pass`
-template <int N, int PASS>
+template <class G, int PASS>
 struct PassInfo {
-  using G = LineGeom<N>;
-  static constexpr int R = (PASS < G::P16) ? 16 : G::REM;
+  static constexpr int R = (PASS < G::PFULL) ? G::RMAX : G::REM;
   static constexpr int NS = [] {
     int ns = 1;
-    for (int p = 0; p < PASS; ++p) ns *= (p < G::P16 ? 16 : G::REM);
+    for (int p = 0; p < PASS; ++p) ns *= (p < G::PFULL ? G::RMAX : G::REM);
     return ns;
   }();
 };
 
-// Twiddles of pass 1 (NS = 16, radix R1): W_N^{r k N/(16 R1)} = W_{16 R1}^{r k} for r < R1, k < 16, whatever N is.
-// Kept in LDS as t1[(r - 1) * 16 + k] (r-major: the lanes of a wave, consecutive k, read consecutive banks).
-template <int N>
+// Twiddles of pass 1 (NS = RMAX, radix R1): W_N^{r k N/(RMAX R1)} = W_{RMAX R1}^{r k} for r < R1, k < RMAX, whatever N
+// is.  Kept in LDS as t1[(r - 1) * RMAX + k] (r-major: the lanes of a wave, consecutive k, read consecutive banks).
+template <class G>
 struct Pass1Table {
-  static constexpr bool USED = LineGeom<N>::NPASS > 1;
-  static constexpr int R1 = USED ? PassInfo<N, 1>::R : 2;
-  static constexpr int SIZE = (R1 - 1) * 16;
+  static constexpr bool USED = G::NPASS > 1;
+  static constexpr int R1 = USED ? PassInfo<G, 1>::R : 2;
+  static constexpr int SIZE = (R1 - 1) * G::RMAX;
 };
 
 // Fill the pass-1 table from the global twiddle table exp(-2 pi i m / N) (all threads of the block; ordered before
 // its first use by the barriers of pass 0's exchange).
-template <typename T, int N>
+template <typename T, class G>
 DBAR_D void fill_pass1_table(cx<T>* __restrict__ t1, const cx<T>* __restrict__ tw, int tid, int nt) {
-  using P1 = Pass1Table<N>;
+  using P1 = Pass1Table<G>;
   if constexpr (P1::USED) {
     for (int t = tid; t < P1::SIZE; t += nt) {
-      const int r = t / 16 + 1, k = t % 16;
-      t1[t] = tw[r * k * (N / (16 * P1::R1))];
+      const int r = t / G::RMAX + 1, k = t % G::RMAX;
+      t1[t] = tw[r * k * (G::size() / (G::RMAX * P1::R1))];
     }
   }
 }
 
 // One Stockham pass in registers (twiddle + DFT).  v[s] holds position jt + s*TPL.  T1: pass 1 reads its twiddles
 // from the LDS table t1 (kernels bound by arithmetic) instead of forming them from tw (kernels bound by memory).
-template <typename T, int N, int PASS, int DIR, bool T1>
+template <typename T, class G, int PASS, int DIR, bool T1>
 DBAR_D void fft_pass_regs(cx<T>* v, int jt, const cx<T>* __restrict__ tw, const cx<T>* __restrict__ t1) {
-  using G = LineGeom<N>;
-  constexpr int R = PassInfo<N, PASS>::R;
-  constexpr int NS = PassInfo<N, PASS>::NS;
+  constexpr int N = G::size();
+  constexpr int R = PassInfo<G, PASS>::R;
+  constexpr int NS = PassInfo<G, PASS>::NS;
   constexpr int NB = G::RMAX / R;  // butterflies per thread
   constexpr int TS = N / (NS * R); // twiddle table stride
 #pragma unroll
@@ -223,11 +217,11 @@ DBAR_D void fft_pass_regs(cx<T>* v, int jt, const cx<T>* __restrict__ tw, const 
     cx<T> b[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) b[r] = v[q + r * NB];
-    if constexpr (T1 && PASS == 1 && NS == 16) {
-      const int k = j % 16;
+    if constexpr (T1 && PASS == 1) {
+      const int k = j % NS;
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        const cx<T> t = t1[(r - 1) * 16 + k];
+        const cx<T> t = t1[(r - 1) * NS + k];
         b[r] = b[r] * (DIR < 0 ? t : conj(t));
       }
     } else if constexpr (NS > 1) {
@@ -259,11 +253,10 @@ DBAR_D void fft_pass_regs(cx<T>* v, int jt, const cx<T>* __restrict__ tw, const 
 // Write the output of pass PASS to LDS (its Stockham destination positions) ...  Element p of a line lives at
 // line[padded(p) * LS]: LS = 1 for a line of its own, LS = lines per tile when the lines of a column tile are
 // interleaved element by element (the threads of one wave then touch consecutive addresses across the tile's lines)
-template <typename T, int N, int PASS, int LS>
+template <typename T, class G, int PASS, int LS>
 DBAR_D void lds_store_pass(cx<T>* __restrict__ line, const cx<T>* v, int jt) {
-  using G = LineGeom<N>;
-  constexpr int R = PassInfo<N, PASS>::R;
-  constexpr int NS = PassInfo<N, PASS>::NS;
+  constexpr int R = PassInfo<G, PASS>::R;
+  constexpr int NS = PassInfo<G, PASS>::NS;
   constexpr int NB = G::RMAX / R;
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
@@ -275,9 +268,8 @@ DBAR_D void lds_store_pass(cx<T>* __restrict__ line, const cx<T>* v, int jt) {
 }
 
 // ... and read the input pattern of the next pass.
-template <typename T, int N, int LS>
+template <typename T, class G, int LS>
 DBAR_D void lds_load_line(const cx<T>* __restrict__ line, cx<T>* v, int jt) {
-  using G = LineGeom<N>;
 #pragma unroll
   for (int s = 0; s < G::RMAX; ++s) v[s] = line[G::padded(jt + s * G::TPL) * LS];
 }
@@ -285,26 +277,17 @@ DBAR_D void lds_load_line(const cx<T>* __restrict__ line, cx<T>* v, int jt) {
 // Full line transform: registers in (positions jt + s*TPL), registers out (same positions, transformed).
 // `line` is this line's LDS buffer (LDS_LINE elements at stride LS).  Must be called by all threads of the block
 // (barriers).
-template <typename T, int N, int DIR, int LS, bool T1>
+template <typename T, class G, int DIR, int LS, bool T1, int PASS = 0>
 DBAR_D void line_fft(cx<T>* v, int jt, cx<T>* __restrict__ line, const cx<T>* __restrict__ tw,
                      const cx<T>* __restrict__ t1) {
-  using G = LineGeom<N>;
-  fft_pass_regs<T, N, 0, DIR, T1>(v, jt, tw, t1);
-  if constexpr (G::NPASS > 1) {
-    lds_store_pass<T, N, 0, LS>(line, v, jt);
+  fft_pass_regs<T, G, PASS, DIR, T1>(v, jt, tw, t1);
+  if constexpr (PASS + 1 < G::NPASS) {
+    lds_store_pass<T, G, PASS, LS>(line, v, jt);
     __syncthreads();
-    lds_load_line<T, N, LS>(line, v, jt);
+    lds_load_line<T, G, LS>(line, v, jt);
     __syncthreads();
-    fft_pass_regs<T, N, 1, DIR, T1>(v, jt, tw, t1);
+    line_fft<T, G, DIR, LS, T1, PASS + 1>(v, jt, line, tw, t1);
   }
-  if constexpr (G::NPASS > 2) {
-    lds_store_pass<T, N, 1, LS>(line, v, jt);
-    __syncthreads();
-    lds_load_line<T, N, LS>(line, v, jt);
-    __syncthreads();
-    fft_pass_regs<T, N, 2, DIR, T1>(v, jt, tw, t1);
-  }
-  static_assert(G::NPASS <= 3, "N <= 4096 needs at most three passes");
 }
 
 }  // namespace dbar

@@ -108,6 +108,7 @@ int box_row_align(int N);
 // sized for the default (narrowest, most tiles) choice.
 int line_tiles(int N, bool cols, bool fp64);
 int line_tiles_variant(int N, bool cols, bool fp64, int variant);
+int moment_tiles(int N, bool fp64);  // tiles of ColsInvMoments (the stride of its partials) with the current choice
 int line_tiles_max(int N, bool cols, bool fp64);  // the most tiles over the variants (sizes partial buffers)
 // Column-tile width choice per (N, precision): the number of valid variants (0: the default width; then up to two
 // wider tiles, 2x and 4x, while the block has at most 1024 threads and its LDS fits; then half the default width),

@@ -231,9 +231,40 @@ DBAR_D void block_reduce_store(const double (&vals)[NV], double* __restrict__ ds
 // ------------------------------------------------------------------------------------------------------------
 // Tiling
 // ------------------------------------------------------------------------------------------------------------
+// Elements per thread of the line kernels (the radix of their passes), by stage, precision and grid size.  Sixteen
+// need the fewest passes and exchanges; eight and four put two and four times as many waves on a line, each with a
+// shorter serial chain (the tails above all) and fewer registers.  The choice depends on nothing but the stage, the
+// precision and the grid size: an entry's result is the same in any batch.
+constexpr int by_n(int N, int e32, int e64, int e128, int e256, int e512, int e1024, int e2048, int e4096) {
+  return N <= 32 ? e32 : N <= 64 ? e64 : N <= 128 ? e128 : N <= 256 ? e256 : N <= 512 ? e512 : N <= 1024 ? e1024
+         : N <= 2048 ? e2048 : e4096;
+}
+// Measured (one entry / a full batch, launch times in us; 16 -> 8 -> 4 elements per thread):
+//   tails, FP64:   N = 128 25 -> 17 -> 13 / 1024 entries 179 -> 179 -> 180;  N = 512 27 -> 17 -> 13 / 45 entries
+//                  82 -> 80 -> 73;  N = 1024 28 -> 20 -> 17 / 8 entries 61 -> 60 -> 53;  N = 2048 35 -> 41 -> 53
+//   tails, FP32:   N = 256 14 -> 11 -> 10 / 16 entries 15 -> 12 -> 11;  N = 512 15 -> 12 -> 9 / 9 entries
+//                  17 -> 14 -> 13;  N = 1024 15 -> 13 -> 10 / 8 entries 24.5 -> 26 -> 28
+//   moments, FP64: N = 64 19 -> 15 / 4096 entries 270 -> 317;  N = 128 17 -> 12 / 151 -> 136 -> 211 (the wave reduction of the moments costs the same whatever a
+//                  thread holds);  N = 256 15 -> 13 -> 12 / 63 entries 27 -> 35 -> 30;  N = 512 16 -> 13 / 54 -> 51
+//   moments, FP32: N = 256 15 -> 12 -> 10;  N = 512 14 -> 11 / 9 entries 17 -> 13.5;  N = 2048 19 -> 17 / 40 -> 37
+//   division, FP64: N = 256 15 -> 12.5 / 44 -> 39;  N = 512 15 -> 12.5 -> 13 / 88 -> 77 -> 109;  N = 1024 19 -> 17.5
+//   division, FP32: N = 128 12.5 -> 10.5 -> 9;  N = 512 13 -> 10 / 17.4 -> 16;  N = 1024 15 -> 14 / 33 -> 41
+template <typename T, int N>
+struct Ept {
+  static constexpr bool D = sizeof(T) == 8;
+  static constexpr int FWD_MOMENTS = D ? by_n(N, 4, 16, 8, 4, 8, 8, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 8, 8, 16);
+  static constexpr int TAIL_ROWS = D ? by_n(N, 4, 4, 4, 4, 4, 4, 16, 16) : by_n(N, 4, 4, 4, 4, 4, 16, 16, 16);
+  static constexpr int REG_COLS = D ? by_n(N, 4, 8, 8, 8, 8, 8, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 16, 16, 16);
+  // the stages of the operator on S itself (one application, N = 64: 70 -> 38 us; N = 1024: 99 -> 87 us)
+  static constexpr int MOMENT_COLS = by_n(N, 4, 4, 4, 8, 8, 8, 16, 16);
+  static constexpr int TAIL_COLS = by_n(N, 4, 4, 4, 4, 4, 4, 16, 16);
+  static constexpr int ROWS = by_n(N, 4, 4, 4, 4, 4, 8, 16, 16);  // the row stages with light work per element
+  static constexpr int COLS = by_n(N, 4, 4, 4, 8, 8, 8, 16, 16);  // the column stages with light work per element
+};
+
 template <typename T, int N>
 struct Tiling {
-  using G = LineGeom<N>;
+  using G = LineGeom<N, 16>;
   static constexpr int cmin(int a, int b) { return a < b ? a : b; }
   static constexpr int cmax(int a, int b) { return a > b ? a : b; }
   static constexpr int kLdsBudget = 150 * 1024;
@@ -241,14 +272,16 @@ struct Tiling {
     while (lines > 1 && lines * G::LDS_LINE * (int)sizeof(cx<T>) > kLdsBudget) lines /= 2;
     return lines;
   }
-  static constexpr int ROWS = fit(cmin(N, cmax(1, 128 / G::TPL)));
+  // Lines of a row tile: enough blocks to spread one entry of a small grid over the chip, two lines in FP32 at N = 1024,
+  // where each leaves half of a line of the tiled array
+  static constexpr int ROWS = cmin(N, N <= 64 ? 16 : N <= 256 ? 4 : N <= 512 ? 2 : N <= 1024 && sizeof(T) == 4 ? 2 : 1);
   // (FP32 at N = 4096: the LDS holds four full-height lines, but a four-line tile needs more than the 128 VGPRs of
   // four waves per SIMD and spills 72 bytes per lane; two lines fit without a spill and run faster)
   static constexpr int COLS = sizeof(T) == 4 && N >= 4096 ? 2
                                                           : fit(cmin(N, cmax(64 / (int)sizeof(cx<T>), cmax(1, 64 / G::TPL))));
-  // Column-tile variants for the tuner: 0 = COLS (the default), then the wider tiles COLS << 1, COLS << 2 while the
-  // block has at most 1024 threads and the tile's lines fit the LDS budget, then the narrower tile COLS / 2 (more
-  // blocks per CU where one full-height tile fills most of the LDS, as at N = 4096).
+  // Column-tile variants for the tuner: 0 = COLS (the default), then the wider tiles COLS << 1, COLS << 2 while a block
+  // of sixteen elements per thread has at most 1024 threads and the tile's lines fit the LDS budget, then the narrower
+  // tile COLS / 2 (more blocks per CU where one full-height tile fills most of the LDS, as at N = 4096).
   static constexpr bool wide_ok(int c) {
     return c <= N && c * G::TPL <= 1024 && c * G::LDS_LINE * (int)sizeof(cx<T>) <= kLdsBudget;
   }
@@ -259,6 +292,12 @@ struct Tiling {
   static constexpr int cols_v() { return V == 0 ? COLS : V <= NWIDE ? (COLS << V) : COLS / 2; }
   template <int V>
   static constexpr bool cols_valid() { return V < variants(); }
+  // the columns a stage of E elements per thread takes of a variant: at most 1024 threads, and with moments at most
+  // 512 / N on small grids (more blocks for the one entry an application has there, and the reduction's scratch)
+  template <int E, int V, bool MOMENTS>
+  static constexpr int cols_of() {
+    return cmin(cmin(cols_v<V>(), MOMENTS ? cmin(16, cmax(4, 512 / N)) : N), 1024 / (N / cmin(N, E)));
+  }
   // Tile width of the FP32 transform array (t_index): the default column tile, but at least 8 columns, so that the
   // row launches move 64-byte pieces.  At N = 4096 the column tile is 2 columns (4 at most); 2- or 4-column pieces
   // cost the row launches more (they leave partial lines) than the narrow column tiles gain from whole pieces.
@@ -281,17 +320,17 @@ DBAR_D size_t t_index(int row, int col) {
 }
 
 // LDS of one line-kernel block: the line data, or the scratch of its reductions, whichever is larger
-template <typename T, int N, int LINES, bool COLS>
+template <typename T, class G, int LINES, bool COLS, bool MOMENTS>
 struct LdsSize {
-  static constexpr int TPL = LineGeom<N>::TPL;
+  static constexpr int TPL = G::TPL;
   static constexpr int NT = LINES * TPL;
-  static constexpr int kData = LINES * LineGeom<N>::LDS_LINE * (int)sizeof(cx<T>);
+  static constexpr int kData = LINES * G::LDS_LINE * (int)sizeof(cx<T>);
   static constexpr int LN = LINES;
   static constexpr int kScratchReduce = (NT >= 64 ? NT / 64 : NT) * 2 * kNMom * (int)sizeof(double);
   // the moment reduction's groups (MomentsBase::finish_kk): runs of min(TPL, 64) lanes of a row; on a column tile
   // (wave, column) pairs when the block has whole waves and fewer than 64 columns, else single threads
   static constexpr int NG = COLS ? ((NT >= 64 && LN < 64) ? (NT / 64) * LN : NT) : NT / (TPL < 64 ? TPL : 64);
-  static constexpr int kScratchMoments = (NG * 2 * (kMaxM + 1) + LN * 2 * kNMom + LN * 2 * (kMaxM + 1)) * 8;
+  static constexpr int kScratchMoments = !MOMENTS ? 0 : (NG * 2 * (kMaxM + 1) + LN * 2 * kNMom + LN * 2 * (kMaxM + 1)) * 8;
   static constexpr int kScratch = kScratchReduce > kScratchMoments ? kScratchReduce : kScratchMoments;
   static constexpr int kElems = ((kData > kScratch ? kData : kScratch) + (int)sizeof(cx<T>) - 1) / (int)sizeof(cx<T>);
 };
@@ -343,8 +382,9 @@ DBAR_D Box<N> entry_box(const LineArgs& a, int b) {
 // ------------------------------------------------------------------------------------------------------------
 struct NoAcc {};
 
-template <typename T, int N>
+template <typename T, int N, int E>
 struct OpBase {
+  using G = LineGeom<N, E>;
   static constexpr bool ROLLED = false;  // heavy per-element epilogue: process through LDS in a rolled loop
   LineArgs a;
   // the blocks of one tile for every entry of the batch are dispatched together, on one XCD (k_lines): for stages
@@ -363,6 +403,8 @@ struct OpBase {
   static constexpr bool LOADACC = false;
   // ROLLED stores: > 1: the op's store_all stores the thread's elements GROUP at a time, else store one at a time
   static constexpr int GROUP = 1;
+  // the op leaves moment partials (its block reduction needs their scratch)
+  static constexpr bool MOMENTS = false;
   // the op works on the entry's box (row launches cover its rows only); its load and loaded take the Pre
   static constexpr bool BOXED = false;
   // per-block data read once at kernel start, before any store (ops that need it define PRE and a Pre type)
@@ -373,7 +415,7 @@ struct OpBase {
 
 // out = IFFT_rows(phase * ci * in)
 template <typename T, int N>
-struct OpRowsInvScaled : OpBase<T, N> {
+struct OpRowsInvScaled : OpBase<T, N, Ept<T, N>::ROWS> {
   static constexpr int DIR1 = +1;
   static constexpr bool TWO = false;
   using Acc = NoAcc;
@@ -403,8 +445,10 @@ DBAR_D void halve_exchange(T (&x)[32], int lane) {
   }
 }
 
-template <typename T, int N, bool ALONG_X>
-struct MomentsBase : OpBase<T, N> {
+template <typename T, int N, bool ALONG_X, int E>
+struct MomentsBase : OpBase<T, N, E> {
+  using G = LineGeom<N, E>;
+  static constexpr bool MOMENTS = true;
   static constexpr int NV = 2 * kNMom;
   static constexpr int NMU = 2 * (kMaxM + 1);  // mu_0 .. mu_kMaxM (re, im)
   // Per-thread moments are accumulated in the transform's precision (16 elements per thread; the FP32 operator's s
@@ -449,7 +493,6 @@ struct MomentsBase : OpBase<T, N> {
   }
   template <int KK>
   DBAR_D void add_all(Acc& acc, int b, int jt, const cx<T>* v) const {
-    using G = LineGeom<N>;
 #pragma unroll
     for (int s = 0; s < G::RMAX; ++s) {
       const int pos = jt + s * G::TPL;
@@ -506,14 +549,14 @@ struct MomentsBase : OpBase<T, N> {
   DBAR_D void finish_kk(Acc& acc, int b, int tile, int slot, int ntiles, double* scratch) const {
     constexpr int NU = 2 * (KK + 1);  // mu values in use
     double* dst = this->a.part + (size_t)b * NV * ntiles + slot;
-    constexpr int TPL = LineGeom<N>::TPL;
+    constexpr int TPL = G::TPL;
     constexpr int LN = NT / TPL;  // lines per tile
     // reduction groups: runs of GS consecutive lanes on a row tile; (wave, column) pairs on a column tile of fewer
     // than 64 columns (SHFL), else single threads
     constexpr int GS = ALONG_X ? (TPL < 64 ? TPL : 64) : 1;
     constexpr bool SHFL = !ALONG_X && NT >= 64 && LN < 64;
     constexpr int NG = ALONG_X ? NT / GS : SHFL ? (NT / 64) * LN : NT;
-    static_assert(NG == LdsSize<T, N, LN, !ALONG_X>::NG, "LDS scratch sized for another reduction layout");
+    static_assert(NG == LdsSize<T, G, LN, !ALONG_X, true>::NG, "LDS scratch sized for another reduction layout");
     __syncthreads();  // scratch aliases the transform's LDS
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double* sc = scratch;                 // [NG][NMU]
@@ -593,11 +636,11 @@ struct MomentsBase : OpBase<T, N> {
 
 // IFFT_cols(in) and the moments of the result (second pass of F^{-1} S; nothing is stored)
 template <typename T, int N>
-struct OpColsInvMoments : MomentsBase<T, N, false> {
+struct OpColsInvMoments : MomentsBase<T, N, false, Ept<T, N>::MOMENT_COLS> {
   static constexpr int DIR1 = +1;
   static constexpr bool TWO = false;
   static constexpr bool ROLLED = true;
-  using Acc = typename MomentsBase<T, N, false>::Acc;
+  using Acc = typename MomentsBase<T, N, false, Ept<T, N>::MOMENT_COLS>::Acc;
   DBAR_D cx<T> load(int b, int col, int pos) const { return this->inp(b)[(size_t)pos * N + col]; }
   DBAR_D void store(Acc& acc, int b, int col, int pos, cx<T> v) const { this->add(acc, b, col, pos, v); }
 };
@@ -608,14 +651,15 @@ struct OpColsInvMoments : MomentsBase<T, N, false> {
 // Gram-Schmidt step that produced s (with its |s|^2 partials in upd_part[b][tile]), or the solution update
 // x += sum y_i V_i of a cycle end (upd_sign -1) -- the operator's first launch reads s anyway.
 template <typename T, int N>
-struct OpRowsFwdMoments : MomentsBase<T, N, true> {
+struct OpRowsFwdMoments : MomentsBase<T, N, true, Ept<T, N>::FWD_MOMENTS> {
+  using G = LineGeom<N, Ept<T, N>::FWD_MOMENTS>;
   static constexpr int DIR1 = -1;
   static constexpr bool TWO = false;
   static constexpr bool LOADACC = true;
   static constexpr bool BOXED = true;
   static constexpr bool PRE = true;
   using Pre = Box<N>;
-  using Acc = typename MomentsBase<T, N, true>::Acc;
+  using Acc = typename MomentsBase<T, N, true, Ept<T, N>::FWD_MOMENTS>::Acc;
   DBAR_D void prologue(int b, Pre& p) const { p = entry_box<N>(this->a, b); }
   DBAR_D cx<T> load(int b, int row, int pos, const Pre& p) const {
     return box_load<T>(entry_rsrc<T, N>(this->inp(b)), row * N + pos, p.col(pos));
@@ -623,7 +667,6 @@ struct OpRowsFwdMoments : MomentsBase<T, N, true> {
   template <int NT>
   DBAR_D void loaded(Acc& acc, int b, int row, int jt, cx<T>* v, int slot, int ntiles, double* scratch,
                      const Pre& p) const {
-    using G = LineGeom<N>;
     const LineArgs& a = this->a;
     if (a.upd_coef) {
       const double* coef = a.upd_coef + (size_t)b * a.upd_coef_bs;
@@ -744,7 +787,7 @@ DBAR_D cx<T> regularised(const LineArgs& a, const RegPre& p, int row, int pos, c
 }
 
 template <typename T, int N>
-struct OpRowsInvRegular : OpBase<T, N> {
+struct OpRowsInvRegular : OpBase<T, N, Ept<T, N>::ROWS> {
   static constexpr int DIR1 = +1;
   static constexpr bool TWO = false;
   using Acc = NoAcc;
@@ -760,7 +803,7 @@ struct OpRowsInvRegular : OpBase<T, N> {
 // R = (S - G)/xi, then out = IFFT_cols(phase ci R), between the two column transforms (rolled through LDS: the FP64
 // G terms)
 template <typename T, int N>
-struct OpColsFwdRegInv : OpBase<T, N> {
+struct OpColsFwdRegInv : OpBase<T, N, Ept<T, N>::REG_COLS> {
   static constexpr int DIR1 = -1;
   static constexpr bool TWO = true;
   static constexpr bool ROLLED = true;
@@ -791,8 +834,8 @@ struct OpColsFwdRegInv : OpBase<T, N> {
 };
 
 // r = IFFT_cols(in); h = r + tail; [hout = h]; u = q_k conj(h); out = FFT_cols(u)   (TAILONLY: stop after hout)
-template <typename T, int N, bool TAILONLY>
-struct OpColsInvTail : OpBase<T, N> {
+template <typename T, int N, bool TAILONLY, int E = Ept<T, N>::TAIL_COLS>
+struct OpColsInvTail : OpBase<T, N, E> {
   static constexpr int DIR1 = +1;
   static constexpr bool TWO = !TAILONLY;
   static constexpr bool ROLLED = true;
@@ -846,7 +889,8 @@ struct OpColsInvTail : OpBase<T, N> {
 
 // X = FFT_rows(in); out = alpha S + beta cf phase X + gamma Y; optional |out|^2 partials
 template <typename T, int N>
-struct OpRowsFwdEpilogue : OpBase<T, N> {
+struct OpRowsFwdEpilogue : OpBase<T, N, Ept<T, N>::ROWS> {
+  using G = LineGeom<N, Ept<T, N>::ROWS>;
   static constexpr int DIR1 = -1;
   static constexpr bool TWO = false;
   static constexpr bool DOTS = true;
@@ -885,7 +929,6 @@ struct OpRowsFwdEpilogue : OpBase<T, N> {
   template <int NT>
   DBAR_D void dots(const Acc& acc, const cx<T>* v, int b, int row, int jt, int tile, int ntiles,
                    double* scratch) const {
-    using G = LineGeom<N>;
     const LineArgs& a = this->a;
     if (a.dot_nv <= 0) return;
     const cx<T>* V = static_cast<const cx<T>*>(a.dotV) + (size_t)b * a.dotV_bs + (size_t)row * N;
@@ -913,7 +956,9 @@ struct OpRowsFwdEpilogue : OpBase<T, N> {
 // optional |out|^2 partials, h itself (hout) and the products Re<V_i, out> of the first Gram-Schmidt pass.
 // Rows keep every global access of the epilogue and the products contiguous across a wave.
 template <typename T, int N>
-struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
+struct OpRowsInvTailEpi : OpColsInvTail<T, N, false, Ept<T, N>::TAIL_ROWS> {
+  using Base = OpColsInvTail<T, N, false, Ept<T, N>::TAIL_ROWS>;
+  using G = LineGeom<N, Ept<T, N>::TAIL_ROWS>;
   static constexpr int DIR1 = +1;
   static constexpr bool TWO = false;
   static constexpr bool ROLLED = true;
@@ -923,11 +968,11 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
   // measured 2-4% slower per launch, and the entry-major order stays
   static constexpr bool TILE_MAJOR = N >= 4096;
   static constexpr bool BOXED = true;
-  struct Pre : OpColsInvTail<T, N, false>::Pre {
+  struct Pre : Base::Pre {
     Box<N> x;
   };
   DBAR_D void prologue(int b, Pre& p) const {
-    OpColsInvTail<T, N, false>::prologue(b, p);
+    Base::prologue(b, p);
     p.x = entry_box<N>(this->a, b);
   }
   struct Acc {
@@ -941,13 +986,12 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
   // four at a time: wider groups hold more registers than the loads in flight repay (the FP32 launch drops to three
   // waves per SIMD at eight)
   static constexpr int GROUP_W = 4;
-  static constexpr int GROUP = LineGeom<N>::RMAX < GROUP_W ? LineGeom<N>::RMAX : GROUP_W;
+  static constexpr int GROUP = G::RMAX < GROUP_W ? G::RMAX : GROUP_W;
   struct GroupIn {
     cx<T> q[GROUP], s[GROUP], y[GROUP], ex[GROUP];
   };
   // the group's q (times the x factor of e_k on the plain operator), S and Y (zero outside the box)
   DBAR_D void group_load(GroupIn& g, int b, int row, int jt, int s0, const bool (&in)[GROUP]) const {
-    using G = LineGeom<N>;
     const LineArgs& a = this->a;
     const Rsrc Qb = entry_rsrc<T, N>(static_cast<const cx<T>*>(a.Q) + (size_t)b * a.Q_bs);
     const Rsrc Sb = entry_rsrc<T, N>(static_cast<const cx<T>*>(a.S) + (size_t)b * a.S_bs);
@@ -967,7 +1011,6 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
   }
   template <int LS>
   DBAR_D void store_all(Acc& acc, int b, int row, int jt, cx<T>* my, const Pre& p) const {
-    using G = LineGeom<N>;
     static_assert(G::RMAX % GROUP == 0, "whole groups");
     const LineArgs& a = this->a;
     const size_t base = (size_t)row * N;
@@ -1030,7 +1073,6 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
   template <int NT>
   DBAR_D void dots(const Acc& acc, const cx<T>* v, int b, int row, int jt, int tile, int ntiles,
                    double* scratch, const Pre& p) const {
-    using G = LineGeom<N>;
     const LineArgs& a = this->a;
     const int nv = a.dot_nv;
     if (nv <= 0) return;
@@ -1086,7 +1128,7 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false> {
 
 // out = FFT_cols(Q e_k)
 template <typename T, int N>
-struct OpColsFwdPotential : OpBase<T, N> {
+struct OpColsFwdPotential : OpBase<T, N, Ept<T, N>::COLS> {
   static constexpr int DIR1 = -1;
   static constexpr bool TWO = false;
   using Acc = NoAcc;
@@ -1100,7 +1142,7 @@ struct OpColsFwdPotential : OpBase<T, N> {
 
 // out = FFT_cols(in) (DIR -1) or IFFT_cols(in) (DIR +1)
 template <typename T, int N, int DIR>
-struct OpColsPlain : OpBase<T, N> {
+struct OpColsPlain : OpBase<T, N, Ept<T, N>::COLS> {
   static constexpr int DIR1 = DIR;
   static constexpr bool TWO = false;
   using Acc = NoAcc;
@@ -1125,19 +1167,19 @@ constexpr int kSpreadTiles = 128;
 
 // Occupancy floor: at least 4 waves per SIMD (<= 128 VGPRs) for the wide column tiles, whose LDS allows two
 // blocks per CU only if the registers do too.
-template <int NT>
+template <int NT, bool COLS, bool MOMENTS>
 struct MinWaves {
-  static constexpr int value = NT >= 256 ? 4 : 1;
+  static constexpr int value = COLS && NT >= 256 ? (MOMENTS ? NT / 256 : 4) : 1;
 };
 
 template <typename T, int N, int LINES, bool COLS, class Op>
-__global__ void __launch_bounds__(LINES * LineGeom<N>::TPL, MinWaves<LINES * LineGeom<N>::TPL>::value)
+__global__ void __launch_bounds__((LINES * Op::G::TPL), (MinWaves<LINES * Op::G::TPL, COLS, Op::MOMENTS>::value))
     k_lines(Op op) {
-  using G = LineGeom<N>;
+  using G = typename Op::G;
   constexpr int NT = LINES * G::TPL;
-  __shared__ cx<T> lds[LdsSize<T, N, LINES, COLS>::kElems];
+  __shared__ cx<T> lds[LdsSize<T, G, LINES, COLS, Op::MOMENTS>::kElems];
   // pass-1 twiddle table: column stages only (their element work makes them arithmetic-bound)
-  __shared__ cx<T> lds_t1[COLS ? Pass1Table<N>::SIZE : 1];
+  __shared__ cx<T> lds_t1[COLS ? Pass1Table<G>::SIZE : 1];
   constexpr int NTILES = N / LINES;
   int b, tile, slot;
   if constexpr (Op::BOXED && !COLS) {
@@ -1182,7 +1224,7 @@ __global__ void __launch_bounds__(LINES * LineGeom<N>::TPL, MinWaves<LINES * Lin
   const int jt = COLS ? (tid / LINES) : (tid % G::TPL);
   const int line = tile * LINES + ln;
   const cx<T>* tw = static_cast<const cx<T>*>(op.a.tw);
-  if constexpr (COLS) fill_pass1_table<T, N>(lds_t1, tw, tid, NT);
+  if constexpr (COLS) fill_pass1_table<T, G>(lds_t1, tw, tid, NT);
 
   typename Op::Acc acc{};
   cx<T> v[G::RMAX];
@@ -1197,7 +1239,7 @@ __global__ void __launch_bounds__(LINES * LineGeom<N>::TPL, MinWaves<LINES * Lin
   // element by element, so that the lanes of a wave (consecutive columns) hit consecutive banks
   constexpr int LS = COLS ? LINES : 1;
   cx<T>* my = COLS ? lds + ln : lds + ln * G::LDS_LINE;
-  line_fft<T, N, Op::DIR1, LS, COLS>(v, jt, my, tw, lds_t1);
+  line_fft<T, G, Op::DIR1, LS, COLS>(v, jt, my, tw, lds_t1);
   // Heavy per-element work (FP64 moments, the closed-form tail) runs in a rolled loop over values parked in LDS at
   // the thread's own positions: registers stay low (occupancy) and no barrier is needed until the next exchange.
   if constexpr (Op::TWO) {
@@ -1222,7 +1264,7 @@ __global__ void __launch_bounds__(LINES * LineGeom<N>::TPL, MinWaves<LINES * Lin
         else op.template mid<typename Op::Acc>(b, line, jt + s * G::TPL, v[s]);
       }
     }
-    line_fft<T, N, -Op::DIR1, LS, COLS>(v, jt, my, tw, lds_t1);
+    line_fft<T, G, -Op::DIR1, LS, COLS>(v, jt, my, tw, lds_t1);
   }
   if constexpr (Op::ROLLED && !Op::TWO) {
 #pragma unroll
@@ -1259,8 +1301,8 @@ __global__ void __launch_bounds__(LINES * LineGeom<N>::TPL, MinWaves<LINES * Lin
 
 template <typename T, int N, bool COLS, class Op, int V = 0>
 void launch_op(const LineArgs& a, hipStream_t s) {
-  constexpr int LINES = COLS ? Tiling<T, N>::template cols_v<V>() : Tiling<T, N>::ROWS;
-  constexpr int NT = LINES * LineGeom<N>::TPL;
+  constexpr int LINES = COLS ? Tiling<T, N>::template cols_of<Op::G::RMAX, V, Op::MOMENTS>() : Tiling<T, N>::ROWS;
+  constexpr int NT = LINES * Op::G::TPL;
   Op op;
   op.a = a;
   int tiles = N / LINES;

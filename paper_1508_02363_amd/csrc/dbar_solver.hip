@@ -693,7 +693,7 @@ void Pipeline::moments(const void* in, size_t in_bs, void* Tbuf, int B, const in
   const double dx = 2.0 * kPi * L / N;
   TimerScope ts(kStageMoments, 0.0, B, act, s);
   TileSpan span;
-  span.stride = line_tiles(N, true, sizeof(T) == 8);
+  span.stride = moment_tiles(N, sizeof(T) == 8);
   hipLaunchKernelGGL(k_moments, dim3(B), dim3(kCtlThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M, coefG,
                      dmom, dmom32);
 }
