@@ -50,42 +50,36 @@ DBAR_D double wsum(double x) {
 }
 
 
-// Deterministic block reduction of one entry's partials: red[v] = sum_blk part[v * nblk + blk] for v < nval
-// (wave w sums the values v = w, w + NW, ...; lanes stride over the partials).  1024 threads.
-constexpr int kCtlThreads = 1024;
-// Values v >= nv1 come from part2 (v - nv1 of it, same nblk) when part2 is given.  stride: between values' partials.
-template <int NT = kCtlThreads>
-DBAR_D void reduce_entry(const double* __restrict__ part, int nval, int nblk, int stride, double* red,
-                         const double* __restrict__ part2 = nullptr, int nv1 = 0) {
-  constexpr int NW = NT / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int v = wave; v < nval; v += NW) {
-    const double* p = (part2 && v >= nv1) ? part2 + (size_t)(v - nv1) * stride : part + (size_t)v * stride;
-    // eight independent partial sums per lane: the loads of a chunk are in flight together
-    double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    int i = lane;
-    for (; i + 7 * 64 < nblk; i += 8 * 64) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] += p[i + u * 64];
-    }
-    for (; i < nblk; i += 64) a[0] += p[i];
-    double acc = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-    acc = wsum(acc);
-    if (lane == 0) red[v] = acc;
-  }
-  __syncthreads();
+// lane l's x in every lane (l uniform: a register read, not a trip through LDS as __shfl is)
+DBAR_D double bcast(double x, int l) {
+  const long long v = __builtin_bit_cast(long long, x);
+  const unsigned lo = __builtin_amdgcn_readlane((int)v, l), hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// d_n = w sum_tiles part, c_n = (-i/2)^n d_n / n! (equation fourreeg4 with Gchoice), R(0) = (-i/2) dt, for entry b,
-// from the reduced tile sums tot: thread n < kNMom forms slot n ((-i/2)^n = (-i)^n 2^-n exactly).
-DBAR_D void moments_combine(int b, const double* tot, double wscale, int M, c64* coefG, c64* dmom, c32* dmom32) {
-  const int n = threadIdx.x;
-  if (n >= kNMom) return;
-  const c64 d{wscale * tot[2 * n], wscale * tot[2 * n + 1]};
+// sum of p[0 .. nblk) over one wave (every lane gets it), in an order fixed by nblk.  Eight independent partial sums
+// per lane: the loads of a chunk are in flight together.
+DBAR_D double wave_reduce(const double* __restrict__ p, int nblk) {
+  double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  int i = threadIdx.x & 63;
+  for (; i + 7 * 64 < nblk; i += 8 * 64) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u] += p[i + u * 64];
+  }
+#pragma unroll
+  for (int u = 0; u < 7; ++u)
+    if (i + u * 64 < nblk) a[u] += p[i + u * 64];
+  return wsum(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
+}
+
+// Taylor slot n of entry b from the sums (re, im) of its moment: d_n = w sum, c_n = (-i/2)^n d_n / n! (equation
+// fourreeg4 with Gchoice; (-i/2)^n = (-i)^n 2^-n exactly), slot kMaxM + 1: the conj(z) moment, R(0) = (-i/2) dt.
+DBAR_D void moments_slot(int b, int n, c64 sum, double wscale, int M, c64* coefG, c64* dmom, c32* dmom32) {
+  const c64 d = wscale * sum;
   c64* cg = coefG + (size_t)b * kNMom;
   c64* dm = dmom + (size_t)b * kNMom;
   c32* dm32 = dmom32 + (size_t)b * kNMom;
-  if (n == kMaxM + 1) {  // the conj(z) moment: R(0) = (-i/2) dt
+  if (n == kMaxM + 1) {
     cg[n] = c64{0.0, -0.5} * d;
     dm[n] = d;
     dm32[n] = cvt<float>(d);
@@ -98,46 +92,90 @@ DBAR_D void moments_combine(int b, const double* tot, double wscale, int M, c64*
   cg[n] = n <= M ? kInvFactC[n] * (p * d) : c64{0.0, 0.0};
 }
 
-// All kCtlThreads threads of the block.
-DBAR_D void moments_entry(int b, const double* part, const TileSpan& span, double wscale, int M, c64* coefG,
-                          c64* dmom, c32* dmom32) {
-  constexpr int NV = 2 * kNMom;
-  __shared__ double tot[NV];
-  reduce_entry(part + (size_t)b * NV * span.stride, NV, span.count(b), span.stride, tot);
-  moments_combine(b, tot, wscale, M, coefG, dmom, dmom32);
+// The moment reduction is split over blocks, two Taylor slots each (one wave per real sum), kMomBlocks per entry: the
+// slots do not depend on each other, and a small block starts at once where one that reduces all 34 sums waits for half
+// a CU and takes as long as its waves' several rounds.  Measured with the Givens step of the same launch (the wave-wide
+// step below): N = 128, one entry 7.2 -> 3.5 us; N = 4096, 4 entries 29 -> 8.6 us.
+constexpr int kMomThreads = 256;
+constexpr int kMomBlocks = (kNMom + 1) / 2;
+DBAR_D void moments_pair(int b, int g, const double* part, const TileSpan& span, double wscale, int M, c64* coefG,
+                         c64* dmom, c32* dmom32) {
+  const int wave = threadIdx.x >> 6, n = 2 * g + (wave >> 1);
+  __shared__ double tot[4];
+  if (n < kNMom && (n <= M || n == kMaxM + 1)) {  // (beyond the order: slots of zeros)
+    const double* p = part + ((size_t)b * 2 * kNMom + 2 * n + (wave & 1)) * span.stride;
+    const double x = wave_reduce(p, span.count(b));
+    if ((threadIdx.x & 63) == 0) tot[wave] = x;
+  } else if ((threadIdx.x & 63) == 0) {
+    tot[wave] = 0.0;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2 && 2 * g + (int)threadIdx.x < kNMom)
+    moments_slot(b, 2 * g + threadIdx.x, c64{tot[2 * threadIdx.x], tot[2 * threadIdx.x + 1]}, wscale, M, coefG, dmom,
+                 dmom32);
 }
 
-// One block of kCtlThreads per entry.
-__global__ void __launch_bounds__(kCtlThreads) k_moments(const double* part, TileSpan span, const int* act,
+__global__ void __launch_bounds__(kMomThreads) k_moments(const double* part, TileSpan span, const int* act,
                                                          double wscale, int M, c64* coefG, c64* dmom, c32* dmom32) {
-  const int b = blockIdx.x;
+  const int b = blockIdx.y;
   if (act && !act[b]) return;
-  moments_entry(b, part, span, wscale, M, coefG, dmom, dmom32);
+  moments_pair(b, blockIdx.x, part, span, wscale, M, coefG, dmom, dmom32);
+}
+
+// One Hessenberg column in a wave's registers: lane i holds sigma_i, hsum_i and rotation i, and the rotations run
+// through all of them with register reads (a single thread that walks the record in memory waits for each term).
+struct HessLane {
+  double cs, sn, raw;  // raw: the column's entry i before the rotations, sigma_j hsum_i
+  int first;           // the first entry that can be nonzero after them (rotation i mixes entries i and i + 1)
+};
+DBAR_D HessLane hess_lane(const Ctl& c, int j, double hsum) {
+  const int lane = threadIdx.x & 63;
+  HessLane h;
+  h.cs = lane < j ? c.cs[lane] : 1.0;
+  h.sn = lane < j ? c.sn[lane] : 0.0;
+  h.raw = lane <= j ? c.sigma[j] * hsum : 0.0;
+  const unsigned long long nz = __ballot(h.raw != 0.0);
+  const int f = nz ? __builtin_ctzll(nz) : j;
+  h.first = f > 0 ? f - 1 : 0;
+  return h;
+}
+// entry j of the rotated column (every lane); mine: entry `lane` for lane < j
+DBAR_D double hess_rotate(const HessLane& h, int j, double& mine) {
+  const int lane = threadIdx.x & 63;
+  double top = bcast(h.raw, h.first);
+  mine = 0.0;
+  for (int i = h.first; i < j; ++i) {
+    const double c = bcast(h.cs, i), s = bcast(h.sn, i), next = bcast(h.raw, i + 1);
+    if (lane == i) mine = c * top + s * next;
+    top = -s * top + c * next;
+  }
+  return top;
 }
 
 // Column j of the Hessenberg matrix from hsum and beta = ||v_{j+1}|| (unnormalised basis: column j is sigma_j times the
 // products of A v_j), the previous Givens rotations applied, the new rotation, g and the residual estimate |g_{j+1}|.
-DBAR_D void givens_commit(Ctl& c, int j, double beta) {
-  const double sj = c.sigma[j];
+// One whole wave (top, mine: hess_rotate's); returns the estimate.
+DBAR_D double givens_commit(Ctl& c, int j, double beta, double top, double mine) {
+  const int lane = threadIdx.x & 63;
   double* col = c.H + (size_t)j * (kMaxRestart + 1);
-  for (int i = 0; i <= j; ++i) col[i] = sj * c.hsum[i];
-  col[j + 1] = sj * beta;
-  c.sigma[j + 1] = beta > 0.0 ? 1.0 / beta : 0.0;
-  for (int i = 0; i < j; ++i) {
-    const double t = c.cs[i] * col[i] + c.sn[i] * col[i + 1];
-    col[i + 1] = -c.sn[i] * col[i] + c.cs[i] * col[i + 1];
-    col[i] = t;
+  const double sub = c.sigma[j] * beta, gj = c.g[j];
+  const double den = hypot(top, sub);
+  const double cs = den > 0.0 ? top / den : 1.0, sn = den > 0.0 ? sub / den : 0.0;
+  const double resid = fabs(-sn * gj);
+  if (lane < j) col[lane] = mine;
+  if (lane == 0) {
+    col[j] = den;
+    col[j + 1] = 0.0;
+    c.sigma[j + 1] = beta > 0.0 ? 1.0 / beta : 0.0;
+    c.cs[j] = cs;
+    c.sn[j] = sn;
+    c.g[j + 1] = -sn * gj;
+    c.g[j] = cs * gj;
+    c.resid = resid;
+    c.jn = j + 1;
+    c.iters += 1;
   }
-  const double den = hypot(col[j], col[j + 1]);
-  c.cs[j] = den > 0.0 ? col[j] / den : 1.0;
-  c.sn[j] = den > 0.0 ? col[j + 1] / den : 0.0;
-  col[j] = den;
-  col[j + 1] = 0.0;
-  c.g[j + 1] = -c.sn[j] * c.g[j];
-  c.g[j] = c.cs[j] * c.g[j];
-  c.resid = fabs(c.g[j + 1]);
-  c.jn = j + 1;
-  c.iters += 1;
+  return resid;
 }
 
 // Gram-Schmidt pass `pass` of step j: h_i = <v_i, w> from the partials, coef_i = sigma_i^2 h_i (the basis is kept
@@ -151,37 +189,44 @@ DBAR_D void givens_commit(Ctl& c, int j, double beta) {
 // waits for the exact norm from the update, as without `early`.
 // The partials cover the vectors lo..j; an entry whose own window starts later (full[b] == 0 with skip > 0: the launch
 // covers the whole basis for entries that orthogonalise fully) takes the vectors lo + skip..j only.
-// NT threads per entry: 256 while the step has at most 4 values (a windowed step), 1024 otherwise (a smaller block
-// starts sooner when another stream's line kernels hold most of every CU; the sums are the same either way)
+// NT threads per entry, one wave per value at a time: 256 while the step has at most 4 values (a windowed step), 1024
+// otherwise (a smaller block starts sooner when another stream's line kernels hold most of every CU; the sums are the
+// same either way)
 template <int NT>
 __global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, int nval, TileSpan span, int* act, int j,
                                                  int pass, int early, int m, int lo, int skip, const int* full) {
   const int b = blockIdx.x;
   if (!act[b]) return;
   __shared__ double red[kMaxRestart + 2];
-  reduce_entry<NT>(part + (size_t)b * nval * span.stride, nval, span.count(b), span.stride, red);
-  if (threadIdx.x == 0) {
-    Ctl& c = ctl[b];
-    double p2 = 0.0;
-    const int lob = lo + ((full && !full[b]) ? skip : 0);
-    for (int i = 0; i < lob; ++i) c.coef[i] = c.hsum[i] = 0.0;  // outside the window (one pass)
-    for (int i = lob; i <= j; ++i) {
-      const double h = red[i - lo];
-      c.coef[i] = c.sigma[i] * c.sigma[i] * h;
-      c.hsum[i] = (pass ? c.hsum[i] : 0.0) + c.sigma[i] * h;
-      p2 += c.hsum[i] * c.hsum[i];
-    }
-    if (early) {
-      const double wn2 = red[j - lo + 1], b2 = wn2 - p2;
-      if (b2 > 1e-4 * wn2) {
-        const double beta = sqrt(b2), sj = c.sigma[j];
-        // column j's last entry after the previous rotations, without touching the record
-        double top = sj * c.hsum[0];
-        for (int i = 0; i < j; ++i) top = -c.sn[i] * top + c.cs[i] * (sj * c.hsum[i + 1]);
-        const double sub = sj * beta, den = hypot(top, sub);
-        const double resid = den > 0.0 ? fabs(sub / den * c.g[j]) : 0.0;
-        if (resid <= c.thresh || j + 1 >= m) {
-          givens_commit(c, j, beta);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nblk = span.count(b);
+  for (int v = wave; v < nval; v += NT / 64) {
+    const double x = wave_reduce(part + ((size_t)b * nval + v) * span.stride, nblk);
+    if (lane == 0) red[v] = x;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  Ctl& c = ctl[b];
+  const int lob = lo + ((full && !full[b]) ? skip : 0);
+  const bool in = lane >= lob && lane <= j;  // outside the window (one pass): zero
+  const double sg = in ? c.sigma[lane] : 0.0, h = in ? red[lane - lo] : 0.0;
+  const double hsum = in ? (pass ? c.hsum[lane] : 0.0) + sg * h : 0.0;
+  if (lane <= j) {
+    c.coef[lane] = sg * sg * h;
+    c.hsum[lane] = hsum;
+  }
+  if (early) {
+    const double wn2 = red[j - lo + 1], b2 = wn2 - wsum(hsum * hsum);
+    if (b2 > 1e-4 * wn2) {
+      const double beta = sqrt(b2);
+      double mine;
+      const HessLane hl = hess_lane(c, j, hsum);
+      const double top = hess_rotate(hl, j, mine);
+      // the residual estimate with this beta, without touching the record
+      const double sub = c.sigma[j] * beta, den = hypot(top, sub);
+      const double resid = den > 0.0 ? fabs(sub / den * c.g[j]) : 0.0;
+      if (resid <= c.thresh || j + 1 >= m) {
+        givens_commit(c, j, beta, top, mine);
+        if (lane == 0) {
           act[b] = 0;
           if (resid > c.thresh) act[gridDim.x + b] = 1;  // stopped by the restart length
         }
@@ -191,79 +236,68 @@ __global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, i
 }
 
 // Column j of the Hessenberg matrix from hsum and beta = ||w_new|| (reduced from the update's partials), Givens
-// rotation, residual estimate; the entry leaves the cycle when the estimate meets its threshold.  All kCtlThreads
-// threads of entry b's block.
-DBAR_D void givens_entry(int b, Ctl* ctl, const double* pnorm, int nblk, int* act, int j, int m) {
-  __shared__ double red[1];
-  reduce_entry(pnorm + (size_t)b * nblk, 1, nblk, nblk, red);
-  if (threadIdx.x != 0) return;
+// rotation, residual estimate; the entry leaves the cycle when the estimate meets its threshold.  One wave of B entries.
+DBAR_D void givens_entry(int b, int B, Ctl* ctl, const double* pnorm, int nblk, int stride, int* act, int j, int m) {
   Ctl& c = ctl[b];
-  const double beta = sqrt(fmax(red[0], 0.0));
-  givens_commit(c, j, beta);
-  if (c.resid <= c.thresh || j + 1 >= m || beta == 0.0) act[b] = 0;
-  if (c.resid > c.thresh && j + 1 >= m && beta != 0.0) act[gridDim.x + b] = 1;  // stopped by the restart length
+  const int lane = threadIdx.x & 63;
+  const double hsum = lane <= j ? c.hsum[lane] : 0.0;
+  const HessLane hl = hess_lane(c, j, hsum);
+  double mine;
+  const double top = hess_rotate(hl, j, mine);
+  const double beta = sqrt(fmax(wave_reduce(pnorm + (size_t)b * stride, nblk), 0.0));
+  const double resid = givens_commit(c, j, beta, top, mine);
+  if (lane == 0) {
+    if (resid <= c.thresh || j + 1 >= m || beta == 0.0) act[b] = 0;
+    if (resid > c.thresh && j + 1 >= m && beta != 0.0) act[B + b] = 1;  // stopped by the restart length
+  }
 }
 
-__global__ void __launch_bounds__(kCtlThreads) k_ctl_givens(Ctl* ctl, const double* pnorm, int nblk, int* act, int j,
-                                                            int m) {
+__global__ void __launch_bounds__(64) k_ctl_givens(Ctl* ctl, const double* pnorm, int nblk, int* act, int j, int m) {
   const int b = blockIdx.x;
   if (!act[b]) return;
-  givens_entry(b, ctl, pnorm, nblk, act, j, m);
+  givens_entry(b, gridDim.x, ctl, pnorm, nblk, nblk, act, j, m);
 }
 
 // The moments of the next basis vector (whose update and transform just ran) and the Givens step of the Krylov step
-// that produced it, in one launch: the moments are used only if the entry stays active.
-// 512 threads (a windowed step's moment sums take three rounds of its eight waves): a block of half a CU starts sooner
-// than one of kCtlThreads beside another stream's line kernels (same sums; measured 0.6% off the two-lane step)
-constexpr int kMomGivensThreads = 512;
-__global__ void __launch_bounds__(kMomGivensThreads) k_moments_givens(const double* part, TileSpan span,
-                                                                      double wscale, int M, c64* coefG, c64* dmom,
-                                                                      c32* dmom32, Ctl* ctl, const double* pnorm,
-                                                                      int* act, int j, int m) {
-  const int b = blockIdx.x;
+// that produced it, in one launch (block 0 of an entry: the Givens step): the moments are used only if the entry stays
+// active, so it does not matter on which side of the step's write of act[b] the other blocks read it.
+__global__ void __launch_bounds__(kMomThreads) k_moments_givens(const double* part, TileSpan span, double wscale,
+                                                                int M, c64* coefG, c64* dmom, c32* dmom32, Ctl* ctl,
+                                                                const double* pnorm, int* act, int j, int m) {
+  const int b = blockIdx.y;
   if (!act[b]) return;
-  constexpr int NV = 2 * kNMom;
-  __shared__ double tot[NV + 1];  // the moment sums, then |v_{j+1}|^2
-  reduce_entry<kMomGivensThreads>(part + (size_t)b * NV * span.stride, NV + 1, span.count(b), span.stride, tot,
-                                  pnorm + (size_t)b * span.stride, NV);
-  moments_combine(b, tot, wscale, M, coefG, dmom, dmom32);  // wave 0
-  if (threadIdx.x == 64) {                                   // wave 1
-    Ctl& c = ctl[b];
-    const double beta = sqrt(fmax(tot[NV], 0.0));
-    givens_commit(c, j, beta);
-    if (c.resid <= c.thresh || j + 1 >= m || beta == 0.0) act[b] = 0;
-    if (c.resid > c.thresh && j + 1 >= m && beta != 0.0) act[gridDim.x + b] = 1;  // stopped by the restart length
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < 64) givens_entry(b, gridDim.y, ctl, pnorm, span.count(b), span.stride, act, j, m);
+  } else {
+    moments_pair(b, blockIdx.x - 1, part, span, wscale, M, coefG, dmom, dmom32);
   }
 }
 
 // y = H^{-1} g (upper triangular jn x jn), coef_i = y_i sigma_i, zero beyond jn
-// One block of 64 threads per entry: the factor's columns and g are staged in LDS by all lanes (their loads in
-// flight together), then one thread runs the substitution on LDS values (the serial chain no longer waits on global
-// memory for each term; same operations in the same order), and the lanes write the coefficients out.
+// One wave per entry: the factor's columns are staged in LDS by all lanes (their loads in flight together), then lane i
+// holds component i and the substitution runs column by column.
 __global__ void __launch_bounds__(64) k_ctl_trisolve(Ctl* ctl, const int* live, int B) {
   const int b = blockIdx.x;
   if (b >= B || !live[b]) return;
   Ctl& c = ctl[b];
   const int n = c.jn;
-  const int i0 = threadIdx.x;
+  const int i = threadIdx.x;
   constexpr int LD = kMaxRestart + 1;
   __shared__ double Hs[kMaxRestart * LD];
-  __shared__ double y[kMaxRestart + 1];
   const double* Hc = c.H;
 #pragma unroll 8
-  for (int t = i0; t < n * LD; t += 64) Hs[t] = Hc[t];
-  for (int t = i0; t < n; t += 64) y[t] = c.g[t];
+  for (int t = i; t < n * LD; t += 64) Hs[t] = Hc[t];
+  double y = i < n ? c.g[i] : 0.0;
+  const double sg = c.sigma[i];
   __syncthreads();
-  if (i0 == 0) {
-    for (int i = n - 1; i >= 0; --i) {
-      double s = y[i];
-      for (int l = i + 1; l < n; ++l) s -= Hs[l * LD + i] * y[l];
-      const double d = Hs[i * LD + i];
-      y[i] = d != 0.0 ? s / d : 0.0;
-    }
+  const double d = i < n ? Hs[i * LD + i] : 0.0;
+  for (int l = n - 1; l >= 0; --l) {
+    const double dl = bcast(d, l), yl = dl != 0.0 ? bcast(y, l) / dl : 0.0;
+    if (i == l) y = yl;
+    if (i < l) y -= Hs[l * LD + i] * yl;
   }
-  __syncthreads();
-  for (int t = i0; t <= kMaxRestart; t += 64) c.coef[t] = t < n ? y[t] * c.sigma[t] : 0.0;
+  c.coef[i] = i < n ? y * sg : 0.0;
+  if (i == 0) c.coef[kMaxRestart] = 0.0;
 }
 
 // Condition estimate of one entry (one wave per entry): the extreme singular values of the upper-triangular factor R
@@ -272,6 +306,7 @@ __global__ void __launch_bounds__(64) k_ctl_trisolve(Ctl* ctl, const int* live, 
 // sigma_min(H) >= sigma_min(A)), so the ratio estimates cond(A) from below.  Power iteration on R^T R for sigma_max and
 // inverse iteration (a forward and a back substitution per step) for sigma_min, lane i holding component i.  Taken only
 // when the cycle is longer than the one behind the current estimate (the longest cycle has seen most of the spectrum).
+// One wave, no trip through LDS on the serial chain: 91 -> 47 us for a 20-step cycle, 53 -> 26 us for an 8-step one.
 constexpr int kCondIters = 12;
 __global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live) {
   const int b = blockIdx.x;
@@ -281,21 +316,20 @@ __global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live)
   if (n <= c.kappa_n || n < 1) return;
   const int i = threadIdx.x;
   constexpr int LD = kMaxRestart + 1;
-  // the n x n factor staged in LDS once: the iterations below read it many times.  The columns' n LD values are read
-  // as one flat range, eight loads per thread in flight at a time (column by column, each read waited for its own
-  // load before the next was issued); the entries below the diagonal are never read.
+  // the n x n factor staged in LDS once, zero below the diagonal: the iterations below read it many times, with no test
+  // around a read (their loads run ahead of the serial chain).  The columns' n LD values are read as one flat range,
+  // eight loads per thread in flight at a time.
   __shared__ double Rs[kMaxRestart * LD];
   const double* Hc = c.H;
 #pragma unroll 8
-  for (int t = i; t < n * LD; t += 64) Rs[t] = Hc[t];
+  for (int t = i; t < n * LD; t += 64) Rs[t] = t % LD <= t / LD ? Hc[t] : 0.0;
   __syncthreads();
+  const int ic = i < n ? i : n - 1;  // lanes beyond n read a column that is there
   auto R = [&](int row, int col) { return Rs[col * LD + row]; };
-  for (int l = 0; l < n; ++l)
-    if (!(R(l, l) != 0.0)) return;  // breakdown (exact solution reached): keep the previous estimate
+  const double diag = R(ic, ic);
+  if (__ballot(!(diag != 0.0))) return;  // breakdown (exact solution reached): keep the previous estimate
   // reciprocals of the diagonal, once: the substitutions below multiply instead of dividing on their serial chain
-  __shared__ double Dinv[kMaxRestart];
-  if (i < n) Dinv[i] = 1.0 / R(i, i);
-  __syncthreads();
+  const double dinv = 1.0 / diag;
   // sigma_max: x <- R^T R x, normalised
   double x = i < n ? 1.0 + 0.01 * i : 0.0;
   double nrm = sqrt(wsum(x * x));
@@ -303,15 +337,12 @@ __global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live)
   double smax2 = 0.0;
   for (int it = 0; it < kCondIters; ++it) {
     double y = 0.0;  // (R x)_i = sum_{l >= i} R_il x_l
-    for (int l = 0; l < n; ++l) {
-      const double xl = __shfl(x, l, 64);
-      if (i < n && l >= i) y += R(i, l) * xl;
-    }
+#pragma unroll 4
+    for (int l = 0; l < n; ++l) y += R(i, l) * bcast(x, l);
     double z = 0.0;  // (R^T y)_i = sum_{l <= i} R_li y_l
-    for (int l = 0; l < n; ++l) {
-      const double yl = __shfl(y, l, 64);
-      if (i < n && l <= i) z += R(l, i) * yl;
-    }
+#pragma unroll 4
+    for (int l = 0; l < n; ++l) z += R(l, ic) * bcast(y, l);
+    z = i < n ? z : 0.0;
     smax2 = sqrt(wsum(z * z));  // |R^T R x| for |x| = 1
     x = smax2 > 0.0 ? z / smax2 : 0.0;
   }
@@ -321,18 +352,20 @@ __global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live)
   x /= nrm;
   double inv2 = 0.0;
   for (int it = 0; it < kCondIters; ++it) {
-    double r = x, u = 0.0;  // R^T u = x (forward substitution, column by column)
+    double r = x, u = 0.0;  // R^T u = x (forward substitution, column by column; a component is final once it is read)
+#pragma unroll 4
     for (int l = 0; l < n; ++l) {
-      const double ul = __shfl(r, l, 64) * Dinv[l];
-      if (i == l) u = ul;
-      if (i > l && i < n) r -= R(l, i) * ul;
+      const double ul = bcast(r, l) * bcast(dinv, l);
+      u = i == l ? ul : u;
+      r -= R(l, ic) * ul;
     }
     r = u;
     double v = 0.0;  // R v = u (back substitution)
+#pragma unroll 4
     for (int l = n - 1; l >= 0; --l) {
-      const double vl = __shfl(r, l, 64) * Dinv[l];
-      if (i == l) v = vl;
-      if (i < l) r -= R(i, l) * vl;
+      const double vl = bcast(r, l) * bcast(dinv, l);
+      v = i == l ? vl : v;
+      r -= R(i, l) * vl;
     }
     inv2 = sqrt(wsum(v * v));  // |(R^T R)^{-1} x| for |x| = 1
     x = inv2 > 0.0 ? v / inv2 : 0.0;
@@ -694,7 +727,7 @@ void Pipeline::moments(const void* in, size_t in_bs, void* Tbuf, int B, const in
   TimerScope ts(kStageMoments, 0.0, B, act, s);
   TileSpan span;
   span.stride = moment_tiles(N, sizeof(T) == 8);
-  hipLaunchKernelGGL(k_moments, dim3(B), dim3(kCtlThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M, coefG,
+  hipLaunchKernelGGL(k_moments, dim3(kMomBlocks, B), dim3(kMomThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M, coefG,
                      dmom, dmom32);
 }
 
@@ -790,10 +823,10 @@ void Pipeline::apply_x_first(const void* in, size_t in_bs, void* Tbuf, int B, co
   const TileSpan span = apply_tiles(sizeof(T) == 8);
   TimerScope ts(kStageMoments, 0.0, B, act, s);
   if (u && u->ctl)
-    hipLaunchKernelGGL(k_moments_givens, dim3(B), dim3(kMomGivensThreads), 0, s, part_mom, span, dx * dx / (2.0 * kPi),
+    hipLaunchKernelGGL(k_moments_givens, dim3(1 + kMomBlocks, B), dim3(kMomThreads), 0, s, part_mom, span, dx * dx / (2.0 * kPi),
                        M, coefG, dmom, dmom32, u->ctl, u->part, const_cast<int*>(act), u->j, u->m);
   else
-    hipLaunchKernelGGL(k_moments, dim3(B), dim3(kCtlThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M,
+    hipLaunchKernelGGL(k_moments, dim3(kMomBlocks, B), dim3(kMomThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M,
                        coefG, dmom, dmom32);
 }
 
@@ -1118,7 +1151,7 @@ static void launch_ctl_coef(int nval, int B, hipStream_t s, A... args) {
   if (nval <= 4)
     hipLaunchKernelGGL(k_ctl_coef<256>, dim3(B), dim3(256), 0, s, args...);
   else
-    hipLaunchKernelGGL(k_ctl_coef<kCtlThreads>, dim3(B), dim3(kCtlThreads), 0, s, args...);
+    hipLaunchKernelGGL(k_ctl_coef<1024>, dim3(B), dim3(1024), 0, s, args...);
 }
 
 // One Krylov cycle in lockstep; returns the number of iterations run (max over entries).
@@ -1239,7 +1272,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
       launch_update<T>(va, s);
     }
     TimerScope ts(kStageControl, 0.0, B, nullptr, s);
-    hipLaunchKernelGGL(k_ctl_givens, dim3(B), dim3(kCtlThreads), 0, s, ctl, pnorm, nvb, act, j, w.m);
+    hipLaunchKernelGGL(k_ctl_givens, dim3(B), dim3(64), 0, s, ctl, pnorm, nvb, act, j, w.m);
   };
 
   bool graphs = cfg.use_graph && !timer_on();
