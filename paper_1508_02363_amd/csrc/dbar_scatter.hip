@@ -19,12 +19,6 @@
 namespace dbar {
 namespace {
 
-bool finite_all(const double* p, size_t cnt) {
-  for (size_t i = 0; i < cnt; ++i)
-    if (!std::isfinite(p[i])) return false;
-  return true;
-}
-
 bool on_grid(double v, double L) {
   const double m = v * L;
   return std::fabs(m - std::nearbyint(m)) <= 1e-9 * std::max(1.0, std::fabs(m));
@@ -36,7 +30,7 @@ int reflection_impl(const dbar_grid* grid, const double* q, int64_t nk, const do
   if (rc) return rc;
   if (nk < 1) return fail(DBAR_EINVAL, "nk must be >= 1");
   if (!q || !k || !r_out) return fail(DBAR_EINVAL, "q, k and r_out must not be NULL");
-  if (!finite_all(k, 2 * (size_t)nk)) return fail(DBAR_EINVAL, "k contains NaN or Inf");
+  if (!all_finite(k, 2 * (size_t)nk)) return fail(DBAR_EINVAL, "k contains NaN or Inf");
   for (int64_t j = 0; j < 2 * nk; ++j)
     if (!on_grid(k[j], grid->L))
       return fail(DBAR_EINVAL, "the reflection coefficient is computed on the xi grid: L Re k and L Im k integers");
@@ -69,7 +63,7 @@ int dbar_reconstruct(const dbar_grid* grid, const double* r, double t, double to
   if (!std::isfinite(t)) return fail(DBAR_EINVAL, "t must be finite");
   const int N = grid->n;
   const size_t n = (size_t)N * N;
-  if (!finite_all(r, 2 * n)) return fail(DBAR_EINVAL, "r contains NaN or Inf");
+  if (!all_finite(r, 2 * n)) return fail(DBAR_EINVAL, "r contains NaN or Inf");
   const double L = grid->L;
   dbar_grid dual{N, grid->M, (double)N / (2.0 * M_PI * L)};
   // potential of the dual problem: conj(r(k, t)) moved from FFT order to the dual x grid (index p -> p + N/2 mod N)

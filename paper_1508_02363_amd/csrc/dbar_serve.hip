@@ -592,8 +592,6 @@ int dbar_submit(dbar_session* s, const dbar_grid* grid, const double* Q, const d
   if (rc) return rc;
   if (!(tol > 0.0) || !std::isfinite(tol)) return fail(DBAR_EINVAL, "tol must be finite and > 0");
   const size_t n = (size_t)grid->n * grid->n;
-  for (size_t i = 0; i < 2 * n; ++i)
-    if (!std::isfinite(Q[i])) return fail(DBAR_EINVAL, "Q contains NaN or Inf");
   if (!std::isfinite(k[0]) || !std::isfinite(k[1])) return fail(DBAR_EINVAL, "k contains NaN or Inf");
   auto r = std::make_shared<SReq>();
   r->grid = *grid;
@@ -603,7 +601,7 @@ int dbar_submit(dbar_session* s, const dbar_grid* grid, const double* Q, const d
   r->pool = &s->pool;
   r->Q = static_cast<c64*>(s->pool.get(r->q_bytes()));
   if (!r->Q) return fail(DBAR_ENOMEM, "pinned host memory for the request's potential could not be allocated");
-  std::memcpy(r->Q, Q, n * sizeof(c64));
+  if (!copy_finite(reinterpret_cast<double*>(r->Q), Q, 2 * n)) return fail(DBAR_EINVAL, "Q contains NaN or Inf");
   r->footprint = footprint_of(grid->n, s->o.precision, s->o.restart, 1);
   r->t_submit = Clock::now();
   std::lock_guard<std::mutex> lock(s->mu);
