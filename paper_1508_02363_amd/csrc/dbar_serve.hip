@@ -16,6 +16,7 @@
 //
 // The paper motivates this by the need for solutions at many k (Section 1, and the outlook's parallelisation over
 // k); each slot is an independent solve of the Section 4 system with Q -> q_k.
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <condition_variable>
@@ -121,7 +122,7 @@ struct SClass {
   std::thread th;
   DevBuf newmask, tolv;
   std::vector<int> h_new, h_live;
-  std::vector<double> h_tol;
+  std::vector<double> h_tol, h_check;
   std::vector<c64> h_k;  // per-slot k (host source of the async upload; stable until the stream synchronises)
   hipStream_t copy_stream = nullptr;  // result copies (device to pinned host), overlapping the next cycle
   hipEvent_t ev_results = nullptr;    // recorded on `stream` after a cycle: the finished slots' results are final
@@ -185,8 +186,9 @@ static int class_init(SClass& c) {
   c.P.xspace = true;
   const size_t nb = (size_t)c.cap * c.N * c.N * sizeof(c64);
   if ((rc = c.w.Sx.ensure(nb)) || (rc = c.w.mx.ensure(nb))) return rc;
+  if (c.N >= kBoxMinN && (rc = c.w.setup_box())) return rc;
   if ((rc = c.newmask.ensure(c.cap * sizeof(int)))) return rc;
-  if ((rc = c.tolv.ensure(c.cap * sizeof(double)))) return rc;
+  if ((rc = c.tolv.ensure(2 * c.cap * sizeof(double)))) return rc;  // the tolerances, then those of a cycle's check
   if (hipStreamCreateWithFlags(&c.stream, hipStreamNonBlocking) != hipSuccess ||
       hipStreamCreateWithFlags(&c.copy_stream, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&c.ev_results, hipEventDisableTiming) != hipSuccess)
@@ -195,6 +197,7 @@ static int class_init(SClass& c) {
   c.h_new.assign(c.cap, 0);
   c.h_live.assign(c.cap, 0);
   c.h_tol.assign(c.cap, 1e-10);
+  c.h_check.assign(c.cap, 1e-10);
   c.h_k.assign(c.cap, c64{0.0, 0.0});
   c.w.B = c.cap;
   if (hipMemsetAsync(c.w.live.p, 0, c.cap * sizeof(int), c.stream) != hipSuccess ||
@@ -386,14 +389,26 @@ static void worker(dbar_session* s, SClass* cp) {
       (void)hipMemcpyAsync(c.newmask.p, c.h_new.data(), c.cap * sizeof(int), hipMemcpyHostToDevice, c.stream);
       (void)hipMemcpyAsync(w.live.p, c.h_live.data(), c.cap * sizeof(int), hipMemcpyHostToDevice, c.stream);
       (void)hipMemcpyAsync(c.tolv.p, c.h_tol.data(), c.cap * sizeof(double), hipMemcpyHostToDevice, c.stream);
-      if (mixed) launch_convert<float, double>(w.Q64.p, n, w.Q32.p, n, n, c.cap, nm, 1.0, c.stream);
-      c.P.rhs_x(w.Q64.p, n, w.V.p, V_bs, mixed, c.cap, nm, 0u, c.stream);  // the first basis vector
+      w.B = 1 + *std::max_element(admitted.begin(), admitted.end());
+      c.P.box = nullptr;
+      if (c.N >= kBoxMinN) {
+        launch_box(static_cast<const c64*>(w.Q64.p), n, c.N, static_cast<double*>(w.part_vec.p),
+                   static_cast<int*>(w.box.p), w.B, nm, c.stream);
+        // (cap boxes: those of the other slots in flight are still there)
+        (void)hipMemcpyAsync(w.host_box.data(), w.box.p, (size_t)c.cap * 4 * sizeof(int), hipMemcpyDeviceToHost,
+                             c.stream);
+        c.P.box = static_cast<const int*>(w.box.p);
+        c.P.box_bs = 4;
+      }
+      if (mixed) launch_convert<float, double>(w.Q64.p, n, w.Q32.p, n, n, w.B, nm, 1.0, c.stream);
+      c.P.rhs_x(w.Q64.p, n, w.V.p, V_bs, mixed, w.B, nm, 0u, c.stream);  // the first basis vector
       TileSpan rhs_span;
       rhs_span.stride = c.P.rhs_blocks();
-      launch_reduce(static_cast<double*>(w.part_vec.p), 1, rhs_span, static_cast<double*>(w.nred.p), c.cap, nm,
+      launch_reduce(static_cast<double*>(w.part_vec.p), 1, rhs_span, static_cast<double*>(w.nred.p), w.B, nm,
                     c.stream);
       launch_ctl_check(w, 0.0, 1, nm, static_cast<const double*>(c.tolv.p), c.stream);
       launch_zero_done(w, nm, false, c.stream);  // admitted requests with b = 0: S = m = 0
+      if (c.P.box) (void)hipStreamSynchronize(c.stream);  // (a failure shows at the cycle's own synchronisation)
     }
     bool computing = false;
     for (int b = 0; b < c.cap; ++b) computing |= c.h_live[b] != 0;
@@ -401,18 +416,40 @@ static void worker(dbar_session* s, SClass* cp) {
       complete_copies(s, c, true);
       continue;
     }
-    // ---- one Krylov cycle for everything in flight
+    // ---- one Krylov cycle for everything in flight: the launches cover the slots up to the last live one and the
+    // rows of the largest box among them
+    int used = 0;
+    for (int b = 0; b < c.cap; ++b)
+      if (c.h_live[b]) used = b + 1;
+    w.B = used;
+    if (c.P.box) c.P.set_box(c.P.box, 4, w.host_box.data(), used, c.h_live.data());
+    // As in a batched solve, the first cycle of a mixed solve cannot be its last when tol is far below the inner
+    // tolerance: such a request never finishes there (whatever else is in flight), and when all of them are in their
+    // first cycle its evaluation leaves S and m unwritten.
+    bool any_first = false, outputs = false;
+    for (int b = 0; b < used; ++b) {
+      const bool first = mixed && c.h_live[b] && c.slots[b]->iters == 0 && c.h_tol[b] < 1e-3 * cfg.inner_tol;
+      c.h_check[b] = first ? -1.0 : c.h_tol[b];
+      any_first |= first;
+      outputs |= c.h_live[b] && !first;
+    }
+    const double* check = static_cast<const double*>(c.tolv.p);
+    if (any_first) {
+      (void)hipMemcpyAsync(static_cast<double*>(c.tolv.p) + c.cap, c.h_check.data(), used * sizeof(double),
+                           hipMemcpyHostToDevice, c.stream);
+      check += c.cap;
+    }
     launch_ctl_start(w, mixed ? 0.3 : 0.5, mixed ? cfg.inner_tol : 0.0, static_cast<const double*>(c.tolv.p),
                      c.stream);
     int ran;
     if (mixed) {
       ran = krylov_cycle<float>(c.P, w, cfg, c.restart, c.stream);
-      end_cycle<float>(c.P, w, ran, w.r64.p, c.stream);
+      end_cycle<float>(c.P, w, ran, w.r64.p, c.stream, 0, true, outputs);
     } else {
       ran = krylov_cycle<double>(c.P, w, cfg, c.restart, c.stream);
-      end_cycle<double>(c.P, w, ran, w.V.p, c.stream);
+      end_cycle<double>(c.P, w, ran, w.V.p, c.stream, 0, true, outputs);
     }
-    launch_ctl_check(w, 0.0, 0, nullptr, static_cast<const double*>(c.tolv.p), c.stream);
+    launch_ctl_check(w, 0.0, 0, nullptr, check, c.stream);
     // (x-space: the residual evaluation wrote the next cycle's FP32 basis vector itself)
     std::vector<int> live_now(c.cap);
     (void)hipMemcpyAsync(live_now.data(), w.live.p, c.cap * sizeof(int), hipMemcpyDeviceToHost, c.stream);

@@ -140,6 +140,7 @@ struct Work {
   Work() = default;
   Work& operator=(Work&& o) noexcept;
   int N = 0, B = 0, m = 0, prec = 0;
+  int flag_stride = 0;  // between the per-entry flags in act: B at setup, whatever part of the entries a launch covers
   // captured Krylov step groups -> executable graph; dropped on reallocation.  A captured kernel node keeps its
   // arguments by value, so the key holds everything those arguments depend on besides the workspace pointers:
   // element bytes + method + space, first and end step, reorth + Gram-Schmidt window + window mode, batch B, and the
@@ -164,13 +165,13 @@ struct Work {
   bool x_zero = false;
   // Per entry: a windowed Krylov cycle ended it at the restart length rather than at its threshold (strong potentials
   // stall under truncated orthogonalisation), so its later cycles orthogonalise against every basis vector.  The
-  // device flags are act[2B + b] (set by the cycle start from the restart flags act[B + b], cleared when the entry's
+  // device flags are act[2 flag_stride + b] (set by the cycle start from the restart flags act[flag_stride + b], cleared when the entry's
   // solve starts); this host mirror, updated from the flags the host reads anyway, tells whether a cycle's launches
   // must cover the whole basis.  Other entries keep their window inside such launches.
   std::vector<int> full_host;
-  // x-space solves: the potentials' index boxes (k_box_cut; one, or one per entry in serving) and their partial sums;
-  // host_box: the host's copy
-  DevBuf box, boxtmp;
+  // x-space solves: the potentials' index boxes (k_box_cut; one, or one per entry in serving; their partial sums go
+  // through part_vec, which holds more than box_scratch doubles per entry from N = kBoxMinN on); host_box: the host's copy
+  DevBuf box;
   PinnedInts host_box;
   int setup_box();
   void* S_dst(int method) { return outS ? outS : method == 1 ? Fx.p : Sx.p; }
@@ -223,7 +224,7 @@ struct UpdReq {
   // with ctl set, the launch that reduces the moments also takes the Givens step of Krylov step j (restart m) from the
   // |v|^2 partials in part
   Ctl* ctl = nullptr;
-  int j = 0, m = 0;
+  int fs = 0, j = 0, m = 0;
 };
 
 struct DotReq {

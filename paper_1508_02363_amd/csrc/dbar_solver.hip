@@ -193,8 +193,8 @@ DBAR_D double givens_commit(Ctl& c, int j, double beta, double top, double mine)
 // otherwise (a smaller block starts sooner when another stream's line kernels hold most of every CU; the sums are the
 // same either way)
 template <int NT>
-__global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, int nval, TileSpan span, int* act, int j,
-                                                 int pass, int early, int m, int lo, int skip, const int* full) {
+__global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, int nval, TileSpan span, int* act, int fs,
+                                                 int j, int pass, int early, int m, int lo, int skip, const int* full) {
   const int b = blockIdx.x;
   if (!act[b]) return;
   __shared__ double red[kMaxRestart + 2];
@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, i
         givens_commit(c, j, beta, top, mine);
         if (lane == 0) {
           act[b] = 0;
-          if (resid > c.thresh) act[gridDim.x + b] = 1;  // stopped by the restart length
+          if (resid > c.thresh) act[fs + b] = 1;  // stopped by the restart length
         }
       }
     }
@@ -236,8 +236,8 @@ __global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, i
 }
 
 // Column j of the Hessenberg matrix from hsum and beta = ||w_new|| (reduced from the update's partials), Givens
-// rotation, residual estimate; the entry leaves the cycle when the estimate meets its threshold.  One wave of B entries.
-DBAR_D void givens_entry(int b, int B, Ctl* ctl, const double* pnorm, int nblk, int stride, int* act, int j, int m) {
+// rotation, residual estimate; the entry leaves the cycle when the estimate meets its threshold.  One wave.
+DBAR_D void givens_entry(int b, int fs, Ctl* ctl, const double* pnorm, int nblk, int stride, int* act, int j, int m) {
   Ctl& c = ctl[b];
   const int lane = threadIdx.x & 63;
   const double hsum = lane <= j ? c.hsum[lane] : 0.0;
@@ -248,14 +248,15 @@ DBAR_D void givens_entry(int b, int B, Ctl* ctl, const double* pnorm, int nblk, 
   const double resid = givens_commit(c, j, beta, top, mine);
   if (lane == 0) {
     if (resid <= c.thresh || j + 1 >= m || beta == 0.0) act[b] = 0;
-    if (resid > c.thresh && j + 1 >= m && beta != 0.0) act[B + b] = 1;  // stopped by the restart length
+    if (resid > c.thresh && j + 1 >= m && beta != 0.0) act[fs + b] = 1;  // stopped by the restart length
   }
 }
 
-__global__ void __launch_bounds__(64) k_ctl_givens(Ctl* ctl, const double* pnorm, int nblk, int* act, int j, int m) {
+__global__ void __launch_bounds__(64) k_ctl_givens(Ctl* ctl, const double* pnorm, int nblk, int* act, int fs, int j,
+                                                   int m) {
   const int b = blockIdx.x;
   if (!act[b]) return;
-  givens_entry(b, gridDim.x, ctl, pnorm, nblk, nblk, act, j, m);
+  givens_entry(b, fs, ctl, pnorm, nblk, nblk, act, j, m);
 }
 
 // The moments of the next basis vector (whose update and transform just ran) and the Givens step of the Krylov step
@@ -263,11 +264,11 @@ __global__ void __launch_bounds__(64) k_ctl_givens(Ctl* ctl, const double* pnorm
 // active, so it does not matter on which side of the step's write of act[b] the other blocks read it.
 __global__ void __launch_bounds__(kMomThreads) k_moments_givens(const double* part, TileSpan span, double wscale,
                                                                 int M, c64* coefG, c64* dmom, c32* dmom32, Ctl* ctl,
-                                                                const double* pnorm, int* act, int j, int m) {
+                                                                const double* pnorm, int* act, int fs, int j, int m) {
   const int b = blockIdx.y;
   if (!act[b]) return;
   if (blockIdx.x == 0) {
-    if (threadIdx.x < 64) givens_entry(b, gridDim.y, ctl, pnorm, span.count(b), span.stride, act, j, m);
+    if (threadIdx.x < 64) givens_entry(b, fs, ctl, pnorm, span.count(b), span.stride, act, j, m);
   } else {
     moments_pair(b, blockIdx.x - 1, part, span, wscale, M, coefG, dmom, dmom32);
   }
@@ -377,15 +378,15 @@ __global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live)
 }
 
 // start a Krylov cycle from the residual whose squared norm is nred[b] (already stored as v_0)
-__global__ void k_ctl_start(Ctl* ctl, const double* nred, const int* live, int* act, double abs_tol, double rel_tol,
-                            const double* tolv, int B) {
+__global__ void k_ctl_start(Ctl* ctl, const double* nred, const int* live, int* act, int fs, double abs_tol,
+                            double rel_tol, const double* tolv, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
   Ctl& c = ctl[b];
   // an entry whose last cycle ended at the restart length orthogonalises fully from now on (read only by windowed
   // cycles); the flag is set by the Givens step when the restart length, not the threshold, ends the entry's cycle
-  if (act[B + b]) act[2 * B + b] = 1;
-  act[B + b] = 0;
+  if (act[fs + b]) act[2 * fs + b] = 1;
+  act[fs + b] = 0;
   if (!live[b]) {
     act[b] = 0;
     return;
@@ -402,7 +403,7 @@ __global__ void k_ctl_start(Ctl* ctl, const double* nred, const int* live, int* 
 }
 
 // after a recomputed residual: done when ||r|| <= tol ||b||
-__global__ void k_ctl_check(Ctl* ctl, const double* nred, int* live, int* act, double tol, int first,
+__global__ void k_ctl_check(Ctl* ctl, const double* nred, int* live, int* act, int fs, double tol, int first,
                             const int* mask, const double* tolv, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B || (!first && !live[b]) || (mask && !mask[b])) return;
@@ -416,8 +417,8 @@ __global__ void k_ctl_check(Ctl* ctl, const double* nred, int* live, int* act, d
     c.jn = 0;
     c.kappa = 0.0;
     c.kappa_n = 0;
-    act[B + b] = 0;
-    act[2 * B + b] = 0;  // a new solve starts with the Gram-Schmidt window
+    act[fs + b] = 0;
+    act[2 * fs + b] = 0;  // a new solve starts with the Gram-Schmidt window
   }
   c.rnorm = rn;
   c.cycles += 1;
@@ -701,7 +702,7 @@ void Work::drop_graphs() {
 Work::~Work() { drop_graphs(); }
 Work& Work::operator=(Work&& o) noexcept {
   drop_graphs();
-  N = o.N; B = o.B; m = o.m; prec = o.prec; n = o.n; Q_bs = o.Q_bs;
+  N = o.N; B = o.B; flag_stride = o.flag_stride; m = o.m; prec = o.prec; n = o.n; Q_bs = o.Q_bs;
   x = std::move(o.x); bvec = std::move(o.bvec); T64 = std::move(o.T64); r64 = std::move(o.r64);
   T32 = std::move(o.T32); V = std::move(o.V); Q64 = std::move(o.Q64); Q32 = std::move(o.Q32);
   ex = std::move(o.ex); ey = std::move(o.ey); coefG = std::move(o.coefG); dmom = std::move(o.dmom);
@@ -711,7 +712,7 @@ Work& Work::operator=(Work&& o) noexcept {
   live = std::move(o.live); kvals = std::move(o.kvals); results = std::move(o.results);
   shv = std::move(o.shv); unit = std::move(o.unit); Hbuf = std::move(o.Hbuf);
   Sx = std::move(o.Sx); mx = std::move(o.mx); Fx = std::move(o.Fx); Ax = std::move(o.Ax);
-  box = std::move(o.box); boxtmp = std::move(o.boxtmp); host_box = std::move(o.host_box);
+  box = std::move(o.box); host_box = std::move(o.host_box);
   outS = o.outS; outm = o.outm; x_zero = o.x_zero;
   full_host = std::move(o.full_host);
   host_act = std::move(o.host_act); host_live = std::move(o.host_live); host_io = std::move(o.host_io);
@@ -730,6 +731,7 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
                           dmom32.p, unit32.p};
   N = N_;
   B = B_;
+  flag_stride = B_;
   m = m_;
   prec = prec_;
   n = (size_t)N * N;
@@ -775,7 +777,7 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
       return fail(DBAR_EDEVICE, "upload of the unit phase table failed");
   }
   if ((rc = results.ensure((size_t)B * sizeof(EntryResult)))) return rc;
-  // [B, 2B): left a cycle at the restart length; [2B, 3B): orthogonalises fully (see full_host)
+  // from flag_stride on: left a cycle at the restart length; from 2 flag_stride on: orthogonalises fully (see full_host)
   if ((rc = act.ensure((size_t)3 * B * sizeof(int)))) return rc;
   full_host.assign(B, 0);
   if ((rc = live.ensure((size_t)B * sizeof(int)))) return rc;
@@ -792,7 +794,6 @@ int Work::setup_box() {
   const int cnt = Q_bs ? B : 1;
   int rc;
   if ((rc = box.ensure((size_t)cnt * 4 * sizeof(int)))) return rc;
-  if ((rc = boxtmp.ensure(box_scratch(N, cnt) * sizeof(double)))) return rc;
   return host_box.ensure((size_t)cnt * 4);
 }
 
@@ -970,7 +971,7 @@ void Pipeline::apply_x_first(const void* in, size_t in_bs, void* Tbuf, int B, co
   TimerScope ts(kStageMoments, 0.0, B, act, s);
   if (u && u->ctl)
     hipLaunchKernelGGL(k_moments_givens, dim3(1 + kMomBlocks, B), dim3(kMomThreads), 0, s, part_mom, span, dx * dx / (2.0 * kPi),
-                       M, coefG, dmom, dmom32, u->ctl, u->part, const_cast<int*>(act), u->j, u->m);
+                       M, coefG, dmom, dmom32, u->ctl, u->part, const_cast<int*>(act), u->fs, u->j, u->m);
   else
     hipLaunchKernelGGL(k_moments, dim3(kMomBlocks, B), dim3(kMomThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M,
                        coefG, dmom, dmom32);
@@ -1331,7 +1332,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
   bool any_full = false;
   if (fused && window > 0)
     for (int b = 0; b < B; ++b) any_full |= w.full_host[b] != 0;
-  const int* full = any_full ? act + 2 * B : nullptr;
+  const int* full = any_full ? act + 2 * w.flag_stride : nullptr;
   auto enqueue = [&](int j) {
     void* vj = V + (size_t)j * n * sizeof(cx<T>);
     void* vj1 = V + (size_t)(j + 1) * n * sizeof(cx<T>);
@@ -1360,7 +1361,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
       }
       {
         TimerScope ts(kStageControl, 0.0, B, nullptr, s);
-        launch_ctl_coef(j - lo + 2, B, s, ctl, part, j - lo + 2, P.apply_tiles(sizeof(T) == 8), act, j, 0, 1, w.m, lo,
+        launch_ctl_coef(j - lo + 2, B, s, ctl, part, j - lo + 2, P.apply_tiles(sizeof(T) == 8), act, w.flag_stride, j, 0, 1, w.m, lo,
                         lo_win - lo, full);
       }
       UpdReq u;
@@ -1371,6 +1372,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
       u.coef_bs = sizeof(Ctl) / sizeof(double);
       u.part = pnorm;
       u.ctl = ctl;  // step j's Givens step rides on the moment reduction of v_{j+1}
+      u.fs = w.flag_stride;
       u.j = j;
       u.m = w.m;
       if (cfg.method == 1)
@@ -1409,7 +1411,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
       }
       {
         TimerScope ts(kStageControl, 0.0, B, nullptr, s);
-        launch_ctl_coef(j + 1, B, s, ctl, part, j + 1, span, act, j, pass, 0, w.m, 0, 0, nullptr);
+        launch_ctl_coef(j + 1, B, s, ctl, part, j + 1, span, act, w.flag_stride, j, pass, 0, w.m, 0, 0, nullptr);
       }
       va.coef = &ctl[0].coef[0];
       va.coef_bs = sizeof(Ctl) / sizeof(double);
@@ -1418,7 +1420,8 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
       launch_update<T>(va, s);
     }
     TimerScope ts(kStageControl, 0.0, B, nullptr, s);
-    hipLaunchKernelGGL(k_ctl_givens, dim3(B), dim3(64), 0, s, ctl, pnorm, nvb, act, j, w.m);
+    hipLaunchKernelGGL(k_ctl_givens, dim3(B), dim3(64), 0, s, ctl, pnorm, nvb, act, w.flag_stride, j,
+                       w.m);
   };
 
   bool graphs = cfg.use_graph && !timer_on();
@@ -1465,14 +1468,14 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
     if (!done)
       for (int jj = j; jj < j1; ++jj) enqueue(jj);
     j = j1;
-    (void)hipMemcpyAsync(w.host_act.data(), act, 2 * B * sizeof(int), hipMemcpyDeviceToHost, s);
+    (void)hipMemcpyAsync(w.host_act.data(), act, (w.flag_stride + B) * sizeof(int), hipMemcpyDeviceToHost, s);
     (void)hipStreamSynchronize(s);
     int active = 0;
     for (int b = 0; b < B; ++b) {
       active += w.host_act[b] != 0;
       // an entry that left this cycle at the restart length orthogonalises fully from the next cycle on (the cycle
       // start sets its device flag from the same restart flag)
-      if (w.host_act[B + b] != 0) w.full_host[b] = 1;
+      if (w.host_act[w.flag_stride + b] != 0) w.full_host[b] = 1;
     }
     if (active == 0) return j;
     if (4 * active <= B) len = std::max(1, cfg.check_every / 2);
@@ -1569,13 +1572,13 @@ void launch_ctl_check(Work& w, double tol, int first, const int* mask, const dou
   TimerScope ts(kStageControl, 0.0, w.B, nullptr, s);
   hipLaunchKernelGGL(k_ctl_check, dim3(ctl_blocks(w.B)), dim3(64), 0, s, static_cast<Ctl*>(w.ctl.p),
                      static_cast<const double*>(w.nred.p), static_cast<int*>(w.live.p), static_cast<int*>(w.act.p),
-                     tol, first, mask, tolv, w.B);
+                     w.flag_stride, tol, first, mask, tolv, w.B);
 }
 void launch_ctl_start(Work& w, double abs_tol, double rel_tol, const double* tolv, hipStream_t s) {
   TimerScope ts(kStageControl, 0.0, w.B, nullptr, s);
   hipLaunchKernelGGL(k_ctl_start, dim3(ctl_blocks(w.B)), dim3(64), 0, s, static_cast<Ctl*>(w.ctl.p),
                      static_cast<const double*>(w.nred.p), static_cast<const int*>(w.live.p),
-                     static_cast<int*>(w.act.p), abs_tol, rel_tol, tolv, w.B);
+                     static_cast<int*>(w.act.p), w.flag_stride, abs_tol, rel_tol, tolv, w.B);
 }
 
 __global__ void k_zero_done(c64* a0, c64* a1, c64* a2, c64* a3, const int* live, const int* mask, size_t n) {
@@ -1628,8 +1631,8 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vec
   if (hipMemcpyAsync(live, w.host_live.data(), B * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess)
     return fail(DBAR_EDEVICE, "hipMemcpyAsync failed");
   // r0 = b (x0 = 0); entries with b = 0 are done at once
-  hipLaunchKernelGGL(k_ctl_check, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, 0.0, 1, nullptr, nullptr,
-                     B);
+  hipLaunchKernelGGL(k_ctl_check, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, w.flag_stride, 0.0, 1,
+                     nullptr, nullptr, B);
   if (P.xspace) {  // S = m = 0 for entries with b = 0 (no residual evaluation writes them)
     launch_zero_done(w, nullptr, cfg.method == 1, s);
   } else if (mixed) {
@@ -1648,7 +1651,8 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vec
     if (!any || total >= cfg.max_iter) break;
     const double rel = mixed ? cfg.inner_tol : 0.0;
     const double abs_tol = mixed ? 0.3 * cfg.tol : 0.5 * cfg.tol;
-    hipLaunchKernelGGL(k_ctl_start, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, abs_tol, rel, nullptr, B);
+    hipLaunchKernelGGL(k_ctl_start, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, w.flag_stride, abs_tol,
+                       rel, nullptr, B);
     int ran;
     // The first cycle of a mixed-precision x-space solve starts from |r| = |b| and asks its FP32 inner solve for
     // inner_tol of that, which FP32 arithmetic cannot better by many orders: with tol far below inner_tol its residual
@@ -1665,7 +1669,7 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vec
       end_cycle<double>(P, w, ran, w.V.p, s, cfg.method, total == 0);
     }
     total += ran;
-    hipLaunchKernelGGL(k_ctl_check, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act,
+    hipLaunchKernelGGL(k_ctl_check, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, w.flag_stride,
                        outputs ? cfg.tol : -1.0, 0, nullptr, nullptr, B);
     if (mixed && !P.xspace) launch_convert<float, double>(w.r64.p, n, w.V.p, n * (w.m + 1), n, B, live, 1.0, s);
     if (ran == 0) break;
@@ -1902,8 +1906,8 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
     if (o.precision == DBAR_MIXED) launch_convert<float, double>(w.Q64.p, 0, w.Q32.p, 0, n, 1, nullptr, 1.0, s);
     if (cfg.xspace && cfg.reorth == 1 && N >= kBoxMinN) {
       if ((rc = w.setup_box())) return rc;
-      launch_box(static_cast<const c64*>(w.Q64.p), 0, N, static_cast<double*>(w.boxtmp.p), static_cast<int*>(w.box.p),
-                 1, nullptr, s);
+      launch_box(static_cast<const c64*>(w.Q64.p), 0, N, static_cast<double*>(w.part_vec.p),
+                 static_cast<int*>(w.box.p), 1, nullptr, s);
       ln[l].P.box = static_cast<const int*>(w.box.p);
     }
     if (cfg.method == 1 && (rc = w.Hbuf.ensure((size_t)Bl * n * sizeof(c64)))) return rc;
