@@ -189,6 +189,66 @@ DBAR_D cx<TT> tail_sum(TT x, TT y, const cx<TT> (&d)[kMaxM + 1]) {
   return mul_i(acc);
 }
 
+// The same sum from a table of what does not depend on the entry: e^{-u} and E_MM = P(MM+1, u)/u^{MM+1} at the point
+// (tab = {e^{-u}, E_MM}, k_tail_table).  omega_n = i E_n (conj(z)/4)^{n+1} and E_n = u E_{n+1} + e^{-u}/(n+1)! hold for
+// every u (positive terms only), so one recurrence serves up to where every P rounds to 1.  It leaves out the
+// exponential, the series (40 dependent steps in FP64) and the division, which bounded the tail launch in FP64; the entry is
+// one more 16-byte read per point, from L2 for all batch entries but the first.  Tail launch, before -> after: FP64 N = 128,
+// 1 entry 12.7 -> 9.7 us, 1024 entries 182 -> 129; N = 256, 63 entries 36 -> 27; N = 512, 45 entries 77 -> 61; N = 1024,
+// 8 entries 53 -> 43; FP32 N = 1024, 8 entries 24.8 -> 23.4.  Error against 64 bits as before (the table is FP64's own).
+template <typename TT, int MM>
+DBAR_D cx<TT> tail_tab(TT x, TT y, const cx<TT> (&d)[kMaxM + 1], cx<TT> tab) {
+  const TT r2 = x * x + y * y;
+  const TT u = TT(0.25) * r2;
+  const TT one_from = sizeof(TT) == 8 ? TT(kTailOneF64[MM]) : TT(kTailOneF32[MM]);
+  cx<TT> acc;
+  if (u >= one_from) {  // all P(n+1, u) = 1: i sum_n d_n / z^{n+1}
+    const TT ir2 = recip(r2);
+    const cx<TT> w{x * ir2, -y * ir2};
+    acc = d[MM];
+#pragma unroll
+    for (int n = MM - 1; n >= 0; --n) acc = cfma(w, acc, d[n]);
+    acc = w * acc;
+  } else {
+    const cx<TT> zeta{TT(0.25) * x, TT(-0.25) * y};
+    TT E = tab.im;
+    acc = E * d[MM];
+#pragma unroll
+    for (int n = MM - 1; n >= 0; --n) {
+      E = fmar(u, E, tab.re * TT(kInvFact[n + 1]));
+      acc = cfma(zeta, acc, E * d[n]);
+    }
+    acc = zeta * acc;
+  }
+  return mul_i(acc);
+}
+// {e^{-u}, E_MM} at u in FP64 (E_MM by its series below u = MM + 1, from the closed form of P beyond)
+template <int MM>
+DBAR_D c64 tail_entry(double u) {
+  const double eu = exp(-u);
+  if (u < MM + 1) {
+    constexpr int W = MM == 11 ? 0 : 1, K = kSerK64[W];
+    const double v = u / (MM + 1);
+    double F = kSeries.d[W][K - 1];
+    for (int k = K - 2; k >= 0; --k) F = F * v + kSeries.d[W][k];
+    return c64{eu, eu * F * kInvFact[MM + 1]};
+  }
+  double t = eu, S = eu, up = u;
+  for (int k = 1; k <= MM; ++k) {
+    t *= u * kInv.d[k];
+    S += t;
+    up *= u;
+  }
+  return c64{eu, (1.0 - S) / up};
+}
+// The table holds one quarter of the plane: |row - N/2|, |col - N/2| <= N/2 (the points of the grid mirror in both axes).
+constexpr int tail_pitch(int N) { return N / 2 + 1; }
+template <int N>
+DBAR_D int tail_index(int row, int col) {
+  const int r = row - N / 2, c = col - N / 2;
+  return (r < 0 ? -r : r) * tail_pitch(N) + (c < 0 ? -c : c);
+}
+
 // ------------------------------------------------------------------------------------------------------------
 // Block reduction of per-thread FP64 values into global partials dst[v * stride]
 // ------------------------------------------------------------------------------------------------------------
@@ -987,8 +1047,9 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false, Ept<T, N>::TAIL_ROWS> {
   // waves per SIMD at eight)
   static constexpr int GROUP_W = 4;
   static constexpr int GROUP = G::RMAX < GROUP_W ? G::RMAX : GROUP_W;
+  static constexpr bool TABLE = N <= kTailTabMaxN;
   struct GroupIn {
-    cx<T> q[GROUP], s[GROUP], y[GROUP], ex[GROUP];
+    cx<T> q[GROUP], s[GROUP], y[GROUP], ex[GROUP], tab[GROUP];
   };
   // the group's q (times the x factor of e_k on the plain operator), S and Y (zero outside the box)
   DBAR_D void group_load(GroupIn& g, int b, int row, int jt, int s0, const bool (&in)[GROUP]) const {
@@ -1003,6 +1064,7 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false, Ept<T, N>::TAIL_ROWS> {
       const uint32_t idx = row * N + pos;
       g.q[u] = box_load<T>(Qb, idx, in[u]);
       g.s[u] = a.alpha != 0.0 ? box_load<T>(Sb, idx, in[u]) : cx<T>{T(0), T(0)};
+      if constexpr (TABLE) g.tab[u] = static_cast<const cx<T>*>(a.ttab)[tail_index<N>(row, pos)];
       g.y[u] = (a.gamma != 0.0 && !a.y_rhs) ? box_load<T>(Yb, idx, in[u]) : cx<T>{T(0), T(0)};
       if (a.shv) g.ex[u] = cx<T>{T(1), T(0)};
       else if constexpr (sizeof(T) == 8) g.ex[u] = a.ex[eo + pos];
@@ -1038,7 +1100,14 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false, Ept<T, N>::TAIL_ROWS> {
           slot = cx<T>{T(0), T(0)};
           continue;
         }
-        const cx<T> h = this->h_at(b, pos, row, slot, p);  // x index pos, y index row
+        cx<T> h;
+        if constexpr (TABLE) {
+          const T x = xgrid_t<T, N>(pos, a.L), y = xgrid_t<T, N>(row, a.L);
+          const cx<T> t = a.M == 11 ? tail_tab<T, 11>(x, y, p.d, cur.tab[u]) : tail_tab<T, kMaxM>(x, y, p.d, cur.tab[u]);
+          h = a.shv ? slot + conj(this->phase(b, pos, row)) * t : slot + t;
+        } else {
+          h = this->h_at(b, pos, row, slot, p);  // x index pos, y index row
+        }
         if (a.hout) (static_cast<cx<T>*>(a.hout) + (size_t)b * a.hout_bs)[base + pos] = h;
         const cx<T> qk = cur.q[u] * (cur.ex[u] * ey);
         const cx<T> w = qk * conj(h);
@@ -1166,14 +1235,14 @@ DBAR_D int xcd_swizzle(int bid, int nblk) {
 constexpr int kSpreadTiles = 128;
 
 // Occupancy floor: at least 4 waves per SIMD (<= 128 VGPRs) for the wide column tiles, whose LDS allows two
-// blocks per CU only if the registers do too.
-template <int NT, bool COLS, bool MOMENTS>
+// blocks per CU only if the registers do too, and for FP32 rows (the tail's reads would take 20 more).
+template <int NT, bool COLS, bool MOMENTS, bool FP32>
 struct MinWaves {
-  static constexpr int value = COLS && NT >= 256 ? (MOMENTS ? NT / 256 : 4) : 1;
+  static constexpr int value = COLS && NT >= 256 ? (MOMENTS ? NT / 256 : 4) : !COLS && FP32 ? 4 : 1;
 };
 
 template <typename T, int N, int LINES, bool COLS, class Op>
-__global__ void __launch_bounds__((LINES * Op::G::TPL), (MinWaves<LINES * Op::G::TPL, COLS, Op::MOMENTS>::value))
+__global__ void __launch_bounds__((LINES * Op::G::TPL), (MinWaves<LINES * Op::G::TPL, COLS, Op::MOMENTS, sizeof(T) == 4>::value))
     k_lines(Op op) {
   using G = typename Op::G;
   constexpr int NT = LINES * G::TPL;

@@ -169,6 +169,7 @@ static size_t footprint_of(int N, int prec, int restart, int cap_hint) {
 static int class_init(SClass& c) {
   int rc = c.w.setup(c.N, c.cap, c.restart, c.prec, false);
   if (rc) return rc;
+  if ((rc = c.w.setup_tail(c.L, c.M, nullptr))) return rc;
   dbar_grid g{c.N, c.M, c.L};
   if ((rc = make_pipeline(&g, c.w, &c.P))) return rc;
   {

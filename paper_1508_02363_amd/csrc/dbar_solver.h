@@ -169,6 +169,11 @@ struct Work {
   // solve starts); this host mirror, updated from the flags the host reads anyway, tells whether a cycle's launches
   // must cover the whole basis.  Other entries keep their window inside such launches.
   std::vector<int> full_host;
+  // the tail's table of the grid (N, L, M) last set up (grids up to kTailTabMaxN)
+  DevBuf tail64, tail32;
+  int tail_N = 0, tail_M = 0;
+  double tail_L = 0.0;
+  int setup_tail(double L, int M, hipStream_t s);
   // x-space solves: the potentials' index boxes (k_box_cut; one, or one per entry in serving; their partial sums go
   // through part_vec, which holds more than box_scratch doubles per entry from N = kBoxMinN on); host_box: the host's copy
   DevBuf box;
@@ -243,6 +248,8 @@ struct Pipeline {
   size_t n = 0;
   const void* tw64 = nullptr;  // exp(-2 pi i j / N), j < N, in FP64 and rounded to FP32
   const void* tw32 = nullptr;
+  const void* tail64 = nullptr;  // x-space tail tables (null beyond kTailTabMaxN)
+  const void* tail32 = nullptr;
   const c64* ex = nullptr;
   const c64* ey = nullptr;
   const c32* ex32 = nullptr;

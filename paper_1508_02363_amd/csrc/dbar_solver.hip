@@ -712,6 +712,8 @@ Work& Work::operator=(Work&& o) noexcept {
   live = std::move(o.live); kvals = std::move(o.kvals); results = std::move(o.results);
   shv = std::move(o.shv); unit = std::move(o.unit); Hbuf = std::move(o.Hbuf);
   Sx = std::move(o.Sx); mx = std::move(o.mx); Fx = std::move(o.Fx); Ax = std::move(o.Ax);
+  tail64 = std::move(o.tail64); tail32 = std::move(o.tail32);
+  tail_N = o.tail_N; tail_M = o.tail_M; tail_L = o.tail_L;
   box = std::move(o.box); host_box = std::move(o.host_box);
   outS = o.outS; outm = o.outm; x_zero = o.x_zero;
   full_host = std::move(o.full_host);
@@ -728,7 +730,7 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   if (N_ != N || B_ != B || m_ != m || prec_ != prec || (shared_q ? 0 : (size_t)N_ * N_) != Q_bs) drop_graphs();
   const void* before[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
                           nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
-                          dmom32.p, unit32.p};
+                          dmom32.p, unit32.p, tail64.p, tail32.p};
   N = N_;
   B = B_;
   flag_stride = B_;
@@ -785,8 +787,27 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   if ((rc = host_live.ensure(B))) return rc;
   const void* after[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
                          nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
-                          dmom32.p, unit32.p};
+                          dmom32.p, unit32.p, tail64.p, tail32.p};
   if (std::memcmp(before, after, sizeof(before)) != 0) drop_graphs();
+  return DBAR_OK;
+}
+
+// The grid's tail table, computed on s when the grid is another than the last (an entry's value depends on nothing else).
+int Work::setup_tail(double L, int M, hipStream_t s) {
+  if (N > kTailTabMaxN) return DBAR_OK;
+  if (tail64.p && tail_N == N && tail_L == L && tail_M == M) return DBAR_OK;
+  int rc;
+  tail_N = 0;
+  drop_graphs();  // captured launches read the table
+  if ((rc = tail64.ensure(tail_table_size(N) * sizeof(c64)))) return rc;
+  if ((rc = tail32.ensure(tail_table_size(N) * sizeof(c32)))) return rc;
+  launch_tail_table(N, L, M, static_cast<c64*>(tail64.p), static_cast<c32*>(tail32.p), s);
+  if (hipGetLastError() != hipSuccess) return fail(DBAR_EDEVICE, "the tail table could not be computed");
+  // (the workspace may be used on another stream next: the table is complete when this returns)
+  if (hipStreamSynchronize(s) != hipSuccess) return fail(DBAR_EDEVICE, "stream synchronize failed");
+  tail_N = N;
+  tail_L = L;
+  tail_M = M;
   return DBAR_OK;
 }
 
@@ -997,6 +1018,7 @@ void Pipeline::apply_x_rest(const void* in, size_t in_bs, void* out, size_t out_
   a.hout_bs = n;
   a.out32 = xo ? xo->r32 : nullptr;
   a.out32_bs = xo ? xo->r32_bs : 0;
+  a.ttab = sizeof(T) == 8 ? tail64 : tail32;
   a.Q = Qp;
   a.Q_bs = Q_bs;
   a.out = out;
@@ -1285,6 +1307,8 @@ int make_pipeline(const dbar_grid* g, Work& w, Pipeline* p) {
   p->part_vec = static_cast<double*>(w.part_vec.p);
   p->unit = static_cast<const c64*>(w.unit.p);
   p->shv = static_cast<const int*>(w.shv.p);
+  p->tail64 = g->n <= kTailTabMaxN ? w.tail64.p : nullptr;
+  p->tail32 = g->n <= kTailTabMaxN ? w.tail32.p : nullptr;
   return DBAR_OK;
 }
 
@@ -1894,6 +1918,7 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
     ln[l].w = &w;
     const hipStream_t s = ln[l].s;
     if ((rc = w.setup(N, Bl, o.restart, o.precision, true))) return rc;
+    if (cfg.xspace && (rc = w.setup_tail(grid->L, grid->M, s))) return rc;
     if ((rc = make_pipeline(grid, w, &ln[l].P))) return rc;
     ln[l].P.xspace = cfg.xspace != 0;
     if (q_on_device) {
@@ -2163,6 +2188,7 @@ int dbar_autotune(const dbar_grid* grid, int32_t precision, int32_t batch, dbar_
   Work& w = g_work;
   // FP32 operator buffers come with the mixed layout; one Krylov vector pair serves as input and output
   if ((rc = w.setup(N, batch, 1, precision == DBAR_FP64 ? DBAR_FP64 : DBAR_MIXED, true))) return rc;
+  if ((rc = w.setup_tail(grid->L, grid->M, s))) return rc;
   Pipeline P;
   if ((rc = make_pipeline(grid, w, &P))) return rc;
   P.xspace = true;  // the operator as the plain method's solves apply it
