@@ -189,7 +189,8 @@ enum Stage : int {
   kStageConvert = 40,
   kStageMoments = 41,
   kStageControl = 42,
-  kNumStages = 43,
+  kStageCycle = 43,                // + (float ? 1 : 0): whole cycles of small grids
+  kNumStages = 45,
 };
 const char* stage_name(int stage);
 bool timer_on();

@@ -129,6 +129,7 @@ struct BatchCfg {
   int max_iter = 1000;
   int reorth = 1;
   int check_every = 4;
+  bool each_step = false;  // the host reads the residual after every step (plain mode)
   double inner_tol = 1e-6;
   int xspace = 0;  // the plain method iterates on s = F^{-1} S
   int orth_window = 0;  // fused x-space step: Gram-Schmidt against the last orth_window vectors (0: all)
@@ -376,6 +377,11 @@ void end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t s, i
 void launch_cond_estimate(Work& w, hipStream_t s);
 // residual check (first = 1: record ||b|| and reset the counters of the entries in mask); tolv: per-entry tol
 void launch_ctl_check(Work& w, double tol, int first, const int* mask, const double* tolv, hipStream_t s);
+// A whole Krylov cycle (x-space, one Gram-Schmidt pass) of every active entry in one launch, for grids that fit one
+// block's LDS: at most mlim steps; the steps of the longest one land in act[3 flag_stride] (cleared by the cycle start).
+bool small_cycle_ok(int N, double L);
+template <typename T>
+void launch_small_cycle(const Pipeline& P, Work& w, int method, int window, int mlim, hipStream_t s);
 // start a cycle for every live entry from its residual norm
 void launch_ctl_start(Work& w, double abs_tol, double rel_tol, const double* tolv, hipStream_t s);
 

@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "dbar.h"
+#include "dbar_ctl.h"
 #include "dbar_launch.h"
 #include "dbar_solver.h"
 
@@ -35,28 +36,8 @@ int fail(int code, const std::string& msg) {
 }
 
 // ------------------------------------------------------------------------------------------------------------
-// Control kernels (one thread per batch entry)
+// Control kernels
 // ------------------------------------------------------------------------------------------------------------
-static __constant__ double kInvFactC[kMaxM + 2] = {
-    1.0, 1.0, 5.0e-1, 1.6666666666666666e-1, 4.1666666666666664e-2, 8.3333333333333332e-3,
-    1.3888888888888889e-3, 1.9841269841269841e-4, 2.4801587301587302e-5, 2.7557319223985893e-6,
-    2.7557319223985888e-7, 2.5052108385441720e-8, 2.0876756987868100e-9, 1.6059043836821613e-10,
-    1.1470745597729725e-11, 7.6471637318198164e-13, 4.7794773323873853e-14};
-
-DBAR_D double wsum(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
-}
-
-
-// lane l's x in every lane (l uniform: a register read, not a trip through LDS as __shfl is)
-DBAR_D double bcast(double x, int l) {
-  const long long v = __builtin_bit_cast(long long, x);
-  const unsigned lo = __builtin_amdgcn_readlane((int)v, l), hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
 // sum of p[0 .. nblk) over one wave (every lane gets it), in an order fixed by nblk.  Eight independent partial sums
 // per lane: the loads of a chunk are in flight together.
 DBAR_D double wave_reduce(const double* __restrict__ p, int nblk) {
@@ -72,8 +53,8 @@ DBAR_D double wave_reduce(const double* __restrict__ p, int nblk) {
   return wsum(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
 }
 
-// Taylor slot n of entry b from the sums (re, im) of its moment: d_n = w sum, c_n = (-i/2)^n d_n / n! (equation
-// fourreeg4 with Gchoice; (-i/2)^n = (-i)^n 2^-n exactly), slot kMaxM + 1: the conj(z) moment, R(0) = (-i/2) dt.
+// Taylor slot n of entry b from the sums (re, im) of its moment: d_n = w sum and c_n; slot kMaxM + 1: the conj(z) moment,
+// R(0) = (-i/2) dt.
 DBAR_D void moments_slot(int b, int n, c64 sum, double wscale, int M, c64* coefG, c64* dmom, c32* dmom32) {
   const c64 d = wscale * sum;
   c64* cg = coefG + (size_t)b * kNMom;
@@ -85,11 +66,9 @@ DBAR_D void moments_slot(int b, int n, c64 sum, double wscale, int M, c64* coefG
     dm32[n] = cvt<float>(d);
     return;
   }
-  const double s = ldexp(1.0, -n);
-  const c64 p = (n & 3) == 0 ? c64{s, 0.0} : (n & 3) == 1 ? c64{0.0, -s} : (n & 3) == 2 ? c64{-s, 0.0} : c64{0.0, s};
   dm[n] = n <= M ? d : c64{0.0, 0.0};
   dm32[n] = cvt<float>(dm[n]);
-  cg[n] = n <= M ? kInvFactC[n] * (p * d) : c64{0.0, 0.0};
+  cg[n] = n <= M ? taylor_coef(n, d) : c64{0.0, 0.0};
 }
 
 // The moment reduction is split over blocks, two Taylor slots each (one wave per real sum), kMomBlocks per entry: the
@@ -120,36 +99,6 @@ __global__ void __launch_bounds__(kMomThreads) k_moments(const double* part, Til
   const int b = blockIdx.y;
   if (act && !act[b]) return;
   moments_pair(b, blockIdx.x, part, span, wscale, M, coefG, dmom, dmom32);
-}
-
-// One Hessenberg column in a wave's registers: lane i holds sigma_i, hsum_i and rotation i, and the rotations run
-// through all of them with register reads (a single thread that walks the record in memory waits for each term).
-struct HessLane {
-  double cs, sn, raw;  // raw: the column's entry i before the rotations, sigma_j hsum_i
-  int first;           // the first entry that can be nonzero after them (rotation i mixes entries i and i + 1)
-};
-DBAR_D HessLane hess_lane(const Ctl& c, int j, double hsum) {
-  const int lane = threadIdx.x & 63;
-  HessLane h;
-  h.cs = lane < j ? c.cs[lane] : 1.0;
-  h.sn = lane < j ? c.sn[lane] : 0.0;
-  h.raw = lane <= j ? c.sigma[j] * hsum : 0.0;
-  const unsigned long long nz = __ballot(h.raw != 0.0);
-  const int f = nz ? __builtin_ctzll(nz) : j;
-  h.first = f > 0 ? f - 1 : 0;
-  return h;
-}
-// entry j of the rotated column (every lane); mine: entry `lane` for lane < j
-DBAR_D double hess_rotate(const HessLane& h, int j, double& mine) {
-  const int lane = threadIdx.x & 63;
-  double top = bcast(h.raw, h.first);
-  mine = 0.0;
-  for (int i = h.first; i < j; ++i) {
-    const double c = bcast(h.cs, i), s = bcast(h.sn, i), next = bcast(h.raw, i + 1);
-    if (lane == i) mine = c * top + s * next;
-    top = -s * top + c * next;
-  }
-  return top;
 }
 
 // Column j of the Hessenberg matrix from hsum and beta = ||v_{j+1}|| (unnormalised basis: column j is sigma_j times the
@@ -381,6 +330,7 @@ __global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live)
 __global__ void k_ctl_start(Ctl* ctl, const double* nred, const int* live, int* act, int fs, double abs_tol,
                             double rel_tol, const double* tolv, int B) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b == 0) act[3 * fs] = 0;
   if (b >= B) return;
   Ctl& c = ctl[b];
   // an entry whose last cycle ended at the restart length orthogonalises fully from now on (read only by windowed
@@ -779,11 +729,12 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
       return fail(DBAR_EDEVICE, "upload of the unit phase table failed");
   }
   if ((rc = results.ensure((size_t)B * sizeof(EntryResult)))) return rc;
-  // from flag_stride on: left a cycle at the restart length; from 2 flag_stride on: orthogonalises fully (see full_host)
-  if ((rc = act.ensure((size_t)3 * B * sizeof(int)))) return rc;
+  // from flag_stride on: left a cycle at the restart length; from 2 flag_stride on: orthogonalises fully (see full_host);
+  // at 3 flag_stride: the steps of the longest cycle (whole-cycle launches)
+  if ((rc = act.ensure(((size_t)3 * B + 1) * sizeof(int)))) return rc;
   full_host.assign(B, 0);
   if ((rc = live.ensure((size_t)B * sizeof(int)))) return rc;
-  if ((rc = host_act.ensure(2 * B))) return rc;
+  if ((rc = host_act.ensure(3 * B + 1))) return rc;
   if ((rc = host_live.ensure(B))) return rc;
   const void* after[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
                          nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
@@ -1448,6 +1399,18 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
                        w.m);
   };
 
+  // a small grid's cycle is one launch, one block per entry (not in the plain mode, which reads the residual at every
+  // step)
+  if (fused && !cfg.each_step && small_cycle_ok(P.N, P.L)) {
+    launch_small_cycle<T>(P, w, cfg.method, window, mlim, s);
+    const size_t flags = (size_t)3 * w.flag_stride + 1;  // act, restart, full, then the steps of the longest cycle
+    (void)hipMemcpyAsync(w.host_act.data(), act, flags * sizeof(int), hipMemcpyDeviceToHost, s);
+    (void)hipStreamSynchronize(s);
+    for (int b = 0; b < B; ++b)
+      if (w.host_act[w.flag_stride + b] != 0) w.full_host[b] = 1;
+    return w.host_act[flags - 1];
+  }
+
   bool graphs = cfg.use_graph && !timer_on();
   if (w.graph_epoch != tuning_epoch()) {  // captured with another tile choice
     w.drop_graphs();
@@ -1903,6 +1866,7 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
   cfg.use_graph = o.mode == DBAR_MODE_PLAIN || lanes > 1 ? 0 : o.use_graph;
   cfg.method = o.method;
   cfg.check_every = o.mode == DBAR_MODE_PLAIN ? 1 : o.check_every;
+  cfg.each_step = o.mode == DBAR_MODE_PLAIN;
   cfg.inner_tol = o.inner_tol;
   cfg.orth_window = o.orth_window;
   cfg.xspace = o.space == DBAR_SPACE_X ? 1 : 0;

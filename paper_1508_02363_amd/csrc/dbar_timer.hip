@@ -72,6 +72,8 @@ const char* stage_name(int stage) {
       names[stage] = "convert";
     } else if (stage == kStageMoments) {
       names[stage] = "moments.finish";
+    } else if (stage >= kStageCycle) {
+      names[stage] = stage == kStageCycle ? "krylov.cycle.f64" : "krylov.cycle.f32";
     } else {
       names[stage] = "control";
     }
