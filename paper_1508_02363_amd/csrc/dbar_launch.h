@@ -106,7 +106,8 @@ constexpr int kBoxCols = 8;
 constexpr int kBoxMinN = 128;
 int box_row_align(int N);
 // Largest grid whose x-space tail reads its entry-independent part from a table: the tail launch gains 5 to 30 percent up
-// to here and is bound by memory beyond, where a table of N^2 / 4 entries (17 and 67 MB in FP64) no longer stays in L2.  The table of a grid: tail_table_size(N) entries, FP64 and rounded to FP32.
+// to here and is bound by memory beyond, where a table of N^2 / 4 entries (17 and 67 MB in FP64) no longer stays in L2.
+// The table of a grid: tail_table_size(N) entries, FP64 and rounded to FP32.
 constexpr int kTailTabMaxN = 1024;
 size_t tail_table_size(int N);
 void launch_tail_table(int N, double L, int M, c64* t64, c32* t32, hipStream_t s);
@@ -168,8 +169,6 @@ template <typename TO, typename TI> void launch_convert(const void* in, size_t i
 int vec_blocks(size_t n);
 
 // Deterministic reduction of partial sums: out[b][v] = scale * sum_blk part[b][v][blk]
-void launch_reduce(const double* part, int nval, const TileSpan& span, double* out, int B, const int* act,
-                   hipStream_t s);
 
 // The box of each potential Q (B of them, stride Q_bs) on an N x N grid: the rows and columns outside hold at most
 // 2^-56 of its 2-norm.  tmp: box_scratch(N, B) doubles.  box: 4 B ints.

@@ -395,9 +395,6 @@ static void worker(dbar_session* s, SClass* cp) {
       if (c.N >= kBoxMinN) {
         launch_box(static_cast<const c64*>(w.Q64.p), n, c.N, static_cast<double*>(w.part_vec.p),
                    static_cast<int*>(w.box.p), w.B, nm, c.stream);
-        // (cap boxes: those of the other slots in flight are still there)
-        (void)hipMemcpyAsync(w.host_box.data(), w.box.p, (size_t)c.cap * 4 * sizeof(int), hipMemcpyDeviceToHost,
-                             c.stream);
         c.P.box = static_cast<const int*>(w.box.p);
         c.P.box_bs = 4;
       }
@@ -405,11 +402,10 @@ static void worker(dbar_session* s, SClass* cp) {
       c.P.rhs_x(w.Q64.p, n, w.V.p, V_bs, mixed, w.B, nm, 0u, c.stream);  // the first basis vector
       TileSpan rhs_span;
       rhs_span.stride = c.P.rhs_blocks();
-      launch_reduce(static_cast<double*>(w.part_vec.p), 1, rhs_span, static_cast<double*>(w.nred.p), w.B, nm,
-                    c.stream);
-      launch_ctl_check(w, 0.0, 1, nm, static_cast<const double*>(c.tolv.p), c.stream);
+      launch_ctl_check(w, rhs_span, 0.0, 1, nm, static_cast<const double*>(c.tolv.p), c.stream);
       launch_zero_done(w, nm, false, c.stream);  // admitted requests with b = 0: S = m = 0
-      if (c.P.box) (void)hipStreamSynchronize(c.stream);  // (a failure shows at the cycle's own synchronisation)
+      // (cap boxes: those of the other slots in flight are still there; a failure shows at the cycle's own wait)
+      if (c.P.box) (void)w.report({{static_cast<const int*>(w.box.p), w.host_box.data(), c.cap * 4}}, c.stream);
     }
     bool computing = false;
     for (int b = 0; b < c.cap; ++b) computing |= c.h_live[b] != 0;
@@ -443,18 +439,17 @@ static void worker(dbar_session* s, SClass* cp) {
     launch_ctl_start(w, mixed ? 0.3 : 0.5, mixed ? cfg.inner_tol : 0.0, static_cast<const double*>(c.tolv.p),
                      c.stream);
     int ran;
+    TileSpan span;
     if (mixed) {
       ran = krylov_cycle<float>(c.P, w, cfg, c.restart, c.stream);
-      end_cycle<float>(c.P, w, ran, w.r64.p, c.stream, 0, true, outputs);
+      span = end_cycle<float>(c.P, w, ran, w.r64.p, c.stream, 0, true, outputs);
     } else {
       ran = krylov_cycle<double>(c.P, w, cfg, c.restart, c.stream);
-      end_cycle<double>(c.P, w, ran, w.V.p, c.stream, 0, true, outputs);
+      span = end_cycle<double>(c.P, w, ran, w.V.p, c.stream, 0, true, outputs);
     }
-    launch_ctl_check(w, 0.0, 0, nullptr, check, c.stream);
+    launch_ctl_check(w, span, 0.0, 0, nullptr, check, c.stream);
     // (x-space: the residual evaluation wrote the next cycle's FP32 basis vector itself)
-    std::vector<int> live_now(c.cap);
-    (void)hipMemcpyAsync(live_now.data(), w.live.p, c.cap * sizeof(int), hipMemcpyDeviceToHost, c.stream);
-    if (hipStreamSynchronize(c.stream) != hipSuccess) {
+    if (w.report({}, c.stream) != DBAR_OK) {
       std::lock_guard<std::mutex> lock(s->mu);
       c.error = DBAR_EDEVICE;
       for (auto& r : c.slots)
@@ -472,7 +467,7 @@ static void worker(dbar_session* s, SClass* cp) {
     for (int b = 0; b < c.cap; ++b) {
       if (!c.slots[b] || !c.h_live[b]) continue;
       c.slots[b]->iters += ran;
-      const bool done = live_now[b] == 0;
+      const bool done = w.host_live[b] == 0;
       const bool exhausted = !done && c.slots[b]->iters >= cfg.max_iter;
       if (done || exhausted || ran == 0) {
         c.h_live[b] = 0;

@@ -114,6 +114,15 @@ struct Ctl {
   int jn, iters, cycles, kappa_n;
 };
 
+// A range of 32-bit words that k_words moves between device and pinned host memory.
+struct WordRange {
+  const int* src = nullptr;
+  int* dst = nullptr;
+  int n = 0;
+};
+constexpr int kMaxWordRanges = 4;
+void launch_words(std::initializer_list<WordRange> ranges, hipStream_t s);
+
 struct EntryResult {
   int iters, cycles;
   double bnorm, rnorm;
@@ -154,7 +163,7 @@ struct Work {
   size_t n = 0;
   size_t Q_bs = 0;
   DevBuf x, bvec, T64, r64, T32, V, Q64, Q32, ex, ey, ex32, ey32, coefG, dmom, dmom32, part_mom, part_vec, part_norm,
-      dred, nred, ctl, act, live, kvals, results, shv, unit, unit32, Hbuf;
+      dred, nred, ctl, act, live, kvals, shv, unit, unit32, Hbuf;
   DevBuf Sx, mx;  // x-space solves: S = F x and m = h(S) of the last residual evaluation (FP64)
   DevBuf Fx, Ax;  // x-space iterated solves: f = H(h) and the shifted inverse of h of the last residual evaluation
   // Where an x-space solve leaves S and m: the caller's device arrays when it passes them (set per batch), else null
@@ -183,6 +192,11 @@ struct Work {
   void* S_dst(int method) { return outS ? outS : method == 1 ? Fx.p : Sx.p; }
   void* m_dst() { return outm ? outm : mx.p; }
   PinnedInts host_act, host_live;
+  PinnedInts host_ticket;
+  int ticket_no = 0;
+  // the ranges to pinned memory, after everything on s; returns when they are there (and with them what earlier kernels
+  // on s wrote to pinned memory)
+  int report(std::initializer_list<WordRange> ranges, hipStream_t s);
   PinnedInts host_io;  // per batch: k values, grid shifts and results on their way between host and device
   int setup(int N_, int B_, int m_, int prec_, bool shared_q);
   size_t vec_bytes(int prec) const;
@@ -358,7 +372,9 @@ int make_pipeline(const dbar_grid* g, Work& w, Pipeline* p);
 // e_k tables of B entries: FP64 ex/ey and their FP32 roundings ex32/ey32 (per-entry stride N)
 void launch_phase_tables(const c64* kv_dev, int N, double L, c64* ex, c64* ey, c32* ex32, c32* ey32, int B,
                          hipStream_t s);
-int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vector<int>& iters_out);
+// Solves the w.B entries set up in w (live flags of the last check in w.host_live once the stream has been waited for).
+// gathered: the entries' results are on their way to hres (pinned) already; else the caller forms S(0) and gathers them.
+int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, EntryResult* hres, bool& gathered);
 // x-space: the residual evaluation's outputs (w.Sx, w.mx; with iterated also w.Fx, w.Ax) = 0 for entries that are
 // not live (and in mask, if given): those no residual evaluation writes
 void launch_zero_done(Work& w, const int* mask, bool iterated, hipStream_t s);
@@ -366,17 +382,20 @@ int ctl_blocks(int B);
 // one lockstep Krylov cycle over the entries flagged in w.act; returns the iterations run
 template <typename T>
 int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget, hipStream_t s);
-// solution update from the cycle and the FP64 residual r = b - A(x) into r_out (norms into w.nred); cond: also the
+// solution update from the cycle and the FP64 residual r = b - A(x) into r_out (returns the span of its squared norms'
+// block sums in w.part_vec, which launch_ctl_check takes); cond: also the
 // condition estimate of the entries whose cycle was their longest so far; outputs (x-space): also the solve's outputs
 // if this evaluation is the last (S = F x and m = h(S), or the iterated method's h, f, the shifted inverse and h(f));
 // false: the caller knows it is not the last
 template <typename T>
-void end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t s, int method = 0, bool cond = true,
-               bool outputs = true);
+TileSpan end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t s, int method = 0, bool cond = true,
+                   bool outputs = true);
 // condition estimate of each live entry from its last cycle's Hessenberg factor, where that cycle is the longest so far
 void launch_cond_estimate(Work& w, hipStream_t s);
-// residual check (first = 1: record ||b|| and reset the counters of the entries in mask); tolv: per-entry tol
-void launch_ctl_check(Work& w, double tol, int first, const int* mask, const double* tolv, hipStream_t s);
+// residual check from the squared norms' block sums (first = 1: record ||b|| and reset the counters of the entries in
+// mask); tolv: per-entry tol; the checked entries' live flags also go to w.host_live
+void launch_ctl_check(Work& w, const TileSpan& span, double tol, int first, const int* mask, const double* tolv,
+                      hipStream_t s);
 // A whole Krylov cycle (x-space, one Gram-Schmidt pass) of every active entry in one launch, for grids that fit one
 // block's LDS: at most mlim steps; the steps of the longest one land in act[3 flag_stride] (cleared by the cycle start).
 bool small_cycle_ok(int N, double L);

@@ -352,14 +352,27 @@ __global__ void k_ctl_start(Ctl* ctl, const double* nred, const int* live, int* 
   act[b] = rn > c.thresh ? 1 : 0;
 }
 
-// after a recomputed residual: done when ||r|| <= tol ||b||
-__global__ void k_ctl_check(Ctl* ctl, const double* nred, int* live, int* act, int fs, double tol, int first,
-                            const int* mask, const double* tolv, int B) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B || (!first && !live[b]) || (mask && !mask[b])) return;
+// After a recomputed residual: |r|^2 from its blocks' sums (in a fixed order), done when ||r|| <= tol ||b||.  One block per
+// entry.  report (pinned host memory, or null): the entry's live flag for the host.
+__global__ void __launch_bounds__(256) k_ctl_check(Ctl* ctl, const double* part, TileSpan span, double* nred, int* live,
+                                                   int* act, int fs, double tol, int first, const int* mask,
+                                                   const double* tolv, int* report) {
+  const int b = blockIdx.x;
+  if ((!first && !live[b]) || (mask && !mask[b])) return;
+  __shared__ double red[4];
+  const int nblk = span.count(b);
+  const double* p = part + (size_t)b * span.stride;
+  double sum = 0.0;
+  for (int i = threadIdx.x; i < nblk; i += 256) sum += p[i];
+  sum = wsum(sum);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const double r2 = red[0] + red[1] + red[2] + red[3];
+  nred[b] = r2;
   Ctl& c = ctl[b];
   // (a sum of squares: no clamp, so that a residual that is not finite stays NaN and never counts as converged)
-  const double rn = sqrt(nred[b]);
+  const double rn = sqrt(r2);
   if (first) {
     c.bnorm = rn;
     c.iters = 0;
@@ -373,7 +386,56 @@ __global__ void k_ctl_check(Ctl* ctl, const double* nred, int* live, int* act, i
   c.rnorm = rn;
   c.cycles += 1;
   const double t = tolv ? tolv[b] : tol;
-  if (rn <= t * c.bnorm) live[b] = 0;
+  const int lv = rn <= t * c.bnorm ? 0 : first && !mask ? 1 : live[b];  // (a solve's first check: every entry starts live)
+  live[b] = lv;
+  if (report) report[b] = lv;
+}
+
+// Flags, indices and k values between device and pinned host memory, at most kMaxWordRanges ranges, then a ticket the host
+// waits for.  The runtime's copies of a few words are a blit kernel each with signals around it; with them out (and with
+// the norm's reduction inside the check and the results gathered with the last flags): N = 128, one problem 790 -> 760 us,
+// N = 512, 45 problems 5.28 -> 5.21 ms, nine iterated ones 1.175 -> 1.154 ms.
+struct Words {
+  WordRange r[kMaxWordRanges];
+  int* ticket = nullptr;
+  int value = 0;
+};
+__global__ void __launch_bounds__(256) k_words(Words a) {
+  for (int k = 0; k < kMaxWordRanges; ++k)
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < a.r[k].n; i += gridDim.x * 256) a.r[k].dst[i] = a.r[k].src[i];
+  if (!a.ticket) return;
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(a.ticket, a.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+static Words words_of(std::initializer_list<WordRange> ranges) {
+  Words a;
+  int k = 0;
+  for (const WordRange& r : ranges) a.r[k++] = r;
+  return a;
+}
+void launch_words(std::initializer_list<WordRange> ranges, hipStream_t s) {
+  TimerScope ts(kStageControl, 0.0, 1, nullptr, s);
+  // (a trip over the bus takes microseconds: a thread reads one word)
+  int most = 1;
+  for (const WordRange& r : ranges) most = std::max(most, r.n);
+  hipLaunchKernelGGL(k_words, dim3((most + 255) / 256), dim3(256), 0, s, words_of(ranges));
+}
+
+int Work::report(std::initializer_list<WordRange> ranges, hipStream_t s) {
+  Words a = words_of(ranges);
+  a.ticket = host_ticket.data();
+  a.value = ++ticket_no;
+  hipLaunchKernelGGL(k_words, dim3(1), dim3(256), 0, s, a);
+  // The ticket for as long as short work takes, then the runtime's wait (which also shows a stream that failed).
+  using Clock = std::chrono::steady_clock;
+  const Clock::time_point until = Clock::now() + std::chrono::microseconds(500);
+  for (unsigned i = 1;; ++i) {
+    if (__atomic_load_n(a.ticket, __ATOMIC_ACQUIRE) == a.value) return DBAR_OK;
+    if ((i & 63) == 0 && Clock::now() > until) break;
+    __builtin_ia32_pause();
+  }
+  return hipStreamSynchronize(s) == hipSuccess ? DBAR_OK : fail(DBAR_EDEVICE, "stream synchronize failed");
 }
 
 // e^{conj(kz) - kz} = e^{-2i k2 x} e^{-2i k1 y} (eq:039) as two FP64 tables per entry, x_j = L(-pi + 2 pi j / N)
@@ -393,19 +455,34 @@ __global__ void k_phase_tables(const c64* kv, int N, double L, c64* ex, c64* ey,
   }
 }
 
-// compact per-entry results: iterations, residual evaluations, ||b||, ||r||, S(0), and with shifts (iterated
+// compact per-entry results (out: pinned host memory): iterations, residual evaluations, ||b||, ||r||, S(0), and with shifts (iterated
 // method) h at the shift offset (m1, m2) = (2 k2 L, 2 k1 L), i.e. h(xi = 2i conj k)
-__global__ void k_gather_results(const Ctl* ctl, const c64* x, size_t n, const c64* h, const int* shv, int N,
+__global__ void __launch_bounds__(64) k_gather_results(const Ctl* ctl, const c64* x, size_t n, const c64* h, const int* shv, int N,
                                  EntryResult* out, int B) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const Ctl& c = ctl[b];
-  c64 hs{0.0, 0.0};
-  if (shv) {
-    const int p1 = ((shv[2 * b] % N) + N) % N, p2 = ((shv[2 * b + 1] % N) + N) % N;
-    hs = h[(size_t)b * n + (size_t)p2 * N + p1];
+  const int b0 = blockIdx.x * 64, b = b0 + threadIdx.x;
+  __shared__ EntryResult res[64];
+  if (b < B) {
+    const Ctl& c = ctl[b];
+    c64 hs{0.0, 0.0};
+    if (shv) {
+      const int p1 = ((shv[2 * b] % N) + N) % N, p2 = ((shv[2 * b + 1] % N) + N) % N;
+      hs = h[(size_t)b * n + (size_t)p2 * N + p1];
+    }
+    res[threadIdx.x] = EntryResult{c.iters, c.cycles, c.bnorm, c.rnorm, x[(size_t)b * n], hs, c.kappa};
   }
-  out[b] = EntryResult{c.iters, c.cycles, c.bnorm, c.rnorm, x[(size_t)b * n], hs, c.kappa};
+  __syncthreads();
+  // (over the bus in whole lines)
+  constexpr int W = sizeof(EntryResult) / sizeof(double);
+  static_assert(sizeof(EntryResult) % sizeof(double) == 0, "whole words");
+  const int cnt = (B - b0 < 64 ? B - b0 : 64) * W;
+  for (int i = threadIdx.x; i < cnt; i += 64)
+    reinterpret_cast<double*>(out + b0)[i] = reinterpret_cast<const double*>(res)[i];
+}
+
+static void launch_gather(Work& w, const c64* S0, const c64* h, bool shifted, EntryResult* out, hipStream_t s) {
+  TimerScope ts(kStageControl, 0.0, w.B, nullptr, s);
+  hipLaunchKernelGGL(k_gather_results, dim3((w.B + 63) / 64), dim3(64), 0, s, static_cast<const Ctl*>(w.ctl.p), S0, w.n,
+                     h, shifted ? static_cast<const int*>(w.shv.p) : nullptr, w.N, out, w.B);
 }
 
 void launch_phase_tables(const c64* kv_dev, int N, double L, c64* ex, c64* ey, c32* ex32, c32* ey32, int B,
@@ -444,7 +521,7 @@ int PinnedInts::ensure(size_t n) {
   if (p) (void)hipHostFree(p);
   p = nullptr;
   count = 0;
-  if (hipHostMalloc(reinterpret_cast<void**>(&p), n * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc(reinterpret_cast<void**>(&p), n * sizeof(int), hipHostMallocCoherent) != hipSuccess) {
     (void)hipGetLastError();
     p = nullptr;
     return fail(DBAR_ENOMEM, "hipHostMalloc failed");
@@ -659,7 +736,7 @@ Work& Work::operator=(Work&& o) noexcept {
   ex32 = std::move(o.ex32); ey32 = std::move(o.ey32); dmom32 = std::move(o.dmom32); unit32 = std::move(o.unit32);
   part_mom = std::move(o.part_mom); part_vec = std::move(o.part_vec); part_norm = std::move(o.part_norm);
   dred = std::move(o.dred); nred = std::move(o.nred); ctl = std::move(o.ctl); act = std::move(o.act);
-  live = std::move(o.live); kvals = std::move(o.kvals); results = std::move(o.results);
+  live = std::move(o.live); kvals = std::move(o.kvals);
   shv = std::move(o.shv); unit = std::move(o.unit); Hbuf = std::move(o.Hbuf);
   Sx = std::move(o.Sx); mx = std::move(o.mx); Fx = std::move(o.Fx); Ax = std::move(o.Ax);
   tail64 = std::move(o.tail64); tail32 = std::move(o.tail32);
@@ -667,6 +744,7 @@ Work& Work::operator=(Work&& o) noexcept {
   box = std::move(o.box); host_box = std::move(o.host_box);
   outS = o.outS; outm = o.outm; x_zero = o.x_zero;
   full_host = std::move(o.full_host);
+  host_ticket = std::move(o.host_ticket); ticket_no = o.ticket_no;
   host_act = std::move(o.host_act); host_live = std::move(o.host_live); host_io = std::move(o.host_io);
   graphs = std::move(o.graphs);
   graph_epoch = o.graph_epoch;
@@ -728,7 +806,6 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
         hipMemcpy(unit32.p, ones32.data(), N * sizeof(c32), hipMemcpyHostToDevice) != hipSuccess)
       return fail(DBAR_EDEVICE, "upload of the unit phase table failed");
   }
-  if ((rc = results.ensure((size_t)B * sizeof(EntryResult)))) return rc;
   // from flag_stride on: left a cycle at the restart length; from 2 flag_stride on: orthogonalises fully (see full_host);
   // at 3 flag_stride: the steps of the longest cycle (whole-cycle launches)
   if ((rc = act.ensure(((size_t)3 * B + 1) * sizeof(int)))) return rc;
@@ -736,6 +813,7 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   if ((rc = live.ensure((size_t)B * sizeof(int)))) return rc;
   if ((rc = host_act.ensure(3 * B + 1))) return rc;
   if ((rc = host_live.ensure(B))) return rc;
+  if ((rc = host_ticket.ensure(1))) return rc;
   const void* after[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
                          nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
                           dmom32.p, unit32.p, tail64.p, tail32.p};
@@ -1404,8 +1482,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
   if (fused && !cfg.each_step && small_cycle_ok(P.N, P.L)) {
     launch_small_cycle<T>(P, w, cfg.method, window, mlim, s);
     const size_t flags = (size_t)3 * w.flag_stride + 1;  // act, restart, full, then the steps of the longest cycle
-    (void)hipMemcpyAsync(w.host_act.data(), act, flags * sizeof(int), hipMemcpyDeviceToHost, s);
-    (void)hipStreamSynchronize(s);
+    (void)w.report({{act, w.host_act.data(), (int)flags}}, s);
     for (int b = 0; b < B; ++b)
       if (w.host_act[w.flag_stride + b] != 0) w.full_host[b] = 1;
     return w.host_act[flags - 1];
@@ -1455,8 +1532,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
     if (!done)
       for (int jj = j; jj < j1; ++jj) enqueue(jj);
     j = j1;
-    (void)hipMemcpyAsync(w.host_act.data(), act, (w.flag_stride + B) * sizeof(int), hipMemcpyDeviceToHost, s);
-    (void)hipStreamSynchronize(s);
+    (void)w.report({{act, w.host_act.data(), w.flag_stride + B}}, s);
     int active = 0;
     for (int b = 0; b < B; ++b) {
       active += w.host_act[b] != 0;
@@ -1470,9 +1546,10 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
   return j;
 }
 
-// x += sum coef_i V_i and the FP64 residual r = b - A(x) (into r_out), with squared norms in nred
+// x += sum coef_i V_i and the FP64 residual r = b - A(x) (into r_out); returns where its squared norms' block sums are
 template <typename T>
-void end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t s, int method, bool cond, bool outputs) {
+TileSpan end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t s, int method, bool cond,
+                   bool outputs) {
   const int B = w.B;
   const size_t n = w.n;
   Ctl* ctl = static_cast<Ctl*>(w.ctl.p);
@@ -1540,14 +1617,13 @@ void end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t s, i
     P.apply_x_rest<double>(w.x.p, n, sizeof(T) == 4 ? nullptr : r_out, r_bs, w.Q64.p, w.Q_bs, w.T64.p, B, live, -1.0,
                            -1.0, kYRhs, 0, true, s, nullptr, &xo, 0u, nullptr, 0);
   }
-  launch_reduce(static_cast<double*>(w.part_vec.p), 1, P.apply_tiles(true, P.xspace && outputs),
-                static_cast<double*>(w.nred.p), B, live, s);
+  return P.apply_tiles(true, P.xspace && outputs);
 }
 
 template int krylov_cycle<float>(const Pipeline&, Work&, const BatchCfg&, int, hipStream_t);
 template int krylov_cycle<double>(const Pipeline&, Work&, const BatchCfg&, int, hipStream_t);
-template void end_cycle<float>(const Pipeline&, Work&, int, void*, hipStream_t, int, bool, bool);
-template void end_cycle<double>(const Pipeline&, Work&, int, void*, hipStream_t, int, bool, bool);
+template TileSpan end_cycle<float>(const Pipeline&, Work&, int, void*, hipStream_t, int, bool, bool);
+template TileSpan end_cycle<double>(const Pipeline&, Work&, int, void*, hipStream_t, int, bool, bool);
 
 void launch_cond_estimate(Work& w, hipStream_t s) {
   TimerScope ts(kStageControl, 0.0, w.B, nullptr, s);
@@ -1555,11 +1631,13 @@ void launch_cond_estimate(Work& w, hipStream_t s) {
                      static_cast<const int*>(w.live.p));
 }
 
-void launch_ctl_check(Work& w, double tol, int first, const int* mask, const double* tolv, hipStream_t s) {
-  TimerScope ts(kStageControl, 0.0, w.B, nullptr, s);
-  hipLaunchKernelGGL(k_ctl_check, dim3(ctl_blocks(w.B)), dim3(64), 0, s, static_cast<Ctl*>(w.ctl.p),
-                     static_cast<const double*>(w.nred.p), static_cast<int*>(w.live.p), static_cast<int*>(w.act.p),
-                     w.flag_stride, tol, first, mask, tolv, w.B);
+void launch_ctl_check(Work& w, const TileSpan& span, double tol, int first, const int* mask, const double* tolv,
+                      hipStream_t s) {
+  TimerScope ts(kStageControl, (double)span.stride * sizeof(double), w.B, nullptr, s);
+  hipLaunchKernelGGL(k_ctl_check, dim3(w.B), dim3(256), 0, s, static_cast<Ctl*>(w.ctl.p),
+                     static_cast<const double*>(w.part_vec.p), span, static_cast<double*>(w.nred.p),
+                     static_cast<int*>(w.live.p), static_cast<int*>(w.act.p), w.flag_stride, tol, first, mask, tolv,
+                     w.host_live.data());
 }
 void launch_ctl_start(Work& w, double abs_tol, double rel_tol, const double* tolv, hipStream_t s) {
   TimerScope ts(kStageControl, 0.0, w.B, nullptr, s);
@@ -1588,7 +1666,7 @@ void launch_zero_done(Work& w, const int* mask, bool iterated, hipStream_t s) {
                      static_cast<const int*>(w.live.p), mask, w.n);
 }
 
-int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vector<int>& iters_out) {
+int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, EntryResult* hres, bool& gathered) {
   const int B = w.B;
   const size_t n = w.n;
   const bool mixed = w.prec == DBAR_MIXED;
@@ -1606,41 +1684,40 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vec
     P.rhs(w.Q64.p, w.Q_bs, w.T64.p, static_cast<c64*>(w.bvec.p), B, nullptr, rhs_flags, s);
   TileSpan rhs_span;
   rhs_span.stride = P.rhs_blocks();
-  launch_reduce(static_cast<double*>(w.part_vec.p), 1, rhs_span, nred, B, nullptr, s);
-  if (P.box && hipMemcpyAsync(w.host_box.data(), P.box, 4 * sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess)
-    return fail(DBAR_EDEVICE, "hipMemcpyAsync failed");
   // x = 0: the x-space residual's first launch writes x = sum y_i V_i on the first update (no memset)
   w.x_zero = P.xspace;
   w.full_host.assign(B, 0);  // device flags: cleared by the first residual check below
   if (!w.x_zero && hipMemsetAsync(w.x.p, 0, (size_t)B * n * sizeof(c64), s) != hipSuccess)
     return fail(DBAR_EDEVICE, "hipMemsetAsync failed");
-  for (int b = 0; b < B; ++b) w.host_live[b] = 1;
-  if (hipMemcpyAsync(live, w.host_live.data(), B * sizeof(int), hipMemcpyHostToDevice, s) != hipSuccess)
-    return fail(DBAR_EDEVICE, "hipMemcpyAsync failed");
   // r0 = b (x0 = 0); entries with b = 0 are done at once
-  hipLaunchKernelGGL(k_ctl_check, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, w.flag_stride, 0.0, 1,
-                     nullptr, nullptr, B);
-  if (P.xspace) {  // S = m = 0 for entries with b = 0 (no residual evaluation writes them)
-    launch_zero_done(w, nullptr, cfg.method == 1, s);
+  launch_ctl_check(w, rhs_span, 0.0, 1, nullptr, nullptr, s);
+  if (P.xspace) {
   } else if (mixed) {
     launch_convert<float, double>(w.bvec.p, n, w.V.p, n * (w.m + 1), n, B, nullptr, 1.0, s);
   } else {
     launch_convert<double, double>(w.bvec.p, n, w.V.p, n * (w.m + 1), n, B, nullptr, 1.0, s);
   }
   int total = 0;
-  iters_out.assign(B, 0);
-  while (true) {
-    (void)hipMemcpyAsync(w.host_live.data(), live, B * sizeof(int), hipMemcpyDeviceToHost, s);
-    if (hipStreamSynchronize(s) != hipSuccess) return fail(DBAR_EDEVICE, "stream synchronize failed");
-    bool any = false;
-    for (int b = 0; b < B; ++b) any |= w.host_live[b] != 0;
-    if (P.box && total == 0) P.set_box(P.box, 0, w.host_box.data(), 1, nullptr);  // (read with the first flags)
+  gathered = false;
+  for (bool start = true;; start = false) {
+    // the check left the live flags in host_live; the box comes with the first ones
+    const int rc = start && P.box ? w.report({{P.box, w.host_box.data(), 4}}, s) : w.report({}, s);
+    if (rc) return rc;
+    bool any = false, all = true;
+    for (int b = 0; b < B; ++b) {
+      any |= w.host_live[b] != 0;
+      all &= w.host_live[b] != 0;
+    }
+    if (start && P.box) P.set_box(P.box, 0, w.host_box.data(), 1, nullptr);
+    // S = m = 0 for entries with b = 0 (no residual evaluation writes them)
+    if (start && P.xspace && !all) launch_zero_done(w, nullptr, cfg.method == 1, s);
     if (!any || total >= cfg.max_iter) break;
     const double rel = mixed ? cfg.inner_tol : 0.0;
     const double abs_tol = mixed ? 0.3 * cfg.tol : 0.5 * cfg.tol;
     hipLaunchKernelGGL(k_ctl_start, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, w.flag_stride, abs_tol,
                        rel, nullptr, B);
     int ran;
+    TileSpan span;
     // The first cycle of a mixed-precision x-space solve starts from |r| = |b| and asks its FP32 inner solve for
     // inner_tol of that, which FP32 arithmetic cannot better by many orders: with tol far below inner_tol its residual
     // evaluation is not the last one, and it leaves S and m unwritten (two N x N FP64 arrays per entry).  So that the
@@ -1650,18 +1727,20 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, std::vec
     // the condition estimate is taken from the first cycle (from x = 0: the longest, every entry in it)
     if (mixed) {
       ran = krylov_cycle<float>(P, w, cfg, cfg.max_iter - total, s);
-      end_cycle<float>(P, w, ran, w.r64.p, s, cfg.method, total == 0, outputs);
+      span = end_cycle<float>(P, w, ran, w.r64.p, s, cfg.method, total == 0, outputs);
     } else {
       ran = krylov_cycle<double>(P, w, cfg, cfg.max_iter - total, s);
-      end_cycle<double>(P, w, ran, w.V.p, s, cfg.method, total == 0);
+      span = end_cycle<double>(P, w, ran, w.V.p, s, cfg.method, total == 0);
     }
     total += ran;
-    hipLaunchKernelGGL(k_ctl_check, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, w.flag_stride,
-                       outputs ? cfg.tol : -1.0, 0, nullptr, nullptr, B);
+    launch_ctl_check(w, span, outputs ? cfg.tol : -1.0, 0, nullptr, nullptr, s);
+    // (plain, in x-space: S(0) and the entries' records are there once an evaluation has written S; if it was the last,
+    // the host has the results with the live flags)
+    gathered = P.xspace && cfg.method == 0 && outputs;
+    if (gathered) launch_gather(w, static_cast<const c64*>(w.S_dst(0)), nullptr, false, hres, s);
     if (mixed && !P.xspace) launch_convert<float, double>(w.r64.p, n, w.V.p, n * (w.m + 1), n, B, live, 1.0, s);
     if (ran == 0) break;
   }
-  if (hipStreamSynchronize(s) != hipSuccess) return fail(DBAR_EDEVICE, "stream synchronize failed");
   return DBAR_OK;
 }
 
@@ -1886,7 +1965,10 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
     if ((rc = make_pipeline(grid, w, &ln[l].P))) return rc;
     ln[l].P.xspace = cfg.xspace != 0;
     if (q_on_device) {
-      if (hipMemcpyAsync(w.Q64.p, Q, n * sizeof(c64), hipMemcpyDeviceToDevice, s) != hipSuccess)
+      // (a launch where its 16-byte loads are aligned: the runtime's copy takes a place in the stream ten times as long)
+      if (reinterpret_cast<uintptr_t>(Q) % 16 == 0)
+        launch_convert<double, double>(Q, 0, w.Q64.p, 0, n, 1, nullptr, 1.0, s);
+      else if (hipMemcpyAsync(w.Q64.p, Q, n * sizeof(c64), hipMemcpyDeviceToDevice, s) != hipSuccess)
         return fail(DBAR_EDEVICE, "Q copy failed");
     } else {
       // (checked on its first way up)
@@ -1927,21 +2009,18 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
       w.outS = cfg.xspace && out_on_device && S ? static_cast<char*>(S) + (size_t)k0 * n * sizeof(c64) : nullptr;
       w.outm = cfg.xspace && out_on_device && m ? static_cast<char*>(m) + (size_t)k0 * n * sizeof(c64) : nullptr;
       std::memcpy(hk, k + 2 * k0, (size_t)nb * sizeof(c64));
-      if (hipMemcpyAsync(w.kvals.p, hk, (size_t)nb * sizeof(c64), hipMemcpyHostToDevice, s) != hipSuccess)
-        return fail(DBAR_EDEVICE, "k upload failed");
       if (cfg.method == 1) {
         for (int b = 0; b < nb; ++b) {
           shifts[2 * b] = shift_of(k[2 * (k0 + b) + 1], grid->L);
           shifts[2 * b + 1] = shift_of(k[2 * (k0 + b)], grid->L);
         }
-        if (hipMemcpyAsync(w.shv.p, shifts, (size_t)nb * 2 * sizeof(int), hipMemcpyHostToDevice, s) !=
-            hipSuccess)
-          return fail(DBAR_EDEVICE, "shift upload failed");
       }
+      launch_words({{reinterpret_cast<const int*>(hk), static_cast<int*>(w.kvals.p), 4 * nb},
+                    {shifts, static_cast<int*>(w.shv.p), cfg.method == 1 ? 2 * nb : 0}}, s);
       launch_phase_tables(static_cast<const c64*>(w.kvals.p), N, grid->L, static_cast<c64*>(w.ex.p),
                           static_cast<c64*>(w.ey.p), static_cast<c32*>(w.ex32.p), static_cast<c32*>(w.ey32.p), nb, s);
-      std::vector<int> its;
-      if (const int brc = run_batch(P, w, cfg, s, its)) return brc;
+      bool gathered = false;
+      if (const int brc = run_batch(P, w, cfg, s, hres, gathered)) return brc;
       // outputs.  Plain on s: S and m from the last residual evaluation.  Iterated on s: S = f + h o (xi + a) (equation
       // Sform, formed in place in Fx) and m = h(f) + e_k F^{-1}(h/(xi - a)) (in place in mx) from that evaluation's
       // h, f and inverses.  On S: S = x and m = h(x) (plain), or formed from h below (iterated).  S0src holds S(0) for
@@ -1995,11 +2074,7 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
                            hipMemcpyDeviceToDevice, s) != hipSuccess)
           return fail(DBAR_EDEVICE, "m copy failed");
       }
-      hipLaunchKernelGGL(k_gather_results, dim3(ctl_blocks(nb)), dim3(64), 0, s, static_cast<const Ctl*>(w.ctl.p),
-                         S0src, n, hsrc, cfg.method == 1 ? static_cast<const int*>(w.shv.p) : nullptr, N,
-                         static_cast<EntryResult*>(w.results.p), nb);
-      (void)hipMemcpyAsync(hres, w.results.p, (size_t)nb * sizeof(EntryResult), hipMemcpyDeviceToHost, s);
-      (void)hipMemcpyAsync(w.host_live.data(), w.live.p, nb * sizeof(int), hipMemcpyDeviceToHost, s);
+      if (!gathered) launch_gather(w, S0src, hsrc, cfg.method == 1, hres, s);
       if (!out_on_device) {
         int src = DBAR_OK;
         if (S && Sout)

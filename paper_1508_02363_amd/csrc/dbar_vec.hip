@@ -164,22 +164,6 @@ __global__ void __launch_bounds__(kVecBlock) k_convert(const TI* in, size_t in_b
     y[i] = cvt<TO>(scale * cvt<double>(x[i]));
 }
 
-// out[b][v] = sum_blk part[b][v][blk], fixed order
-__global__ void __launch_bounds__(256) k_reduce(const double* part, int nval, TileSpan span, double* out,
-                                                const int* act) {
-  const int b = blockIdx.y, v = blockIdx.x;
-  if (act && !act[b]) return;
-  __shared__ double red[4];
-  const int nblk = span.count(b);
-  const double* p = part + ((size_t)b * nval + v) * span.stride;
-  double s = 0.0;
-  for (int i = threadIdx.x; i < nblk; i += 256) s += p[i];
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) out[(size_t)b * nval + v] = red[0] + red[1] + red[2] + red[3];
-}
-
 template <typename T>
 void launch_dots(const VecArgs& a, hipStream_t s) {
   TimerScope ts(kStageDots + (sizeof(T) == 4), (double)(a.nv + 1) * a.n * sizeof(cx<T>), a.B, a.act, s);
@@ -204,11 +188,6 @@ void launch_convert(const void* in, size_t in_bs, void* out, size_t out_bs, size
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL((k_convert<TO, TI>), dim3(blocks, B), dim3(kVecBlock), 0, s, static_cast<const TI*>(in), in_bs,
                      static_cast<TO*>(out), out_bs, n, act, scale);
-}
-void launch_reduce(const double* part, int nval, const TileSpan& span, double* out, int B, const int* act,
-                   hipStream_t s) {
-  TimerScope ts(kStageReduce, (double)nval * span.stride * sizeof(double), B, act, s);
-  hipLaunchKernelGGL(k_reduce, dim3(nval, B), dim3(256), 0, s, part, nval, span, out, act);
 }
 
 // ------------------------------------------------------------------------------------------------------------
