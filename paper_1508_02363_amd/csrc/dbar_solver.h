@@ -390,8 +390,6 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
 template <typename T>
 TileSpan end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t s, int method = 0, bool cond = true,
                    bool outputs = true);
-// condition estimate of each live entry from its last cycle's Hessenberg factor, where that cycle is the longest so far
-void launch_cond_estimate(Work& w, hipStream_t s);
 // residual check from the squared norms' block sums (first = 1: record ||b|| and reset the counters of the entries in
 // mask); tolv: per-entry tol; the checked entries' live flags also go to w.host_live
 void launch_ctl_check(Work& w, const TileSpan& span, double tol, int first, const int* mask, const double* tolv,

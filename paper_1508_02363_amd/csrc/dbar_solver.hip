@@ -223,67 +223,35 @@ __global__ void __launch_bounds__(kMomThreads) k_moments_givens(const double* pa
   }
 }
 
-// y = H^{-1} g (upper triangular jn x jn), coef_i = y_i sigma_i, zero beyond jn
-// One wave per entry: the factor's columns are staged in LDS by all lanes (their loads in flight together), then lane i
-// holds component i and the substitution runs column by column.
-__global__ void __launch_bounds__(64) k_ctl_trisolve(Ctl* ctl, const int* live, int B) {
-  const int b = blockIdx.x;
-  if (b >= B || !live[b]) return;
-  Ctl& c = ctl[b];
-  const int n = c.jn;
-  const int i = threadIdx.x;
+// y = H^{-1} g (upper triangular jn x jn), coef_i = y_i sigma_i, zero beyond jn: lane i holds component i and the
+// substitution runs column by column.  R: column l in R[l * (kMaxRestart + 1)].  One wave.
+DBAR_D void trisolve_wave(Ctl& c, const double* R, int n) {
   constexpr int LD = kMaxRestart + 1;
-  __shared__ double Hs[kMaxRestart * LD];
-  const double* Hc = c.H;
-#pragma unroll 8
-  for (int t = i; t < n * LD; t += 64) Hs[t] = Hc[t];
+  const int i = threadIdx.x & 63;
   double y = i < n ? c.g[i] : 0.0;
   const double sg = c.sigma[i];
-  __syncthreads();
-  const double d = i < n ? Hs[i * LD + i] : 0.0;
+  const double d = i < n ? R[i * LD + i] : 0.0;
   for (int l = n - 1; l >= 0; --l) {
     const double dl = bcast(d, l), yl = dl != 0.0 ? bcast(y, l) / dl : 0.0;
     if (i == l) y = yl;
-    if (i < l) y -= Hs[l * LD + i] * yl;
+    if (i < l) y -= R[l * LD + i] * yl;
   }
   c.coef[i] = i < n ? y * sg : 0.0;
   if (i == 0) c.coef[kMaxRestart] = 0.0;
 }
 
-// Condition estimate of one entry (one wave per entry): the extreme singular values of the upper-triangular factor R
-// (jn x jn, column j in H[j * (kMaxRestart + 1)]) that the Givens rotations leave of the cycle's Hessenberg matrix --
-// the same singular values as the (jn + 1) x jn Hessenberg matrix, and those lie inside A's (sigma_max(H) <= sigma_max(A),
-// sigma_min(H) >= sigma_min(A)), so the ratio estimates cond(A) from below.  Power iteration on R^T R for sigma_max and
-// inverse iteration (a forward and a back substitution per step) for sigma_min, lane i holding component i.  Taken only
-// when the cycle is longer than the one behind the current estimate (the longest cycle has seen most of the spectrum).
-// One wave, no trip through LDS on the serial chain: 91 -> 47 us for a 20-step cycle, 53 -> 26 us for an 8-step one.
+// Extreme singular values of R (n x n, zero below the diagonal, no zero on it), lane i holding component i: sigma_max^2 by
+// power iteration on R^T R, sigma_min^-2 by inverse iteration (a forward and a back substitution per step).  One wave each.
 constexpr int kCondIters = 12;
-__global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live) {
-  const int b = blockIdx.x;
-  if (live && !live[b]) return;
-  Ctl& c = ctl[b];
-  const int n = c.jn;
-  if (n <= c.kappa_n || n < 1) return;
-  const int i = threadIdx.x;
+DBAR_D double unit_start(int i, int n) {
+  const double x = i < n ? 1.0 + 0.01 * i : 0.0;
+  return x / sqrt(wsum(x * x));
+}
+DBAR_D double smax2_wave(const double* Rs, int n) {
   constexpr int LD = kMaxRestart + 1;
-  // the n x n factor staged in LDS once, zero below the diagonal: the iterations below read it many times, with no test
-  // around a read (their loads run ahead of the serial chain).  The columns' n LD values are read as one flat range,
-  // eight loads per thread in flight at a time.
-  __shared__ double Rs[kMaxRestart * LD];
-  const double* Hc = c.H;
-#pragma unroll 8
-  for (int t = i; t < n * LD; t += 64) Rs[t] = t % LD <= t / LD ? Hc[t] : 0.0;
-  __syncthreads();
-  const int ic = i < n ? i : n - 1;  // lanes beyond n read a column that is there
+  const int i = threadIdx.x & 63, ic = i < n ? i : n - 1;  // lanes beyond n read a column that is there
   auto R = [&](int row, int col) { return Rs[col * LD + row]; };
-  const double diag = R(ic, ic);
-  if (__ballot(!(diag != 0.0))) return;  // breakdown (exact solution reached): keep the previous estimate
-  // reciprocals of the diagonal, once: the substitutions below multiply instead of dividing on their serial chain
-  const double dinv = 1.0 / diag;
-  // sigma_max: x <- R^T R x, normalised
-  double x = i < n ? 1.0 + 0.01 * i : 0.0;
-  double nrm = sqrt(wsum(x * x));
-  x /= nrm;
+  double x = unit_start(i, n);
   double smax2 = 0.0;
   for (int it = 0; it < kCondIters; ++it) {
     double y = 0.0;  // (R x)_i = sum_{l >= i} R_il x_l
@@ -296,10 +264,15 @@ __global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live)
     smax2 = sqrt(wsum(z * z));  // |R^T R x| for |x| = 1
     x = smax2 > 0.0 ? z / smax2 : 0.0;
   }
-  // sigma_min: x <- (R^T R)^{-1} x = R^{-1} R^{-T} x, normalised
-  x = i < n ? 1.0 + 0.01 * i : 0.0;
-  nrm = sqrt(wsum(x * x));
-  x /= nrm;
+  return smax2;
+}
+DBAR_D double inv2_wave(const double* Rs, int n) {
+  constexpr int LD = kMaxRestart + 1;
+  const int i = threadIdx.x & 63, ic = i < n ? i : n - 1;
+  auto R = [&](int row, int col) { return Rs[col * LD + row]; };
+  // reciprocals of the diagonal, once: the substitutions below multiply instead of dividing on their serial chain
+  const double dinv = 1.0 / R(ic, ic);
+  double x = unit_start(i, n);
   double inv2 = 0.0;
   for (int it = 0; it < kCondIters; ++it) {
     double r = x, u = 0.0;  // R^T u = x (forward substitution, column by column; a component is final once it is read)
@@ -320,8 +293,42 @@ __global__ void __launch_bounds__(64) k_cond_estimate(Ctl* ctl, const int* live)
     inv2 = sqrt(wsum(v * v));  // |(R^T R)^{-1} x| for |x| = 1
     x = inv2 > 0.0 ? v / inv2 : 0.0;
   }
-  if (i == 0 && smax2 > 0.0 && inv2 > 0.0) {
-    c.kappa = fmax(c.kappa, sqrt(smax2 * inv2));
+  return inv2;
+}
+
+// The end of a cycle, one block per entry: the coefficients of the solution update (first wave) and, with cond, beside it
+// (a wave each) the extreme singular values of the upper-triangular factor R that the Givens rotations leave of the
+// cycle's Hessenberg matrix -- the same singular values as the (jn + 1) x jn Hessenberg matrix, and those lie inside A's
+// (sigma_max(H) <= sigma_max(A), sigma_min(H) >= sigma_min(A)), so their ratio estimates cond(A) from below.  Taken only
+// when the cycle is longer than the one behind the current estimate (the longest cycle has seen most of the spectrum).
+// Bound by the serial chain of the iterations (no trip through LDS on it but R's entries).  A 20-step cycle, the three one
+// after the other in two launches -> side by side: 6 + 48 -> 29 us; an 8-step one 7 + 18 -> 9 us.
+__global__ void __launch_bounds__(192) k_ctl_trisolve(Ctl* ctl, const int* live, int cond) {
+  const int b = blockIdx.x;
+  if (!live[b]) return;
+  Ctl& c = ctl[b];
+  const int n = c.jn, wave = threadIdx.x >> 6;
+  const bool estimate = cond && n > c.kappa_n;
+  constexpr int LD = kMaxRestart + 1;
+  // the factor staged in LDS once, zero below the diagonal: read as one flat range, eight loads per thread in flight
+  __shared__ double Rs[kMaxRestart * LD];
+  __shared__ double sv[2];
+  const double* Hc = c.H;
+#pragma unroll 8
+  for (int t = threadIdx.x; t < n * LD; t += blockDim.x) Rs[t] = t % LD <= t / LD ? Hc[t] : 0.0;
+  __syncthreads();
+  const int i = threadIdx.x & 63;
+  // (breakdown, the exact solution reached: keep the previous estimate)
+  const bool regular = estimate && !__ballot(i < n && !(Rs[i * LD + i] != 0.0));
+  if (wave == 0) trisolve_wave(c, Rs, n);
+  if (!regular) return;
+  if (wave > 0) {
+    const double x = wave == 1 ? smax2_wave(Rs, n) : inv2_wave(Rs, n);
+    if (i == 0) sv[wave - 1] = x;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && sv[0] > 0.0 && sv[1] > 0.0) {
+    c.kappa = fmax(c.kappa, sqrt(sv[0] * sv[1]));
     c.kappa_n = n;
   }
 }
@@ -1554,8 +1561,10 @@ TileSpan end_cycle(const Pipeline& P, Work& w, int nv, void* r_out, hipStream_t 
   const size_t n = w.n;
   Ctl* ctl = static_cast<Ctl*>(w.ctl.p);
   int* live = static_cast<int*>(w.live.p);
-  hipLaunchKernelGGL(k_ctl_trisolve, dim3(B), dim3(64), 0, s, ctl, live, B);
-  if (cond) launch_cond_estimate(w, s);
+  {
+    TimerScope ts(kStageControl, 0.0, B, nullptr, s);
+    hipLaunchKernelGGL(k_ctl_trisolve, dim3(B), dim3(cond ? 192 : 64), 0, s, ctl, live, cond ? 1 : 0);
+  }
   VecArgs va;
   va.B = B;
   va.act = live;
@@ -1624,12 +1633,6 @@ template int krylov_cycle<float>(const Pipeline&, Work&, const BatchCfg&, int, h
 template int krylov_cycle<double>(const Pipeline&, Work&, const BatchCfg&, int, hipStream_t);
 template TileSpan end_cycle<float>(const Pipeline&, Work&, int, void*, hipStream_t, int, bool, bool);
 template TileSpan end_cycle<double>(const Pipeline&, Work&, int, void*, hipStream_t, int, bool, bool);
-
-void launch_cond_estimate(Work& w, hipStream_t s) {
-  TimerScope ts(kStageControl, 0.0, w.B, nullptr, s);
-  hipLaunchKernelGGL(k_cond_estimate, dim3(w.B), dim3(64), 0, s, static_cast<Ctl*>(w.ctl.p),
-                     static_cast<const int*>(w.live.p));
-}
 
 void launch_ctl_check(Work& w, const TileSpan& span, double tol, int first, const int* mask, const double* tolv,
                       hipStream_t s) {
