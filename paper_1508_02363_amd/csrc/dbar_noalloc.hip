@@ -5,8 +5,8 @@
 // The scratch array holds, for grids up to N = kNoAllocMaxN:
 //   * the transform scratch of the operator (FP64: one N x N complex128 array; FP32: the transform array and the
 //     FP32 roundings of Q, S and the result, N x N complex64 each -- 32 N^2 bytes either way);
-//   * the per-k phase tables e^{-2i k2 x_j}, e^{-2i k1 y_j} (FP64 and FP32), k itself, the Taylor data (d_n, c_n,
-//     R(0)) and the per-tile partial sums of the moment reduction.
+//   * the per-k phase tables e^{-2i k2 x_j}, e^{-2i k1 y_j} (FP64 and FP32), the Taylor data (d_n, c_n, R(0))
+//     and the per-tile partial sums of the moment reduction.
 // Nothing in it has to start at zero: every call writes each part it reads before reading it.  All calls on one GPU
 // share that GPU's copy (it keeps the last call's contents), so calls that overlap on one GPU race: serialise them on
 // one stream.  The twiddle tables exp(-2 pi i j / N) of every power of two 8 <= N <= kNoAllocMaxN sit in a second
@@ -33,8 +33,8 @@ constexpr size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 constexpr size_t kTwEntries = 2 * (size_t)kNoAllocMaxN - 8;
 constexpr size_t kOffBig = 0;                                        // 32 N^2 bytes (see above)
 constexpr size_t kOffPhase = align256(kOffBig + 32 * kNMax);         // ex, ey (FP64), ex32, ey32 (FP32)
-constexpr size_t kOffK = align256(kOffPhase + (size_t)kNoAllocMaxN * 2 * (sizeof(c64) + sizeof(c32)));
-constexpr size_t kOffMom = align256(kOffK + sizeof(c64));            // coefG, dmom (FP64), dmom32
+constexpr size_t kOffMom =                                           // coefG, dmom (FP64), dmom32
+    align256(kOffPhase + (size_t)kNoAllocMaxN * 2 * (sizeof(c64) + sizeof(c32)));
 constexpr size_t kOffPartMom = align256(kOffMom + (size_t)kNMom * (2 * sizeof(c64) + sizeof(c32)));
 // moment partials: 2 kNMom values per tile, at most N tiles per entry (one line per tile)
 constexpr size_t kOffPartVec = align256(kOffPartMom + 2 * (size_t)kNMom * kNoAllocMaxN * sizeof(double));
@@ -122,8 +122,6 @@ static int noalloc_setup(int dev, unsigned char** out, const TwTables** tw) {
   return DBAR_OK;
 }
 
-__global__ void k_store_k(c64* kv, double kre, double kim) { *kv = c64{kre, kim}; }
-
 }  // namespace dbar
 
 using namespace dbar;
@@ -176,9 +174,7 @@ int dbar_apply_noalloc(const dbar_grid* grid, const void* Q_dev, const double* k
   P.part_mom = reinterpret_cast<double*>(base + kOffPartMom);
   P.part_vec = reinterpret_cast<double*>(base + kOffPartVec);
   P.xspace = false;  // the operator as written on S (Section 4 algorithm, step 4)
-  c64* kv = reinterpret_cast<c64*>(base + kOffK);
-  hipLaunchKernelGGL(k_store_k, dim3(1), dim3(1), 0, s, kv, k[0], k[1]);
-  launch_phase_tables(kv, N, grid->L, ex, ey, ex32, ey32, 1, s);
+  P.own_k = k;
   if (precision == DBAR_FP64) {
     void* T = base + kOffBig;
     P.apply<double>(S_dev, n, AS_dev, n, Q_dev, 0, T, 1, nullptr, 1.0, 1.0, nullptr, 0, false, s);

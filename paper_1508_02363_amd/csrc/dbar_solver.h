@@ -265,6 +265,7 @@ struct Pipeline {
   const void* tw32 = nullptr;
   const void* tail64 = nullptr;  // x-space tail tables (null beyond kTailTabMaxN)
   const void* tail32 = nullptr;
+  const double* own_k = nullptr;  // single xi-space application: k (host), whose tables the moments' launch makes
   const c64* ex = nullptr;
   const c64* ey = nullptr;
   const c32* ex32 = nullptr;
