@@ -11,13 +11,6 @@ static __constant__ double kInvFactC[kMaxM + 2] = {
     2.7557319223985888e-7, 2.5052108385441720e-8, 2.0876756987868100e-9, 1.6059043836821613e-10,
     1.1470745597729725e-11, 7.6471637318198164e-13, 4.7794773323873853e-14};
 
-DBAR_D double wsum(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
-}
-
-
 // lane l's x in every lane (l uniform: a register read, not a trip through LDS as __shfl is)
 DBAR_D double bcast(double x, int l) {
   const long long v = __builtin_bit_cast(long long, x);

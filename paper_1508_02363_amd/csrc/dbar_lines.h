@@ -252,12 +252,6 @@ DBAR_D int tail_index(int row, int col) {
 // ------------------------------------------------------------------------------------------------------------
 // Block reduction of per-thread FP64 values into global partials dst[v * stride]
 // ------------------------------------------------------------------------------------------------------------
-DBAR_D double wsum64(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
-}
-
 template <int NT, int NV>
 DBAR_D void block_reduce_store(const double (&vals)[NV], double* __restrict__ dst, size_t stride, double* scratch) {
   __syncthreads();  // scratch aliases the transform's LDS
@@ -265,9 +259,7 @@ DBAR_D void block_reduce_store(const double (&vals)[NV], double* __restrict__ ds
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      double x = vals[v];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+      const double x = wsum(vals[v]);
       if (lane == 0) scratch[wave * NV + v] = x;
     }
     __syncthreads();
@@ -492,19 +484,6 @@ struct OpRowsInvScaled : OpBase<T, N, Ept<T, N>::ROWS> {
 // formed once at the end: on a column d_n = sum_k C(n,k) x^{n-k} i^k mu_k, conj moment x mu_0 - i mu_1; on a row
 // d_n = sum_k C(n,k) (iy)^{n-k} mu_k, conj moment mu_1 - iy mu_0 (the binomial terms exceed |z|^n by at most
 // 2^{n/2}, i.e. < 50x at n = 11: a few ulps of FP64).
-// One step of a recursive-halving wave reduction: lanes with bit OFF clear keep the lower NV/2 of their values, the
-// others the upper half, each summed with its partner's copy of the same half (lane ^ OFF).
-template <typename T, int NV, int OFF>
-DBAR_D void halve_exchange(T (&x)[32], int lane) {
-  const bool hi = (lane & OFF) != 0;
-#pragma unroll
-  for (int i = 0; i < NV / 2; ++i) {
-    const T keep = hi ? x[i + NV / 2] : x[i];
-    const T send = hi ? x[i] : x[i + NV / 2];
-    x[i] = keep + __shfl_xor(send, OFF, 64);
-  }
-}
-
 template <typename T, int N, bool ALONG_X, int E>
 struct MomentsBase : OpBase<T, N, E> {
   using G = LineGeom<N, E>;
@@ -622,50 +601,23 @@ struct MomentsBase : OpBase<T, N, E> {
     double* sc = scratch;                 // [NG][NMU]
     double* colv = scratch + NG * NMU;    // [LN][NV]
     double* mus = colv + LN * NV;         // [LN][NMU]
-    if constexpr (ALONG_X && GS == 64) {
-      // a whole wave per row: recursive halving over the NMU = 32 values (those beyond NU are zero), five exchanges
-      // that each send half of a lane's values and keep the other half summed with the partner's, then one plain
-      // exchange; lane l ends with value l >> 1 summed over the wave (32 shuffles per lane instead of 6 NU)
-      static_assert(NMU == 32, "the halving below is laid out for 32 values");
-      T x[NMU];
+    if constexpr (ALONG_X || SHFL) {
+      // over the lanes of a group: halved as far as NU splits evenly (24 or 32 values over 64 lanes: 30 exchanges per
+      // lane instead of 6 NU)
+      constexpr int OFF = ALONG_X ? GS / 2 : 32, LAST = ALONG_X ? 1 : LN;
+      const int base = reduce_lanes<NU, OFF, LAST>(acc.v, lane);
+      const int g = ALONG_X ? threadIdx.x / GS : wave * LN + lane % LN;
+      if ((lane & reduce_copies<NU, OFF, LAST>()) == 0) {
 #pragma unroll
-      for (int q = 0; q < NMU; ++q) x[q] = q < NU ? acc.v[q] : T(0);
-      halve_exchange<T, 32, 32>(x, lane);
-      halve_exchange<T, 16, 16>(x, lane);
-      halve_exchange<T, 8, 8>(x, lane);
-      halve_exchange<T, 4, 4>(x, lane);
-      halve_exchange<T, 2, 2>(x, lane);
-      x[0] += __shfl_xor(x[0], 1, 64);
-      if ((lane & 1) == 0) sc[wave * NMU + (lane >> 1)] = static_cast<double>(x[0]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < NU; ++q) {
-        T x = acc.v[q];
-        if constexpr (ALONG_X) {
-#pragma unroll
-          for (int off = GS / 2; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
-        } else if constexpr (SHFL) {
-#pragma unroll
-          for (int off = 32; off >= LN; off >>= 1) x += __shfl_xor(x, off, 64);
-        }
-        acc.v[q] = x;
+        for (int i = 0; i < reduce_left<NU, OFF, LAST>(); ++i) sc[g * NMU + base + i] = static_cast<double>(acc.v[i]);
       }
-      int g = -1;
-      if constexpr (ALONG_X) {
-        if (threadIdx.x % GS == 0) g = threadIdx.x / GS;
-      } else if constexpr (SHFL) {
-        if (lane < LN) g = wave * LN + lane;
-      } else {
-        g = threadIdx.x;  // thread t serves column t % LN
-      }
-      if (g >= 0) {
+    } else {  // thread t serves column t % LN
 #pragma unroll
-        for (int q = 0; q < NMU; ++q) sc[g * NMU + q] = q < NU ? static_cast<double>(acc.v[q]) : 0.0;
-      }
+      for (int q = 0; q < NU; ++q) sc[threadIdx.x * NMU + q] = static_cast<double>(acc.v[q]);
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < LN * NMU; t += NT) {
-      const int c = t / NMU, q = t % NMU;
+    for (int t = threadIdx.x; t < LN * NU; t += NT) {
+      const int c = t / NU, q = t % NU;
       double v = 0.0;
       if constexpr (ALONG_X) {
         constexpr int GPL = TPL / GS;  // groups per row
@@ -1165,15 +1117,15 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false, Ept<T, N>::TAIL_ROWS> {
       constexpr int NW = NT / 64;
       const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
       __syncthreads();  // scratch aliases the LDS the stores and the norm reduction used
-      double x = wsum64(acc.sdot);
+      double x = wsum(acc.sdot);
       if (lane == 0) scratch[(nv - 1) * NW + wave] = x;
       if (a.dot_self) {
-        x = wsum64(acc.v[0]);
+        x = wsum(acc.v[0]);
         if (lane == 0) scratch[nv * NW + wave] = x;
       }
 #pragma unroll 1
       for (int i = 0; i < nv - 1; ++i) {
-        x = i < skip ? 0.0 : wsum64(partial(i));
+        x = i < skip ? 0.0 : wsum(partial(i));
         if (lane == 0) scratch[i * NW + wave] = x;
       }
       __syncthreads();

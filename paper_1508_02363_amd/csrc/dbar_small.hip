@@ -111,19 +111,6 @@ DBAR_D double uniform(double x) {
 }
 DBAR_D float uniform(float x) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); }
 
-// One step of a recursive-halving reduction over lanes OFF apart (see halve_exchange): the lower NV / 2 values stay with
-// the lanes whose bit OFF is clear, the upper half with the others.
-template <typename T, int NV, int OFF>
-DBAR_D void halve(T* x, int lane) {
-  const bool hi = (lane & OFF) != 0;
-#pragma unroll
-  for (int i = 0; i < NV / 2; ++i) {
-    const T keep = hi ? x[i + NV / 2] : x[i];
-    const T send = hi ? x[i] : x[i + NV / 2];
-    x[i] = keep + __shfl_xor(send, OFF, 64);
-  }
-}
-
 // 1/r to about one ulp for r = 0 (infinite, unused) and the normal range: the hardware estimate and two Newton steps
 DBAR_D double recip_newton(double r) {
   double y = __builtin_amdgcn_rcp(r);
@@ -160,29 +147,10 @@ DBAR_D void small_moments(const LineArgs& a, int b, const cx<T>* v, int row, int
     }
   }
   const int lane = threadIdx.x & 63;
-  int base = 0;
-  bool mine = true;
-  constexpr int HALVED = S::TPL < 8 ? S::TPL : 8;  // (24 and 32 sums split evenly three times)
-  constexpr int KEEP = NV / HALVED;
-  static_assert(NV % HALVED == 0, "the halving splits the sums evenly");
-  if constexpr (HALVED == 8) {
-    constexpr int O = S::TPL / 8;
-    halve<T, NV, 4 * O>(acc, lane);
-    halve<T, NV / 2, 2 * O>(acc, lane);
-    halve<T, NV / 4, O>(acc, lane);
-    base = ((lane & (4 * O)) ? NV / 2 : 0) + ((lane & (2 * O)) ? NV / 4 : 0) + ((lane & O) ? NV / 8 : 0);
-    if constexpr (O == 2) {
-#pragma unroll
-      for (int i = 0; i < KEEP; ++i) acc[i] += __shfl_xor(acc[i], 1, 64);
-      mine = (lane & 1) == 0;
-    }
-    static_assert(O <= 2, "at most sixteen threads per row");
-  } else {
-    static_assert(S::TPL == 4, "four, eight or sixteen threads per row");
-    halve<T, NV, 2>(acc, lane);
-    halve<T, NV / 2, 1>(acc, lane);
-    base = ((lane & 2) ? NV / 2 : 0) + ((lane & 1) ? NV / 4 : 0);
-  }
+  constexpr int OFF = S::TPL / 2;
+  const int base = reduce_lanes<NV, OFF, 1>(acc, lane);
+  const bool mine = (lane & reduce_copies<NV, OFF, 1>()) == 0;
+  constexpr int KEEP = reduce_left<NV, OFF, 1>();
   double* mu = reinterpret_cast<double*>(sh.data);  // [row][S::MU]
   double* P = mu + N * S::MU;                       // [half of the rows][k, l][re, im]
   __syncthreads();                                  // the data area is free
@@ -422,23 +390,17 @@ __global__ void __launch_bounds__((SmallGeom<T, N>::NT), (SmallGeom<T, N>::NW >=
       double p = 0.0;
 #pragma unroll
       for (int s = 0; s < S::E; ++s) p += rdot(Vi[jt + s * S::TPL], v[s]);
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        p += __shfl_xor(p, off, 64);
-        sdot += __shfl_xor(sdot, off, 64);
-        nrm += __shfl_xor(nrm, off, 64);
-      }
+      p = wsum(p);
+      sdot = wsum(sdot);
+      nrm = wsum(nrm);
       if (lane == 0) {
         sh.red[wave] = p;
         sh.red[S::NW + wave] = sdot;
         sh.red[2 * S::NW + wave] = nrm;
       }
     } else {
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        sdot += __shfl_xor(sdot, off, 64);
-        nrm += __shfl_xor(nrm, off, 64);
-      }
+      sdot = wsum(sdot);
+      nrm = wsum(nrm);
       if (lane == 0) {
         sh.red[(nv - 1) * S::NW + wave] = sdot;
         sh.red[nv * S::NW + wave] = nrm;

@@ -15,12 +15,6 @@ DBAR_D cx<T> ld(const void* p, size_t i) {
   return static_cast<const cx<T>*>(p)[i];
 }
 
-DBAR_D double wave_sum(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
-}
-
 // part[b][i][blk] = sum over the block's chunk of Re(conj(V_i) w), i < nv; optionally part[b][nv][blk] = |w|^2
 template <typename T>
 __global__ void __launch_bounds__(kVecBlock) k_dots(VecArgs a) {
@@ -58,7 +52,7 @@ __global__ void __launch_bounds__(kVecBlock) k_dots(VecArgs a) {
 #pragma unroll
         for (int e = 0; e < kVecEPT; ++e) acc += norm2(wv[e]);
       }
-      acc = wave_sum(acc);
+      acc = wsum(acc);
       if (lane == 0) red[wave][ii] = acc;
     }
     __syncthreads();
@@ -109,7 +103,7 @@ __global__ void __launch_bounds__(kVecBlock) k_update(VecArgs a) {
     }
   }
   if (a.want_self) {
-    nrm = wave_sum(nrm);
+    nrm = wsum(nrm);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = nrm;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -216,7 +210,7 @@ __global__ void __launch_bounds__(256) k_box_sums(const c64* Q, size_t Q_bs, int
   for (int i = 0; i < kBoxTile / 4; ++i) {
     const int row = ty * kBoxTile + wave + 4 * i;
     ce += e[i];
-    const double r = wave_sum(e[i]);
+    const double r = wsum(e[i]);
     if (lane == 0 && row < N) rowp[(size_t)tx * N + row] = r;
   }
   cs[wave][lane] = ce;
