@@ -19,11 +19,12 @@ DBAR_D double bcast(double x, int l) {
 }
 
 // c_n from d_n: (-i/2)^n d_n / n! (equation fourreeg4 with Gchoice; (-i/2)^n = (-i)^n 2^-n exactly)
-DBAR_D c64 taylor_coef(int n, c64 d) {
+DBAR_D c64 taylor_power(int n, c64 d) {  // (-i/2)^n d
   const double s = ldexp(1.0, -n);
-  const c64 p = (n & 3) == 0 ? c64{s, 0.0} : (n & 3) == 1 ? c64{0.0, -s} : (n & 3) == 2 ? c64{-s, 0.0} : c64{0.0, s};
-  return kInvFactC[n] * (p * d);
+  const c64 p = s * d;
+  return (n & 3) == 0 ? p : (n & 3) == 1 ? mul_mi(p) : (n & 3) == 2 ? -p : mul_i(p);
 }
+DBAR_D c64 taylor_coef(int n, c64 d) { return kInvFactC[n] * taylor_power(n, d); }
 
 // One Hessenberg column in a wave's registers: lane i holds sigma_i, hsum_i and rotation i, and the rotations run
 // through all of them with register reads (a single thread that walks the record in memory waits for each term).

@@ -26,6 +26,8 @@
 namespace dbar {
 namespace {
 
+constexpr int kMaxM1 = kMaxM + 1;
+
 template <typename T, int N>
 struct SmallGeom {
   static constexpr int E = N == 64 ? 8 : 4;
@@ -60,6 +62,7 @@ struct SmallShared {
   c64 coefG[kNMom];
   cx<T> d[kMaxM + 1];
   double ypow[N * (kMaxM + 2)];  // y_row^l
+  double binom[kMaxM1 * kMaxM1], invfact[kMaxM1];
   T e1[2][2][N];                 // e^{-(xi - a)^2} of either pass, along xi1 and xi2
   double red[(kMaxRestart + 2) * SmallGeom<T, N>::NW];
   // the GMRES record of the cycle (Ctl's fields of the same names)
@@ -177,28 +180,31 @@ DBAR_D void small_moments(const LineArgs& a, int b, const cx<T>* v, int row, int
     P[half * S::NP + i] = x0 + x1;
   }
   __syncthreads();
-  const int n = threadIdx.x;
-  if (n < kNMom) {
-    // slot of P_kl: the pairs of smaller l come first
-    auto at = [&](int k, int l) {
-      const int i = 2 * (l * nl - l * (l - 1) / 2 + k);
-      return c64{P[i] + P[S::NP + i], P[i + 1] + P[S::NP + i + 1]};
-    };
-    if (n == kMaxM + 1) {
-      const c64 p10 = at(1, 0), p01 = at(0, 1);
-      sh.coefG[n] = c64{0.0, -0.5} * (wscale * c64{p10.re + p01.im, p10.im - p01.re});
-    } else {
-      c64 d{0.0, 0.0};
-      if (n <= a.M) {
-        for (int k = 0; k <= n; ++k) {
-          const c64 p = kBinom.v[n][k] * at(k, n - k);
-          const int e = (n - k) & 3;  // times i^{n-k}
-          d = d + (e == 0 ? p : e == 1 ? mul_i(p) : e == 2 ? -p : mul_mi(p));
-        }
-        d = wscale * d;
+  // sixteen lanes per Taylor slot, one term each
+  const int k = threadIdx.x & 15;
+  for (int n = threadIdx.x >> 4; n < kNMom; n += S::NT / 16) {
+    c64 p{0.0, 0.0};
+    const bool dt = n == kMaxM + 1;  // P_10 - i P_01
+    if (dt ? k < 2 : n <= a.M && k <= n) {
+      const int l = dt ? 1 - k : n - k, i = 2 * (l * nl - l * (l - 1) / 2 + k);  // (the pairs of smaller l come first)
+      p = c64{P[i] + P[S::NP + i], P[i + 1] + P[S::NP + i + 1]};
+      if (dt) {
+        if (k == 0) p = mul_mi(p);
+      } else {
+        p = sh.binom[n * kMaxM1 + k] * p;
+        const int e = l & 3;  // times i^{n-k}
+        p = e == 0 ? p : e == 1 ? mul_i(p) : e == 2 ? -p : mul_mi(p);
       }
-      sh.d[n] = cvt<T>(d);
-      sh.coefG[n] = n <= a.M ? taylor_coef(n, d) : c64{0.0, 0.0};
+    }
+    const c64 d{wscale * add_xor<1>(add_xor<2>(add_xor<4>(add_xor<8>(p.re)))),
+                wscale * add_xor<1>(add_xor<2>(add_xor<4>(add_xor<8>(p.im))))};
+    if (k == 0) {
+      if (dt) {
+        sh.coefG[n] = c64{0.0, -0.5} * d;
+      } else {
+        sh.d[n] = cvt<T>(d);
+        sh.coefG[n] = taylor_power(n, sh.invfact[n] * d);
+      }
     }
   }
   __syncthreads();
@@ -343,6 +349,8 @@ __global__ void __launch_bounds__((SmallGeom<T, N>::NT), (SmallGeom<T, N>::NW >=
     sh.sigma[0] = c.sigma[0];
     sh.g[0] = c.g[0];
   }
+  for (int t = threadIdx.x; t < kMaxM1 * kMaxM1; t += S::NT) sh.binom[t] = kBinom.v[t / kMaxM1][t % kMaxM1];
+  if (threadIdx.x < kMaxM1) sh.invfact[threadIdx.x] = kInvFactC[threadIdx.x];
   for (int t = threadIdx.x; t < N; t += S::NT) {
     const double y = xgrid<N>(t, sa.first.L);
     double p = 1.0;
