@@ -13,11 +13,12 @@
 // (rows of one wave then start 16 banks apart).  Eight elements per thread at N = 64 (512 threads, up to 256 VGPRs, one
 // block per CU), four below; sixteen waves with four elements each spend more on exchanges and spill (N = 64 FP64).
 //
-// What bounds it: the chain of a step inside one block, about 67 thousand cycles at N = 64 in FP64 (sum of P_kl and the
-// Taylor slots 11, division with its polynomial 10, tail 10, Gram-Schmidt products and first decision 11, update 5, Givens
-// 3, row moments 3, the four transforms and two transposes 13); LDS allows a second block in FP32 only.  Measured, launch
-// per stage -> whole cycle: a scattering transform and its inverse on 64^2 (2 x 4096 entries) 11.7 -> 7.0 ms, one FP64
-// problem at N = 64 1.15 -> 0.78 ms, 4096 problems 20.3 -> 13.1 ms.  N = 128 does not fit one block's LDS.
+// What bounds it: the chain of a step inside one block, about 55 thousand cycles at N = 64 in FP64 (division with its
+// polynomial 10, tail 14, the four transforms and two transposes 13, moments 10, Gram-Schmidt products, decision and update
+// 7, Givens 3); LDS and registers allow one block per CU.  Measured, launch per stage -> whole cycle: a potential
+// reconstructed on 64^2 (4096 problems) 11.7 -> 6.1 ms, one FP64 problem at N = 64 1.15 -> 0.64 ms, 4096
+// problems 20.3 -> 11.3 ms.  N = 128 does not fit one block's LDS.  The previous basis vector stays in LDS (its products
+// and its part of the update read it there: 4096 problems 12.3 -> 11.3 ms, what is left of the L2 goes to v_j).
 #include "dbar_ctl.h"
 #include "dbar_launch.h"
 #include "dbar_lines.h"
@@ -59,6 +60,7 @@ struct SmallArgs {
 template <typename T, int N>
 struct SmallShared {
   alignas(16) unsigned char data[SmallGeom<T, N>::kBytes];
+  alignas(16) cx<T> prev[N * N];  // v_{j-1}, row layout, each thread's own elements (element s of thread t at s NT + t)
   c64 coefG[kNMom];
   cx<T> d[kMaxM + 1];
   double ypow[N * (kMaxM + 2)];  // y_row^l
@@ -394,10 +396,9 @@ __global__ void __launch_bounds__((SmallGeom<T, N>::NT), (SmallGeom<T, N>::NW >=
     const int nv = j - lo + 1;
     double x;
     if (nv == 2) {  // a windowed step: its three sums side by side
-      const cx<T>* Vi = V + (size_t)lo * n + row * N;
       double p = 0.0;
 #pragma unroll
-      for (int s = 0; s < S::E; ++s) p += rdot(Vi[jt + s * S::TPL], v[s]);
+      for (int s = 0; s < S::E; ++s) p += rdot(sh.prev[s * S::NT + tid], v[s]);
       p = wsum(p);
       sdot = wsum(sdot);
       nrm = wsum(nrm);
@@ -461,11 +462,21 @@ __global__ void __launch_bounds__((SmallGeom<T, N>::NT), (SmallGeom<T, N>::NW >=
 #pragma unroll
       for (int s = 0; s < S::E; ++s) w[s] = cvt<double>(v[s]);
 #pragma unroll 1
-      for (int i = lo; i <= j; ++i) {
+      for (int i = lo; i < j - 1; ++i) {
         const double cf = sh.coef[i];
         const cx<T>* Vi = V + (size_t)i * n + row * N;
 #pragma unroll
         for (int s = 0; s < S::E; ++s) w[s] = w[s] - cf * cvt<double>(Vi[jt + s * S::TPL]);
+      }
+      const bool two = j - 1 >= lo;
+      const double cp = two ? sh.coef[j - 1] : 0.0, cj = sh.coef[j];
+      const cx<T>* Vr = Vj + row * N;
+#pragma unroll
+      for (int s = 0; s < S::E; ++s) {
+        const cx<T> vj = Vr[jt + s * S::TPL];
+        if (two) w[s] = w[s] - cp * cvt<double>(sh.prev[s * S::NT + tid]);
+        w[s] = w[s] - cj * cvt<double>(vj);
+        sh.prev[s * S::NT + tid] = vj;
       }
       cx<T>* out = V + (size_t)(j + 1) * n + row * N;
       nrm = 0.0;
