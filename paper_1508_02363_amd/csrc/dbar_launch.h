@@ -27,6 +27,30 @@ enum class LineOp : int {
                             // optional |out|^2 -> part and Gram-Schmidt products -> dot_part
 };
 
+// Tiles (partial sums) of a row launch, per entry: all of them, or those of the entry's box.
+struct TileSpan {
+  int stride = 0;              // tiles of the whole grid: the stride between the partials of one value
+  int rows = 1;                // rows per tile
+  const int* box = nullptr;    int box_bs = 0;
+  DBAR_HD int count(int b) const {
+    return box ? (box[(size_t)b * box_bs + 1] - box[(size_t)b * box_bs]) / rows : stride;
+  }
+};
+
+struct Ctl;
+// The Gram-Schmidt coefficients of the step that a RowsFwdMoments launch applies, formed by the launch itself: part, span,
+// .. as ctl_coef_entry takes them (part null: the coefficients are there already).
+struct CoefReq {
+  const double* part = nullptr;
+  TileSpan span;
+  int nval = 0, j = 0, m = 0, lo = 0, skip = 0, fs = 0;
+  const int* full = nullptr;
+  int* act = nullptr;
+  Ctl* ctl = nullptr;
+};
+// Largest grid whose RowsFwdMoments can do so (on larger ones the launches are long beside one of a few microseconds).
+constexpr int kOwnCoefMaxN = 512;
+
 struct LineArgs {
   int B = 1;                   // batch entries (grid.y)
   const int* act = nullptr;    // per-entry active flag (nullptr = all active)
@@ -77,6 +101,7 @@ struct LineArgs {
   double upd_sign = 1.0;       // -1: in += sum coef_i V_i
   int upd_v32 = 0;             // the V_i are FP32 (an FP64 launch updating with an FP32 basis)
   int upd_zero = 0;            // the input counts as zero (its loaded values are ignored)
+  CoefReq own;                 // the update's coefficients come from the products' partials (upd_coef unused)
   void* upd_out = nullptr;
   double* upd_part = nullptr;
   // x-space stages: the index box {row0, row1, col0, col1} that holds the potential (k_box_cut), one per entry at
@@ -90,15 +115,6 @@ struct LineArgs {
   double box_fr = 1.0, box_fc = 1.0;  // rows and columns of the box over N (byte accounting)
 };
 
-// Tiles (partial sums) of a row launch, per entry: all of them, or those of the entry's box.
-struct TileSpan {
-  int stride = 0;              // tiles of the whole grid: the stride between the partials of one value
-  int rows = 1;                // rows per tile
-  const int* box = nullptr;    int box_bs = 0;
-  DBAR_HD int count(int b) const {
-    return box ? (box[(size_t)b * box_bs + 1] - box[(size_t)b * box_bs]) / rows : stride;
-  }
-};
 // Rows of a box are whole tiles of the row launches (of either precision) and its columns whole kBoxCols groups.
 constexpr int kBoxCols = 8;
 // Smallest grid on which x-space solves keep to the potential's index box: on smaller ones a row tile is most of the

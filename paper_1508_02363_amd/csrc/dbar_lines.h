@@ -27,6 +27,7 @@
 // entries, FP64, a sum of three Gaussians: 134 -> 47, 93 -> 73, 153 -> 85 us; 11.4 -> 7.7 ms.
 #pragma once
 
+#include "dbar_ctl.h"
 #include "dbar_fft.h"
 #include "dbar_launch.h"
 
@@ -442,6 +443,7 @@ struct OpBase {
   // the blocks of one tile for every entry of the batch are dispatched together, on one XCD (k_lines): for stages
   // that read an array all entries share (the potential), whose rows then stay in that XCD's L2 while the entries pass
   static constexpr bool TILE_MAJOR = false;
+  static constexpr bool OWN_COEF = false;
   DBAR_D bool active(int b) const { return a.act == nullptr || a.act[b] != 0; }
   DBAR_D const cx<T>* inp(int b) const { return static_cast<const cx<T>*>(a.in) + (size_t)b * a.in_bs; }
   DBAR_D cx<T>* outp(int b) const { return static_cast<cx<T>*>(a.out) + (size_t)b * a.out_bs; }
@@ -662,7 +664,9 @@ struct OpColsInvMoments : MomentsBase<T, N, false, Ept<T, N>::MOMENT_COLS> {
 // upd_nv of them (FP64 accumulation, as the vector kernels; V in FP32 if upd_v32), and stores s back in place: the
 // Gram-Schmidt step that produced s (with its |s|^2 partials in upd_part[b][tile]), or the solution update
 // x += sum y_i V_i of a cycle end (upd_sign -1) -- the operator's first launch reads s anyway.
-template <typename T, int N>
+// OWN: the update's coefficients are formed by the launch itself (CoefReq), a kernel of its own: its registers cost a full
+// batch 8 percent
+template <typename T, int N, bool OWN = false>
 struct OpRowsFwdMoments : MomentsBase<T, N, true, Ept<T, N>::FWD_MOMENTS> {
   using G = LineGeom<N, Ept<T, N>::FWD_MOMENTS>;
   static constexpr int DIR1 = -1;
@@ -673,6 +677,13 @@ struct OpRowsFwdMoments : MomentsBase<T, N, true, Ept<T, N>::FWD_MOMENTS> {
   using Pre = Box<N>;
   using Acc = typename MomentsBase<T, N, true, Ept<T, N>::FWD_MOMENTS>::Acc;
   DBAR_D void prologue(int b, Pre& p) const { p = entry_box<N>(this->a, b); }
+  static constexpr bool OWN_COEF = OWN;
+  // coef_{lo + i} = sigma^2 <v_{lo + i}, w> as ctl_coef_entry forms it (every wave for itself)
+  DBAR_D static double own_coef(const CoefReq& o, int b, int i) {
+    const double sg = o.ctl[b].sigma[o.lo + i];
+    const double h = wave_reduce(o.part + ((size_t)b * o.nval + i) * o.span.stride, o.span.count(b));
+    return sg * sg * h;
+  }
   DBAR_D cx<T> load(int b, int row, int pos, const Pre& p) const {
     return box_load<T>(entry_rsrc<T, N>(this->inp(b)), row * N + pos, p.col(pos));
   }
@@ -682,12 +693,15 @@ struct OpRowsFwdMoments : MomentsBase<T, N, true, Ept<T, N>::FWD_MOMENTS> {
     const LineArgs& a = this->a;
     if (a.upd_coef) {
       const double* coef = a.upd_coef + (size_t)b * a.upd_coef_bs;
+      const int own_lo = OWN && a.own.full && !a.own.full[b] ? a.own.skip : 0;  // (the entry's own window)
       c64 w[G::RMAX];
 #pragma unroll
       for (int s = 0; s < G::RMAX; ++s) w[s] = a.upd_zero ? c64{0.0, 0.0} : cvt<double>(v[s]);
 #pragma unroll 1
       for (int i = 0; i < a.upd_nv; ++i) {
-        const double c = a.upd_sign * coef[i];
+        double c = 0.0;
+        if constexpr (!OWN) c = a.upd_sign * coef[i];
+        else if (i >= own_lo) c = own_coef(a.own, b, i);
         if (c == 0.0) continue;  // also keeps never-written basis slots (any bit pattern) out of the sum
         if (sizeof(T) == 8 && a.upd_v32) {
           const Rsrc Vi = entry_rsrc<float, N>(static_cast<const c32*>(a.dotV) + (size_t)b * a.dotV_bs +
@@ -1217,6 +1231,17 @@ __global__ void __launch_bounds__((LINES * Op::G::TPL), (MinWaves<LINES * Op::G:
       k /= nb;
     } else {
       b = blockIdx.y;
+      if constexpr (Op::OWN_COEF) {
+        // The blocks beyond the entries take the step's coefficients to its record and decide on its end, beside the
+        // update.  An entry that ends there may still be updated and transformed by blocks that read its flag before:
+        // nothing uses what they write (the flag is off for every later launch of the cycle).
+        if (b >= op.a.B) {
+          const CoefReq& o = op.a.own;
+          if (NT >= 64 && blockIdx.x < op.a.B && o.act[blockIdx.x])
+            ctl_coef_entry(blockIdx.x, o.ctl, o.part, o.nval, o.span, o.act, o.fs, o.j, 0, 1, o.m, o.lo, o.skip, o.full);
+          return;
+        }
+      }
     }
     if (!op.active(b)) return;
     int t0 = 0, cnt = NTILES;
@@ -1334,7 +1359,7 @@ void launch_op(const LineArgs& a, hipStream_t s) {
     static_assert(N / LINES < kSpreadTiles || STEP % 8 == 0, "whole rounds");
     if (a.box && !a.box_full) tiles = (a.box_rows / LINES + STEP - 1) / STEP * STEP;
   }
-  const dim3 grid = Op::TILE_MAJOR ? dim3(tiles * a.B) : dim3(tiles, a.B);
+  const dim3 grid = Op::TILE_MAJOR ? dim3(tiles * a.B) : dim3(tiles, a.B + (Op::OWN_COEF ? 1 : 0));
   hipLaunchKernelGGL((k_lines<T, N, LINES, COLS, Op>), grid, dim3(NT), 0, s, op);
 }
 
@@ -1365,7 +1390,15 @@ void launch_lines(LineOp op, const LineArgs& a, hipStream_t s) {
     case LineOp::ColsFwdPotential: launch_cols<T, N, OpColsFwdPotential<T, N>>(a, s); break;
     case LineOp::ColsFwdPlain: launch_cols<T, N, OpColsPlain<T, N, -1>>(a, s); break;
     case LineOp::ColsInvPlain: launch_cols<T, N, OpColsPlain<T, N, +1>>(a, s); break;
-    case LineOp::RowsFwdMoments: launch_op<T, N, false, OpRowsFwdMoments<T, N>>(a, s); break;
+    case LineOp::RowsFwdMoments:
+      if constexpr (N >= 64 && N <= kOwnCoefMaxN) {
+        if (a.own.part) {
+          launch_op<T, N, false, OpRowsFwdMoments<T, N, true>>(a, s);
+          break;
+        }
+      }
+      launch_op<T, N, false, OpRowsFwdMoments<T, N>>(a, s);
+      break;
     case LineOp::ColsFwdRegularInv: launch_cols<T, N, OpColsFwdRegInv<T, N>>(a, s); break;
     case LineOp::RowsInvTailEpilogue: launch_op<T, N, false, OpRowsInvTailEpi<T, N>>(a, s); break;
   }

@@ -245,6 +245,7 @@ struct UpdReq {
   // |v|^2 partials in part
   Ctl* ctl = nullptr;
   int fs = 0, j = 0, m = 0;
+  CoefReq own;             // with a partials pointer: the launch forms the coefficients itself
 };
 
 struct DotReq {

@@ -38,21 +38,6 @@ int fail(int code, const std::string& msg) {
 // ------------------------------------------------------------------------------------------------------------
 // Control kernels
 // ------------------------------------------------------------------------------------------------------------
-// sum of p[0 .. nblk) over one wave (every lane gets it), in an order fixed by nblk.  Eight independent partial sums
-// per lane: the loads of a chunk are in flight together.
-DBAR_D double wave_reduce(const double* __restrict__ p, int nblk) {
-  double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  int i = threadIdx.x & 63;
-  for (; i + 7 * 64 < nblk; i += 8 * 64) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) a[u] += p[i + u * 64];
-  }
-#pragma unroll
-  for (int u = 0; u < 7; ++u)
-    if (i + u * 64 < nblk) a[u] += p[i + u * 64];
-  return wsum(((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
-}
-
 // Taylor slot n of entry b from the sums (re, im) of its moment: d_n = w sum and c_n; slot kMaxM + 1: the conj(z) moment,
 // R(0) = (-i/2) dt.
 DBAR_D void moments_slot(int b, int n, c64 sum, double wscale, int M, c64* coefG, c64* dmom, c32* dmom32) {
@@ -101,43 +86,7 @@ __global__ void __launch_bounds__(kMomThreads) k_moments(const double* part, Til
   moments_pair(b, blockIdx.x, part, span, wscale, M, coefG, dmom, dmom32);
 }
 
-// Column j of the Hessenberg matrix from hsum and beta = ||v_{j+1}|| (unnormalised basis: column j is sigma_j times the
-// products of A v_j), the previous Givens rotations applied, the new rotation, g and the residual estimate |g_{j+1}|.
-// One whole wave (top, mine: hess_rotate's); returns the estimate.
-DBAR_D double givens_commit(Ctl& c, int j, double beta, double top, double mine) {
-  const int lane = threadIdx.x & 63;
-  double* col = c.H + (size_t)j * (kMaxRestart + 1);
-  const double sub = c.sigma[j] * beta, gj = c.g[j];
-  const double den = hypot(top, sub);
-  const double cs = den > 0.0 ? top / den : 1.0, sn = den > 0.0 ? sub / den : 0.0;
-  const double resid = fabs(-sn * gj);
-  if (lane < j) col[lane] = mine;
-  if (lane == 0) {
-    col[j] = den;
-    col[j + 1] = 0.0;
-    c.sigma[j + 1] = beta > 0.0 ? 1.0 / beta : 0.0;
-    c.cs[j] = cs;
-    c.sn[j] = sn;
-    c.g[j + 1] = -sn * gj;
-    c.g[j] = cs * gj;
-    c.resid = resid;
-    c.jn = j + 1;
-    c.iters += 1;
-  }
-  return resid;
-}
-
-// Gram-Schmidt pass `pass` of step j: h_i = <v_i, w> from the partials, coef_i = sigma_i^2 h_i (the basis is kept
-// unnormalised, v_i / ||v_i|| = sigma_i v_i), hsum_i accumulates sigma_i h_i over the passes.  One block per entry.
-// early (one pass, value j + 1 of the partials = ||w||^2): the step's convergence is decided here, before the update
-// that forms v_{j+1} runs.  With one classical pass v_{j+1} = w - sum_i hsum_i q_i (q_i = sigma_i v_i orthonormal), so
-// ||v_{j+1}||^2 = ||w||^2 - sum_i hsum_i^2; where that difference keeps at least 1e-4 of ||w||^2 (the FP64 sums of
-// products then fix beta to about 1e-3 relative or better), the rotation it implies gives the residual estimate, and
-// an entry that meets its threshold (or the restart length) takes its last Givens step with this beta and leaves the
-// cycle: the update, transform and moments of a v_{j+1} no step would use are not run for it.  Otherwise the step
-// waits for the exact norm from the update, as without `early`.
-// The partials cover the vectors lo..j; an entry whose own window starts later (full[b] == 0 with skip > 0: the launch
-// covers the whole basis for entries that orthogonalise fully) takes the vectors lo + skip..j only.
+// ctl_coef_entry of every active entry, one block each.
 // NT threads per entry, one wave per value at a time: 256 while the step has at most 4 values (a windowed step), 1024
 // otherwise (a smaller block starts sooner when another stream's line kernels hold most of every CU; the sums are the
 // same either way)
@@ -145,43 +94,7 @@ template <int NT>
 __global__ void __launch_bounds__(NT) k_ctl_coef(Ctl* ctl, const double* part, int nval, TileSpan span, int* act, int fs,
                                                  int j, int pass, int early, int m, int lo, int skip, const int* full) {
   const int b = blockIdx.x;
-  if (!act[b]) return;
-  __shared__ double red[kMaxRestart + 2];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nblk = span.count(b);
-  for (int v = wave; v < nval; v += NT / 64) {
-    const double x = wave_reduce(part + ((size_t)b * nval + v) * span.stride, nblk);
-    if (lane == 0) red[v] = x;
-  }
-  __syncthreads();
-  if (wave != 0) return;
-  Ctl& c = ctl[b];
-  const int lob = lo + ((full && !full[b]) ? skip : 0);
-  const bool in = lane >= lob && lane <= j;  // outside the window (one pass): zero
-  const double sg = in ? c.sigma[lane] : 0.0, h = in ? red[lane - lo] : 0.0;
-  const double hsum = in ? (pass ? c.hsum[lane] : 0.0) + sg * h : 0.0;
-  if (lane <= j) {
-    c.coef[lane] = sg * sg * h;
-    c.hsum[lane] = hsum;
-  }
-  if (early) {
-    const double wn2 = red[j - lo + 1], b2 = wn2 - wsum(hsum * hsum);
-    if (b2 > 1e-4 * wn2) {
-      const double beta = sqrt(b2);
-      double mine;
-      const HessLane hl = hess_lane(c, j, hsum);
-      const double top = hess_rotate(hl, j, mine);
-      // the residual estimate with this beta, without touching the record
-      const double sub = c.sigma[j] * beta, den = hypot(top, sub);
-      const double resid = den > 0.0 ? fabs(sub / den * c.g[j]) : 0.0;
-      if (resid <= c.thresh || j + 1 >= m) {
-        givens_commit(c, j, beta, top, mine);
-        if (lane == 0) {
-          act[b] = 0;
-          if (resid > c.thresh) act[fs + b] = 1;  // stopped by the restart length
-        }
-      }
-    }
-  }
+  if (act[b]) ctl_coef_entry(b, ctl, part, nval, span, act, fs, j, pass, early, m, lo, skip, full);
 }
 
 // Column j of the Hessenberg matrix from hsum and beta = ||w_new|| (reduced from the update's partials), Givens
@@ -1043,6 +956,7 @@ void Pipeline::apply_x_first(const void* in, size_t in_bs, void* Tbuf, int B, co
     a.upd_sign = u->sign;
     a.upd_v32 = u->v32 ? 1 : 0;
     a.upd_zero = u->zero_in ? 1 : 0;
+    a.own = u->own;
   }
   launch_lines_any<T>(N, LineOp::RowsFwdMoments, a, s);
   const double dx = 2.0 * kPi * L / N;
@@ -1383,6 +1297,17 @@ static void launch_ctl_coef(int nval, int B, hipStream_t s, A... args) {
     hipLaunchKernelGGL(k_ctl_coef<1024>, dim3(B), dim3(1024), 0, s, args...);
 }
 
+// Whether the update's launch forms the Gram-Schmidt coefficients itself (every wave reduces the products' partials) or a
+// launch of its own does: while the update's blocks are about what the chip holds at once, the reduction costs each of them
+// about a microsecond and saves a launch of 3.5; beyond, rounds of blocks add up.  Own launch -> inside: N = 128, one problem
+// 718 -> 690 us; N = 512, 45 problems (not taken) 49 -> 59 us a launch.
+constexpr int kOwnCoefBlocks = 2048;
+static bool own_coef_ok(const Pipeline& P, int B, int nval, bool fp64) {
+  const int tiles = line_tiles(P.N, false, fp64);
+  const int used = P.box ? std::min(tiles, P.box_rows / (P.N / tiles)) : tiles;
+  return P.N >= 64 && P.N <= kOwnCoefMaxN && nval <= 4 && B <= used && used * B <= kOwnCoefBlocks;
+}
+
 // One Krylov cycle in lockstep; returns the number of iterations run (max over entries).
 // With cfg.use_graph each group of iterations between two convergence reads is captured once into a HIP graph (per
 // element size, method, space, group, passes and batch) and replayed on later cycles and calls; nothing in a
@@ -1441,12 +1366,25 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
         P.apply_x_rest<T>(vj, V_bs, vj1, V_bs, Qp, w.Q_bs, Tbuf, B, act, 1.0, 1.0, nullptr, 0, false, s, &dr, nullptr,
                           0u, nullptr, 0);
       }
-      {
-        TimerScope ts(kStageControl, 0.0, B, nullptr, s);
-        launch_ctl_coef(j - lo + 2, B, s, ctl, part, j - lo + 2, P.apply_tiles(sizeof(T) == 8), act, w.flag_stride, j, 0, 1, w.m, lo,
-                        lo_win - lo, full);
-      }
       UpdReq u;
+      const int nval = j - lo + 2;
+      const TileSpan span = P.apply_tiles(sizeof(T) == 8);
+      if (own_coef_ok(P, B, nval, sizeof(T) == 8)) {
+        u.own.part = part;
+        u.own.span = span;
+        u.own.nval = nval;
+        u.own.j = j;
+        u.own.m = w.m;
+        u.own.lo = lo;
+        u.own.skip = lo_win - lo;
+        u.own.fs = w.flag_stride;
+        u.own.full = full;
+        u.own.act = act;
+        u.own.ctl = ctl;
+      } else {
+        TimerScope ts(kStageControl, 0.0, B, nullptr, s);
+        launch_ctl_coef(nval, B, s, ctl, part, nval, span, act, w.flag_stride, j, 0, 1, w.m, lo, lo_win - lo, full);
+      }
       u.V = Vlo;
       u.V_bs = V_bs;
       u.nv = j - lo + 1;
