@@ -92,21 +92,14 @@ int line_tiles(int N, bool cols, bool fp64) {
 
 size_t tail_table_size(int N) { return (size_t)tail_pitch(N) * tail_pitch(N); }
 
-// u = |z|^2 / 4 at the quarter plane's points, x = L 2 pi |j - N/2| / N
-__global__ void __launch_bounds__(256) k_tail_table(int N, double L, int m11, c64* t64, c32* t32) {
-  const int np = tail_pitch(N), n = np * np;
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
-    const double h = L * (2.0 * kPi / N), x = h * (i % np), y = h * (i / np);
-    const double u = 0.25 * (x * x + y * y);
-    const c64 e = m11 ? tail_entry<11>(u) : tail_entry<kMaxM>(u);
-    t64[i] = e;
-    t32[i] = cvt<float>(e);
-  }
+__global__ void __launch_bounds__(256) k_tail_table(int N, double L, int M, c64* t64, c32* t32) {
+  const int n = tail_pitch(N) * tail_pitch(N);
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) tail_table_entry(i, N, L, M, t64, t32);
 }
 void launch_tail_table(int N, double L, int M, c64* t64, c32* t32, hipStream_t s) {
   const size_t n = tail_table_size(N);
   TimerScope ts(kStageControl, 0.0, 1, nullptr, s);
-  hipLaunchKernelGGL(k_tail_table, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, N, L, M == 11 ? 1 : 0, t64, t32);
+  hipLaunchKernelGGL(k_tail_table, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, N, L, M, t64, t32);
 }
 
 int box_row_align(int N) {

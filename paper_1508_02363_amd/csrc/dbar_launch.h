@@ -108,7 +108,7 @@ struct LineArgs {
   // box + b * box_bs (0: shared).  s, the basis, the result and the products live on it: nothing outside is read or
   // written, and the transform array's rows outside [row0, row1) count as zero.  Null: the whole grid.
   const int* box = nullptr;    int box_bs = 0;
-  const void* ttab = nullptr;  // RowsInvTailEpilogue up to N = kTailTabMaxN: the tail's table (k_tail_table), in the
+  const void* ttab = nullptr;  // the stages with the tail, up to N = kTailTabMaxN: its table (k_tail_table), in the
                                // transform's precision
   int box_rows = 0;            // rows the launch covers (at least every entry's row1 - row0)
   int box_full = 0;            // ColsFwdRegularInv, RowsInvTailEpilogue: the h that comes out is wanted on the whole grid
@@ -121,7 +121,7 @@ constexpr int kBoxCols = 8;
 // grid and the launches are bound by latency, not by the rows they cover.
 constexpr int kBoxMinN = 128;
 int box_row_align(int N);
-// Largest grid whose x-space tail reads its entry-independent part from a table: the tail launch gains 5 to 30 percent up
+// Largest grid whose tail reads its entry-independent part from a table: the tail launch gains 5 to 30 percent up
 // to here and is bound by memory beyond, where a table of N^2 / 4 entries (17 and 67 MB in FP64) no longer stays in L2.
 // The table of a grid: tail_table_size(N) entries, FP64 and rounded to FP32.
 constexpr int kTailTabMaxN = 1024;

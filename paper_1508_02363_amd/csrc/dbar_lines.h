@@ -244,6 +244,15 @@ DBAR_D c64 tail_entry(double u) {
 }
 // The table holds one quarter of the plane: |row - N/2|, |col - N/2| <= N/2 (the points of the grid mirror in both axes).
 constexpr int tail_pitch(int N) { return N / 2 + 1; }
+// entry i of the table (t32: rounded; either may be null), x = L 2 pi |j - N/2| / N
+DBAR_D void tail_table_entry(int i, int N, double L, int M, c64* t64, c32* t32) {
+  const int np = tail_pitch(N);
+  const double h = L * (2.0 * kPi / N), x = h * (i % np), y = h * (i / np);
+  const double u = 0.25 * (x * x + y * y);
+  const c64 e = M == 11 ? tail_entry<11>(u) : tail_entry<kMaxM>(u);
+  if (t64) t64[i] = e;
+  if (t32) t32[i] = cvt<float>(e);
+}
 template <int N>
 DBAR_D int tail_index(int row, int col) {
   const int r = row - N / 2, c = col - N / 2;
@@ -866,6 +875,8 @@ struct OpColsInvTail : OpBase<T, N, E> {
   static constexpr bool TWO = !TAILONLY;
   static constexpr bool ROLLED = true;
   using Acc = NoAcc;
+  // (h alone, once per call, keeps the series: its launch gains nothing from the table)
+  static constexpr bool TABLE = !TAILONLY && N <= kTailTabMaxN;
   DBAR_D cx<T> load(int b, int col, int pos) const { return this->inp(b)[(size_t)pos * N + col]; }
   DBAR_D cx<T> phase(int b, int col, int pos) const {
     // tabulated in FP64 (arguments up to hundreds of radians; the FP32 operator reads their FP32 roundings); the
@@ -889,7 +900,13 @@ struct OpColsInvTail : OpBase<T, N, E> {
   // h = F^{-1}R + sum d_n omega_n; with the shifted regularisation the closed-form part is e^{i a.x} sum d_n omega_n
   DBAR_D cx<T> h_at(int b, int col, int pos, cx<T> v, const Pre& p) const {
     const T x = xgrid_t<T, N>(col, this->a.L), y = xgrid_t<T, N>(pos, this->a.L);
-    const cx<T> t = this->a.M == 11 ? tail_sum<T, 11>(x, y, p.d) : tail_sum<T, kMaxM>(x, y, p.d);
+    cx<T> t;
+    if constexpr (TABLE) {
+      const cx<T> e = static_cast<const cx<T>*>(this->a.ttab)[tail_index<N>(pos, col)];
+      t = this->a.M == 11 ? tail_tab<T, 11>(x, y, p.d, e) : tail_tab<T, kMaxM>(x, y, p.d, e);
+    } else {
+      t = this->a.M == 11 ? tail_sum<T, 11>(x, y, p.d) : tail_sum<T, kMaxM>(x, y, p.d);
+    }
     return this->a.shv ? v + conj(phase(b, col, pos)) * t : v + t;
   }
   template <class A>
@@ -1013,7 +1030,7 @@ struct OpRowsInvTailEpi : OpColsInvTail<T, N, false, Ept<T, N>::TAIL_ROWS> {
   // waves per SIMD at eight)
   static constexpr int GROUP_W = 4;
   static constexpr int GROUP = G::RMAX < GROUP_W ? G::RMAX : GROUP_W;
-  static constexpr bool TABLE = N <= kTailTabMaxN;
+  static constexpr bool TABLE = N <= kTailTabMaxN;  // (read with the group)
   struct GroupIn {
     cx<T> q[GROUP], s[GROUP], y[GROUP], ex[GROUP], tab[GROUP];
   };

@@ -5,8 +5,8 @@
 // The scratch array holds, for grids up to N = kNoAllocMaxN:
 //   * the transform scratch of the operator (FP64: one N x N complex128 array; FP32: the transform array and the
 //     FP32 roundings of Q, S and the result, N x N complex64 each -- 32 N^2 bytes either way);
-//   * the per-k phase tables e^{-2i k2 x_j}, e^{-2i k1 y_j} (FP64 and FP32), the Taylor data (d_n, c_n, R(0))
-//     and the per-tile partial sums of the moment reduction.
+//   * the per-k phase tables e^{-2i k2 x_j}, e^{-2i k1 y_j} (FP64 and FP32), the Taylor data (d_n, c_n, R(0)),
+//     the per-tile partial sums of the moment reduction and the grid's tail table.
 // Nothing in it has to start at zero: every call writes each part it reads before reading it.  All calls on one GPU
 // share that GPU's copy (it keeps the last call's contents), so calls that overlap on one GPU race: serialise them on
 // one stream.  The twiddle tables exp(-2 pi i j / N) of every power of two 8 <= N <= kNoAllocMaxN sit in a second
@@ -38,7 +38,10 @@ constexpr size_t kOffMom =                                           // coefG, d
 constexpr size_t kOffPartMom = align256(kOffMom + (size_t)kNMom * (2 * sizeof(c64) + sizeof(c32)));
 // moment partials: 2 kNMom values per tile, at most N tiles per entry (one line per tile)
 constexpr size_t kOffPartVec = align256(kOffPartMom + 2 * (size_t)kNMom * kNoAllocMaxN * sizeof(double));
-constexpr size_t kScratchBytes = align256(kOffPartVec + (size_t)kNoAllocMaxN * sizeof(double));
+constexpr size_t kOffTail = align256(kOffPartVec + (size_t)kNoAllocMaxN * sizeof(double));  // tail table (FP64 or FP32)
+constexpr size_t kTailMax = (size_t)(kNoAllocMaxN / 2 + 1) * (kNoAllocMaxN / 2 + 1);
+static_assert(kNoAllocMaxN <= kTailTabMaxN, "every grid here has a tail table");
+constexpr size_t kScratchBytes = align256(kOffTail + kTailMax * sizeof(c64));
 constexpr int kMaxDevices = 64;
 }  // namespace
 
@@ -175,6 +178,9 @@ int dbar_apply_noalloc(const dbar_grid* grid, const void* Q_dev, const double* k
   P.part_vec = reinterpret_cast<double*>(base + kOffPartVec);
   P.xspace = false;  // the operator as written on S (Section 4 algorithm, step 4)
   P.own_k = k;
+  P.own_tail = true;
+  P.tail64 = base + kOffTail;
+  P.tail32 = base + kOffTail;
   if (precision == DBAR_FP64) {
     void* T = base + kOffBig;
     P.apply<double>(S_dev, n, AS_dev, n, Q_dev, 0, T, 1, nullptr, 1.0, 1.0, nullptr, 0, false, s);

@@ -264,7 +264,8 @@ struct Pipeline {
   size_t n = 0;
   const void* tw64 = nullptr;  // exp(-2 pi i j / N), j < N, in FP64 and rounded to FP32
   const void* tw32 = nullptr;
-  const void* tail64 = nullptr;  // x-space tail tables (null beyond kTailTabMaxN)
+  bool own_tail = false;         // with own_k: the tail table too is still to be made (into tail64 or tail32)
+  const void* tail64 = nullptr;  // tail tables (null beyond kTailTabMaxN)
   const void* tail32 = nullptr;
   const double* own_k = nullptr;  // single xi-space application: k (host), whose tables the moments' launch makes
   const c64* ex = nullptr;

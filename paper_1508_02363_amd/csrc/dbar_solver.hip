@@ -24,6 +24,7 @@
 #include "dbar.h"
 #include "dbar_ctl.h"
 #include "dbar_launch.h"
+#include "dbar_lines.h"
 #include "dbar_solver.h"
 
 namespace dbar {
@@ -377,17 +378,19 @@ __global__ void k_phase_tables(const c64* kv, int N, double L, c64* ex, c64* ey,
   for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < N; j += gridDim.x * blockDim.x)
     phase_point(k, N, L, j, ex + o, ey + o, ex32 + o, ey32 + o);
 }
-// The moments of one entry and its phase tables (blocks from kMomBlocks on) in one launch: nothing before it reads the
-// tables of a single application, and k comes as an argument.  In place of two launches of their own: one
-// application at N = 64 37.7 -> 34.2 us, at N = 1024 82.9 -> 78.7 us.
+// The moments of one entry and, in the blocks from kMomBlocks on, its phase tables and (t64 or t32 not null) the grid's tail
+// table in one launch: nothing before it reads the tables of a single application, and k comes as an argument.  In place of two launches of their own: one
+// application at N = 64 37.7 -> 34.2 us, at N = 1024 82.9 -> 78.7 us; the column tail with the table, made here for every call:
+// 33.8 -> 30.2 and 74.5 -> 69.8 us.
 __global__ void __launch_bounds__(kMomThreads) k_moments_phase(const double* part, TileSpan span, double wscale, int M,
                                                                c64* coefG, c64* dmom, c32* dmom32, c64 k, int N, double L,
-                                                               c64* ex, c64* ey, c32* ex32, c32* ey32) {
+                                                               c64* ex, c64* ey, c32* ex32, c32* ey32, c64* t64, c32* t32) {
   if (blockIdx.x < kMomBlocks) {
     moments_pair(0, blockIdx.x, part, span, wscale, M, coefG, dmom, dmom32);
   } else {
     const int j = (blockIdx.x - kMomBlocks) * kMomThreads + threadIdx.x;
     if (j < N) phase_point(k, N, L, j, ex, ey, ex32, ey32);
+    if ((t64 || t32) && j < tail_pitch(N) * tail_pitch(N)) tail_table_entry(j, N, L, M, t64, t32);
   }
 }
 
@@ -861,9 +864,13 @@ void Pipeline::moments(const void* in, size_t in_bs, void* Tbuf, int B, const in
   TileSpan span;
   span.stride = moment_tiles(N, sizeof(T) == 8);
   if (own_k) {  // one entry, and its tables are still to be made
-    hipLaunchKernelGGL(k_moments_phase, dim3(kMomBlocks + (N + kMomThreads - 1) / kMomThreads), dim3(kMomThreads), 0, s,
+    const bool table = own_tail && N <= kTailTabMaxN;  // (of the precision in use)
+    c64* t64 = table && sizeof(T) == 8 ? static_cast<c64*>(const_cast<void*>(tail64)) : nullptr;
+    c32* t32 = table && sizeof(T) == 4 ? static_cast<c32*>(const_cast<void*>(tail32)) : nullptr;
+    const int points = table ? std::max(N, (int)tail_table_size(N)) : N;
+    hipLaunchKernelGGL(k_moments_phase, dim3(kMomBlocks + (points + kMomThreads - 1) / kMomThreads), dim3(kMomThreads), 0, s,
                        part_mom, span, dx * dx / (2.0 * kPi), M, coefG, dmom, dmom32, c64{own_k[0], own_k[1]}, N, L,
-                       const_cast<c64*>(ex), const_cast<c64*>(ey), const_cast<c32*>(ex32), const_cast<c32*>(ey32));
+                       const_cast<c64*>(ex), const_cast<c64*>(ey), const_cast<c32*>(ex32), const_cast<c32*>(ey32), t64, t32);
     return;
   }
   hipLaunchKernelGGL(k_moments, dim3(kMomBlocks, B), dim3(kMomThreads), 0, s, part_mom, span, act, dx * dx / (2.0 * kPi), M, coefG,
@@ -888,6 +895,7 @@ void Pipeline::apply_impl(const void* in, size_t in_bs, void* out, size_t out_bs
   a.in_bs = n;
   a.Q = Qp;
   a.Q_bs = Q_bs;
+  a.ttab = sizeof(T) == 8 ? tail64 : tail32;
   launch_lines_any<T>(N, LineOp::ColsInvTailFwd, a, s);
   a.out = out;
   a.out_bs = out_bs;
@@ -1924,7 +1932,7 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
     ln[l].w = &w;
     const hipStream_t s = ln[l].s;
     if ((rc = w.setup(N, Bl, o.restart, o.precision, true))) return rc;
-    if (cfg.xspace && (rc = w.setup_tail(grid->L, grid->M, s))) return rc;
+    if ((rc = w.setup_tail(grid->L, grid->M, s))) return rc;
     if ((rc = make_pipeline(grid, w, &ln[l].P))) return rc;
     ln[l].P.xspace = cfg.xspace != 0;
     if (q_on_device) {
@@ -2293,7 +2301,8 @@ int dbar_get_tile(int32_t n, int32_t precision, int32_t* variant, int32_t* colum
   return DBAR_OK;
 }
 
-static int single_prep(const dbar_grid* grid, int precision, Work*& w, Pipeline& P) {
+// tail: the call needs the tail's table
+static int single_prep(const dbar_grid* grid, int precision, bool tail, Work*& w, Pipeline& P) {
   int rc = validate_grid(grid);
   if (rc) return rc;
   if (precision != DBAR_FP64 && precision != DBAR_FP32) return fail(DBAR_EINVAL, "precision must be FP64 or FP32");
@@ -2301,6 +2310,7 @@ static int single_prep(const dbar_grid* grid, int precision, Work*& w, Pipeline&
   w = &g_work;
   if ((rc = w->setup(grid->n, 1, 1, precision == DBAR_FP32 ? DBAR_MIXED : DBAR_FP64, true))) return rc;
   w->B = 1;
+  if (tail && (rc = w->setup_tail(grid->L, grid->M, nullptr))) return rc;
   return make_pipeline(grid, *w, &P);
 }
 
@@ -2310,7 +2320,7 @@ int dbar_apply(const dbar_grid* grid, const double* Q, const double* k, const do
   std::lock_guard<std::mutex> lock(g_mutex);
   Work* w;
   Pipeline P;
-  int rc = single_prep(grid, precision, w, P);
+  int rc = single_prep(grid, precision, true, w, P);
   if (rc) return rc;
   const int N = grid->n;
   const size_t n = (size_t)N * N;
@@ -2340,7 +2350,7 @@ int dbar_transform(const dbar_grid* grid, int32_t inverse, const double* in, dou
   std::lock_guard<std::mutex> lock(g_mutex);
   Work* w;
   Pipeline P;
-  int rc = single_prep(grid, precision, w, P);
+  int rc = single_prep(grid, precision, false, w, P);
   if (rc) return rc;
   const size_t n = (size_t)grid->n * grid->n;
   if ((rc = g_stage[0].upload(w->x.p, in, n * sizeof(c64), nullptr, true, "NaN or Inf in the input"))) return rc;
@@ -2360,7 +2370,7 @@ int dbar_dbar_inverse(const dbar_grid* grid, const double* S_in, double* h_out, 
   std::lock_guard<std::mutex> lock(g_mutex);
   Work* w;
   Pipeline P;
-  int rc = single_prep(grid, precision, w, P);
+  int rc = single_prep(grid, precision, false, w, P);
   if (rc) return rc;
   const size_t n = (size_t)grid->n * grid->n;
   if ((rc = g_stage[0].upload(w->x.p, S_in, n * sizeof(c64), nullptr, true, "NaN or Inf in the input"))) return rc;

@@ -34,3 +34,20 @@ def test_table_solve_matches_the_iteration_on_S(N, L, M, prec):
     for j in range(len(ks)):
         assert np.max(np.abs(S[j] - S2[j])) <= 1e-10 * np.max(np.abs(S2[j]))
         assert np.max(np.abs(m[j] - m2[j])) <= 1e-10 * np.max(np.abs(m2[j]))
+
+
+@pytest.mark.parametrize("N,L,M", [(8, 1.0, 15), (64, 1.0, 3), (64, 4.0, 11), (512, 12.0, 15)])
+def test_single_application_with_its_own_table(N, L, M):
+    """The allocation-free application makes the table in every call, whatever grid the last one had: against the oracle to
+    1e-12 of the largest value, as for every operator test in FP64."""
+    g = O.make_grid(N, L)
+    Q = (0.5 - 0.3j) * np.exp(-np.abs(g.z - 0.3) ** 2)
+    S = O.Fd(g, np.exp(-np.abs(g.z) ** 2 / 2) * (1 + 0.3j * g.z.real))
+    ref = O.apply_A(g, Q, 0.4 + 0.2j, S, M)
+    Qd, Sd = torch.from_numpy(Q).cuda(), torch.from_numpy(np.ascontiguousarray(S)).cuda()
+    out = torch.empty_like(Sd)
+    for prec in (D.DBAR_FP64, D.DBAR_FP32, D.DBAR_FP64):  # (the two precisions' tables share their place)
+        D.apply_noalloc(Qd, 0.4 + 0.2j, Sd, out, L, M=M, precision=prec)
+        torch.cuda.synchronize()
+        if prec == D.DBAR_FP64:
+            assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(ref))
