@@ -1254,7 +1254,8 @@ __global__ void __launch_bounds__((LINES * Op::G::TPL), (MinWaves<LINES * Op::G:
         // nothing uses what they write (the flag is off for every later launch of the cycle).
         if (b >= op.a.B) {
           const CoefReq& o = op.a.own;
-          if (NT >= 64 && blockIdx.x < op.a.B && o.act[blockIdx.x])
+          static_assert(NT >= 64, "whole waves");
+          if (blockIdx.x < op.a.B && o.act[blockIdx.x])
             ctl_coef_entry(blockIdx.x, o.ctl, o.part, o.nval, o.span, o.act, o.fs, o.j, 0, 1, o.m, o.lo, o.skip, o.full);
           return;
         }

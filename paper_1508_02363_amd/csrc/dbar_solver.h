@@ -193,7 +193,7 @@ struct Work {
   void* m_dst() { return outm ? outm : mx.p; }
   PinnedInts host_act, host_live;
   PinnedInts host_ticket;
-  int ticket_no = 0;
+  unsigned ticket_no = 0;  // the last one posted
   // the ranges to pinned memory, after everything on s; returns when they are there (and with them what earlier kernels
   // on s wrote to pinned memory)
   int report(std::initializer_list<WordRange> ranges, hipStream_t s);

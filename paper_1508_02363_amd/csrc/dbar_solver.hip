@@ -346,7 +346,7 @@ void launch_words(std::initializer_list<WordRange> ranges, hipStream_t s) {
 int Work::report(std::initializer_list<WordRange> ranges, hipStream_t s) {
   Words a = words_of(ranges);
   a.ticket = host_ticket.data();
-  a.value = ++ticket_no;
+  a.value = (int)++ticket_no;
   hipLaunchKernelGGL(k_words, dim3(1), dim3(256), 0, s, a);
   // The ticket for as long as short work takes, then the runtime's wait (which also shows a stream that failed).
   using Clock = std::chrono::steady_clock;
@@ -356,7 +356,9 @@ int Work::report(std::initializer_list<WordRange> ranges, hipStream_t s) {
     if ((i & 63) == 0 && Clock::now() > until) break;
     __builtin_ia32_pause();
   }
-  return hipStreamSynchronize(s) == hipSuccess ? DBAR_OK : fail(DBAR_EDEVICE, "stream synchronize failed");
+  if (hipStreamSynchronize(s) != hipSuccess) return fail(DBAR_EDEVICE, "stream synchronize failed");
+  if (__atomic_load_n(a.ticket, __ATOMIC_ACQUIRE) != a.value) return fail(DBAR_EDEVICE, "a launch failed");
+  return DBAR_OK;
 }
 
 // e^{conj(kz) - kz} = e^{-2i k2 x} e^{-2i k1 y} (eq:039) as two FP64 tables per entry, x_j = L(-pi + 2 pi j / N)
@@ -752,7 +754,10 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   if ((rc = live.ensure((size_t)B * sizeof(int)))) return rc;
   if ((rc = host_act.ensure(3 * B + 1))) return rc;
   if ((rc = host_live.ensure(B))) return rc;
-  if ((rc = host_ticket.ensure(1))) return rc;
+  if (!host_ticket.p) {  // (pinned memory comes with whatever its last owner left in it: not a ticket to come)
+    if ((rc = host_ticket.ensure(1))) return rc;
+    host_ticket[0] = (int)ticket_no;
+  }
   const void* after[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
                          nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
                           dmom32.p, unit32.p, tail64.p, tail32.p};
