@@ -11,6 +11,16 @@ static __constant__ double kInvFactC[kMaxM + 2] = {
     2.7557319223985888e-7, 2.5052108385441720e-8, 2.0876756987868100e-9, 1.6059043836821613e-10,
     1.1470745597729725e-11, 7.6471637318198164e-13, 4.7794773323873853e-14};
 
+// *flag as one thread reads it, in every thread of the block: for a flag that another block of the launch may clear
+// meanwhile, where waves that read it for themselves could part, some past the block's barriers and some not.  A barrier
+// behind a load the launch begins with anyway.
+DBAR_D int block_flag(const int* flag) {
+  __shared__ int f;
+  if (threadIdx.x == 0) f = *flag;
+  __syncthreads();
+  return f;
+}
+
 // lane l's x in every lane (l uniform: a register read, not a trip through LDS as __shfl is)
 DBAR_D double bcast(double x, int l) {
   const long long v = __builtin_bit_cast(long long, x);

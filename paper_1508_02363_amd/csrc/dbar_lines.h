@@ -1250,8 +1250,9 @@ __global__ void __launch_bounds__((LINES * Op::G::TPL), (MinWaves<LINES * Op::G:
       b = blockIdx.y;
       if constexpr (Op::OWN_COEF) {
         // The blocks beyond the entries take the step's coefficients to its record and decide on its end, beside the
-        // update.  An entry that ends there may still be updated and transformed by blocks that read its flag before:
-        // nothing uses what they write (the flag is off for every later launch of the cycle).
+        // update.  An entry that ends there may still be updated and transformed by blocks that read its flag before
+        // (a whole block at a time: block_flag): nothing uses what they write (the flag is off for every later launch of
+        // the cycle).
         if (b >= op.a.B) {
           const CoefReq& o = op.a.own;
           static_assert(NT >= 64, "whole waves");
@@ -1261,7 +1262,11 @@ __global__ void __launch_bounds__((LINES * Op::G::TPL), (MinWaves<LINES * Op::G:
         }
       }
     }
-    if (!op.active(b)) return;
+    if constexpr (Op::OWN_COEF) {
+      if (!block_flag(op.a.act + b)) return;
+    } else {
+      if (!op.active(b)) return;
+    }
     int t0 = 0, cnt = NTILES;
     if (N >= kBoxMinN && op.a.box && !op.a.box_full) {
       const Box<N> x = entry_box<N>(op.a, b);

@@ -124,12 +124,12 @@ __global__ void __launch_bounds__(64) k_ctl_givens(Ctl* ctl, const double* pnorm
 
 // The moments of the next basis vector (whose update and transform just ran) and the Givens step of the Krylov step
 // that produced it, in one launch (block 0 of an entry: the Givens step): the moments are used only if the entry stays
-// active, so it does not matter on which side of the step's write of act[b] the other blocks read it.
+// active, so it does not matter on which side of the step's write of act[b] another block reads it (once for the block).
 __global__ void __launch_bounds__(kMomThreads) k_moments_givens(const double* part, TileSpan span, double wscale,
                                                                 int M, c64* coefG, c64* dmom, c32* dmom32, Ctl* ctl,
                                                                 const double* pnorm, int* act, int fs, int j, int m) {
   const int b = blockIdx.y;
-  if (!act[b]) return;
+  if (!block_flag(act + b)) return;
   if (blockIdx.x == 0) {
     if (threadIdx.x < 64) givens_entry(b, fs, ctl, pnorm, span.count(b), span.stride, act, j, m);
   } else {
