@@ -422,7 +422,7 @@ static void worker(dbar_session* s, SClass* cp) {
     if (c.P.box) c.P.set_box(c.P.box, 4, w.host_box.data(), used, c.h_live.data());
     // As in a batched solve, the first cycle of a mixed solve cannot be its last when tol is far below the inner
     // tolerance: such a request never finishes there (whatever else is in flight), and when all of them are in their
-    // first cycle its evaluation leaves S and m unwritten.
+    // first cycle its evaluation leaves S and m unwritten -- unless the cycle took no step, which ends them all.
     bool any_first = false, outputs = false;
     for (int b = 0; b < used; ++b) {
       const bool first = mixed && c.h_live[b] && c.slots[b]->iters == 0 && c.h_tol[b] < 1e-3 * cfg.inner_tol;
@@ -442,6 +442,7 @@ static void worker(dbar_session* s, SClass* cp) {
     TileSpan span;
     if (mixed) {
       ran = krylov_cycle<float>(c.P, w, cfg, c.restart, c.stream);
+      outputs |= ran == 0;
       span = end_cycle<float>(c.P, w, ran, w.r64.p, c.stream, 0, true, outputs);
     } else {
       ran = krylov_cycle<double>(c.P, w, cfg, c.restart, c.stream);

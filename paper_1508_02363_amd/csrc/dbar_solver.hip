@@ -1698,11 +1698,14 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, EntryRes
     // inner_tol of that, which FP32 arithmetic cannot better by many orders: with tol far below inner_tol its residual
     // evaluation is not the last one, and it leaves S and m unwritten (two N x N FP64 arrays per entry).  So that the
     // outputs always come from the last evaluation, an entry that would meet tol there anyway runs one more cycle
-    // (whose evaluation writes them) instead of finishing.
-    const bool outputs = !(mixed && P.xspace && total == 0 && cfg.tol < 1e-3 * cfg.inner_tol);
+    // (whose evaluation writes them) instead of finishing.  Where the cycle took no step (a residual that is not finite)
+    // or the step limit ends the solve here, the evaluation is the last one after all.
+    const bool early = mixed && P.xspace && total == 0 && cfg.tol < 1e-3 * cfg.inner_tol;
+    bool outputs = true;
     // the condition estimate is taken from the first cycle (from x = 0: the longest, every entry in it)
     if (mixed) {
       ran = krylov_cycle<float>(P, w, cfg, cfg.max_iter - total, s);
+      outputs = !early || ran == 0 || ran >= cfg.max_iter;
       span = end_cycle<float>(P, w, ran, w.r64.p, s, cfg.method, total == 0, outputs);
     } else {
       ran = krylov_cycle<double>(P, w, cfg, cfg.max_iter - total, s);
