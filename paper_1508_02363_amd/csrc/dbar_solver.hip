@@ -292,7 +292,8 @@ __global__ void __launch_bounds__(256) k_ctl_check(Ctl* ctl, const double* part,
   const double r2 = red[0] + red[1] + red[2] + red[3];
   nred[b] = r2;
   Ctl& c = ctl[b];
-  // (a sum of squares: no clamp, so that a residual that is not finite stays NaN and never counts as converged)
+  // (a sum of squares: no clamp, so that a residual that is not a number stays one; nor does an infinite one count as
+  // converged, whatever |b| is)
   const double rn = sqrt(r2);
   if (first) {
     c.bnorm = rn;
@@ -307,7 +308,7 @@ __global__ void __launch_bounds__(256) k_ctl_check(Ctl* ctl, const double* part,
   c.rnorm = rn;
   c.cycles += 1;
   const double t = tolv ? tolv[b] : tol;
-  const int lv = rn <= t * c.bnorm ? 0 : first && !mask ? 1 : live[b];  // (a solve's first check: every entry starts live)
+  const int lv = rn <= t * c.bnorm && isfinite(rn) ? 0 : first && !mask ? 1 : live[b];  // (a solve's first check: every entry starts live)
   live[b] = lv;
   if (report) report[b] = lv;
 }

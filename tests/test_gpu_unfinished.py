@@ -59,3 +59,12 @@ def test_a_served_request_whose_energy_overflows_leaves_zero():
         for q, zero in ((Q, False), (1e200 * Q, True)):
             S, m, info, _ = s.wait(s.submit(q, 0.5, L, tol=1e-12))
             assert np.any(S != 0) != zero and np.any(m != 0) != zero, info
+
+
+@pytest.mark.parametrize("prec", [D.DBAR_FP64, D.DBAR_MIXED])
+@pytest.mark.parametrize("N", [64, 128])
+def test_an_infinite_residual_is_not_converged(N, prec):
+    """||b|| overflows, so that ||r|| <= tol ||b|| holds as inf <= inf: the status says that the solve did not converge."""
+    Q = W.potential_gaussian(N, L, 0.8 + 0.6j)
+    _, _, info = D.solve(1e200 * Q, [0.5, 0.0], L, precision=prec, max_iter=40)
+    assert all(i.status == D.DBAR_ENOCONV and i.iters == 0 for i in info), info
