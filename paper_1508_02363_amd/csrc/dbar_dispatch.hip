@@ -96,10 +96,15 @@ __global__ void __launch_bounds__(256) k_tail_table(int N, double L, int M, c64*
   const int n = tail_pitch(N) * tail_pitch(N);
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) tail_table_entry(i, N, L, M, t64, t32);
 }
-void launch_tail_table(int N, double L, int M, c64* t64, c32* t32, hipStream_t s) {
+bool launch_tail_table(int N, double L, int M, c64* t64, c32* t32, hipStream_t s) {
   const size_t n = tail_table_size(N);
   TimerScope ts(kStageControl, 0.0, 1, nullptr, s);
-  hipLaunchKernelGGL(k_tail_table, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, N, L, M, t64, t32);
+  void* args[] = {&N, &L, &M, &t64, &t32};
+  if (hipLaunchKernel(reinterpret_cast<const void*>(k_tail_table), dim3((unsigned)((n + 255) / 256)), dim3(256), args, 0,
+                      s) == hipSuccess)
+    return true;
+  (void)hipGetLastError();
+  return false;
 }
 
 int box_row_align(int N) {

@@ -123,10 +123,10 @@ constexpr int kBoxMinN = 128;
 int box_row_align(int N);
 // Largest grid whose tail reads its entry-independent part from a table: the tail launch gains 5 to 30 percent up
 // to here and is bound by memory beyond, where a table of N^2 / 4 entries (17 and 67 MB in FP64) no longer stays in L2.
-// The table of a grid: tail_table_size(N) entries, FP64 and rounded to FP32.
+// The table of a grid: tail_table_size(N) entries, FP64 and rounded to FP32 (false: the launch failed).
 constexpr int kTailTabMaxN = 1024;
 size_t tail_table_size(int N);
-void launch_tail_table(int N, double L, int M, c64* t64, c32* t32, hipStream_t s);
+bool launch_tail_table(int N, double L, int M, c64* t64, c32* t32, hipStream_t s);
 
 // Number of blocks (tiles) per batch entry used by a line stage with the current tile choice; partial buffers are
 // sized for the default (narrowest, most tiles) choice.

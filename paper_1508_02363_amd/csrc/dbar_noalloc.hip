@@ -181,6 +181,7 @@ int dbar_apply_noalloc(const dbar_grid* grid, const void* Q_dev, const double* k
   P.own_tail = true;
   P.tail64 = base + kOffTail;
   P.tail32 = base + kOffTail;
+  const LaunchWatch watch;
   if (precision == DBAR_FP64) {
     void* T = base + kOffBig;
     P.apply<double>(S_dev, n, AS_dev, n, Q_dev, 0, T, 1, nullptr, 1.0, 1.0, nullptr, 0, false, s);
@@ -194,9 +195,7 @@ int dbar_apply_noalloc(const dbar_grid* grid, const void* Q_dev, const double* k
     P.apply<float>(S32, n, out32, n, Q32, 0, T32, 1, nullptr, 1.0, 1.0, nullptr, 0, false, s);
     launch_convert<double, float>(out32, 0, AS_dev, 0, n, 1, nullptr, 1.0, s);
   }
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail(DBAR_EDEVICE, std::string("launch failed: ") + hipGetErrorString(e));
-  return DBAR_OK;
+  return watch.check();
 }
 
 }  // extern "C"

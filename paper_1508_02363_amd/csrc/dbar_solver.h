@@ -24,6 +24,20 @@ constexpr int kDefaultOrthWindow = 2;
 int fail(int code, const std::string& msg);
 extern thread_local std::string g_last_error;  // the calling thread's last message (dbar_last_error)
 
+// A launch of this thread that failed since the object was made, where that can be told: not while an earlier call of the
+// caller's own has left an error behind (it stays until it is read).
+class LaunchWatch {
+ public:
+  LaunchWatch() : before_(hipPeekAtLastError()) {}
+  int check() const {
+    if (before_ != hipSuccess || hipPeekAtLastError() == hipSuccess) return DBAR_OK;
+    return fail(DBAR_EDEVICE, std::string("launch failed: ") + hipGetErrorString(hipGetLastError()));
+  }
+
+ private:
+  hipError_t before_;
+};
+
 // Owning device allocation that only grows.
 struct DevBuf {
   void* p = nullptr;

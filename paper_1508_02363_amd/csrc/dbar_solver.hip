@@ -524,10 +524,16 @@ bool copy_finite(double* dst, const double* src, size_t cnt) { return scan<true>
 __global__ void __launch_bounds__(256) k_stage_copy(uint4* __restrict__ dst, const uint4* __restrict__ src, unsigned n) {
   for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) dst[i] = src[i];
 }
-static void stage_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {  // whole 16-byte elements
-  const unsigned n = (unsigned)(bytes / 16);
-  hipLaunchKernelGGL(k_stage_copy, dim3(std::min(256u, (n + 255) / 256)), dim3(256), 0, s, static_cast<uint4*>(dst),
-                     static_cast<const uint4*>(src), n);
+// Whole 16-byte elements.  False if the launch itself failed: hipGetLastError would also return an error that an earlier
+// call of the caller's own left.
+static bool stage_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  unsigned n = (unsigned)(bytes / 16);
+  void* args[] = {&dst, &src, &n};
+  if (hipLaunchKernel(reinterpret_cast<const void*>(k_stage_copy), dim3(std::min(256u, (n + 255) / 256)), dim3(256), args, 0,
+                      s) == hipSuccess)
+    return true;
+  (void)hipGetLastError();
+  return false;
 }
 
 int HostStage::ensure() {
@@ -550,7 +556,7 @@ int HostStage::ensure() {
   return DBAR_OK;
 }
 int HostStage::mark(int i, hipStream_t s) {
-  if (hipGetLastError() != hipSuccess || hipEventRecord(ev_[i], s) != hipSuccess)
+  if (hipEventRecord(ev_[i], s) != hipSuccess)
     return fail(DBAR_EDEVICE, "a host transfer could not be queued");
   owner_[i] = i;
   return DBAR_OK;
@@ -585,7 +591,10 @@ int HostStage::upload(void* dst, const void* src, size_t bytes, hipStream_t s, b
     const bool ok = !check || copy_finite(reinterpret_cast<double*>(slot), reinterpret_cast<const double*>(from),
                                           n / sizeof(double));
     if (!check) std::memcpy(slot, from, n);
-    if (ok) stage_copy(static_cast<char*>(dst) + off, slot, n, s);
+    if (ok && !stage_copy(static_cast<char*>(dst) + off, slot, n, s)) {
+      (void)hipStreamSynchronize(s);  // (the slots of the chunks before are still being read)
+      return fail(DBAR_EDEVICE, "a host transfer could not be queued");
+    }
     // an event where a later chunk takes the slot; the last one stands for every slot still in flight
     const bool last = c + 1 == count || !ok;
     if (last || c + kSlots < count)
@@ -605,7 +614,8 @@ int HostStage::download(void* dst, const void* src, size_t bytes, hipStream_t s)
     if (c < count) {
       const int i = (int)(c % kSlots);
       const size_t off = c * chunk;
-      stage_copy(buf_ + i * kChunk, static_cast<const char*>(src) + off, std::min(chunk, bytes - off), s);
+      if (!stage_copy(buf_ + i * kChunk, static_cast<const char*>(src) + off, std::min(chunk, bytes - off), s))
+        return fail(DBAR_EDEVICE, "a host transfer could not be queued");
       if (int rc = mark(i, s)) return rc;
     }
     if (c + 1 >= (size_t)kSlots) {  // kSlots - 1 chunks behind: the copy that is due out
@@ -775,8 +785,8 @@ int Work::setup_tail(double L, int M, hipStream_t s) {
   drop_graphs();  // captured launches read the table
   if ((rc = tail64.ensure(tail_table_size(N) * sizeof(c64)))) return rc;
   if ((rc = tail32.ensure(tail_table_size(N) * sizeof(c32)))) return rc;
-  launch_tail_table(N, L, M, static_cast<c64*>(tail64.p), static_cast<c32*>(tail32.p), s);
-  if (hipGetLastError() != hipSuccess) return fail(DBAR_EDEVICE, "the tail table could not be computed");
+  if (!launch_tail_table(N, L, M, static_cast<c64*>(tail64.p), static_cast<c32*>(tail32.p), s))
+    return fail(DBAR_EDEVICE, "the tail table could not be computed");
   // (the workspace may be used on another stream next: the table is complete when this returns)
   if (hipStreamSynchronize(s) != hipSuccess) return fail(DBAR_EDEVICE, "stream synchronize failed");
   tail_N = N;
@@ -2336,6 +2346,7 @@ int dbar_apply(const dbar_grid* grid, const double* Q, const double* k, const do
   if (!all_finite(k, 2)) return fail(DBAR_EINVAL, "NaN or Inf in the inputs");
   hipStream_t s = nullptr;
   HostStage& st = g_stage[0];
+  const LaunchWatch watch;
   if ((rc = st.upload(w->Q64.p, Q, n * sizeof(c64), s, true, "NaN or Inf in the inputs")) ||
       (rc = st.upload(w->x.p, S_in, n * sizeof(c64), s, true, "NaN or Inf in the inputs")))
     return rc;
@@ -2349,6 +2360,7 @@ int dbar_apply(const dbar_grid* grid, const double* Q, const double* k, const do
     P.apply<float>(w->V.p, n, V1, n, w->Q32.p, 0, w->T32.p, 1, nullptr, 1.0, 1.0, nullptr, 0, false, s);
     launch_convert<double, float>(V1, 0, w->bvec.p, 0, n, 1, nullptr, 1.0, s);
   }
+  if ((rc = watch.check())) return rc;
   if ((rc = st.download(AS_out, w->bvec.p, n * sizeof(c64), s))) return rc;
   if (hipDeviceSynchronize() != hipSuccess) return fail(DBAR_EDEVICE, "kernel failure");
   return DBAR_OK;
@@ -2362,6 +2374,7 @@ int dbar_transform(const dbar_grid* grid, int32_t inverse, const double* in, dou
   int rc = single_prep(grid, precision, false, w, P);
   if (rc) return rc;
   const size_t n = (size_t)grid->n * grid->n;
+  const LaunchWatch watch;
   if ((rc = g_stage[0].upload(w->x.p, in, n * sizeof(c64), nullptr, true, "NaN or Inf in the input"))) return rc;
   if (precision == DBAR_FP64) {
     P.transform<double>(inverse != 0, w->x.p, w->bvec.p, w->T64.p, nullptr);
@@ -2371,6 +2384,7 @@ int dbar_transform(const dbar_grid* grid, int32_t inverse, const double* in, dou
     P.transform<float>(inverse != 0, w->V.p, V1, w->T32.p, nullptr);
     launch_convert<double, float>(V1, 0, w->bvec.p, 0, n, 1, nullptr, 1.0, nullptr);
   }
+  if ((rc = watch.check())) return rc;
   return g_stage[0].download(out, w->bvec.p, n * sizeof(c64), nullptr);
 }
 
@@ -2382,6 +2396,7 @@ int dbar_dbar_inverse(const dbar_grid* grid, const double* S_in, double* h_out, 
   int rc = single_prep(grid, precision, false, w, P);
   if (rc) return rc;
   const size_t n = (size_t)grid->n * grid->n;
+  const LaunchWatch watch;
   if ((rc = g_stage[0].upload(w->x.p, S_in, n * sizeof(c64), nullptr, true, "NaN or Inf in the input"))) return rc;
   if (precision == DBAR_FP64) {
     P.h_of<double>(w->x.p, n, w->bvec.p, n, w->T64.p, 1, nullptr, nullptr);
@@ -2391,6 +2406,7 @@ int dbar_dbar_inverse(const dbar_grid* grid, const double* S_in, double* h_out, 
     P.h_of<float>(w->V.p, n, V1, n, w->T32.p, 1, nullptr, nullptr);
     launch_convert<double, float>(V1, 0, w->bvec.p, 0, n, 1, nullptr, 1.0, nullptr);
   }
+  if ((rc = watch.check())) return rc;
   return g_stage[0].download(h_out, w->bvec.p, n * sizeof(c64), nullptr);
 }
 

@@ -1,0 +1,37 @@
+"""The host code where calls of the runtime fail, on a stand-in for the runtime (fake_hip.cpp: no GPU, kernels do nothing)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_1508_02363_amd import _lib
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+EINVAL, ENOMEM, ENOCONV, EDEVICE = _lib.DBAR_EINVAL, _lib.DBAR_ENOMEM, _lib.DBAR_ENOCONV, _lib.DBAR_EDEVICE
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    exe = str(tmp_path_factory.mktemp("fake_hip") / "fake_hip")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I" + os.path.join(os.path.dirname(HERE), "include"),
+                    os.path.join(HERE, "fake_hip.cpp"), "-o", exe, "-rdynamic", "-ldl", "-pthread"], check=True)
+
+    def call(scenario):
+        r = subprocess.run([exe, _lib.LIB_PATH, scenario], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        return [(a, int(b)) for a, b in (ln.split() for ln in r.stdout.splitlines())]
+
+    return call
+
+
+def test_an_error_left_by_the_caller_does_not_refuse_a_call(run):
+    """(the stand-in's solve has nothing to converge to: DBAR_ENOCONV; the error is still there for its owner)"""
+    assert run("left_error") == [("transform", 0), ("apply", 0), ("solve", ENOCONV), ("left", 101)]
+
+
+def test_a_launch_that_fails_is_an_error(run):
+    assert run("failed_launch") == [("k_stage_copy", EDEVICE), ("after", 0), ("k_lines", EDEVICE), ("after", 0),
+                                    ("k_tail_table", EDEVICE), ("after", 0)]
