@@ -299,29 +299,38 @@ static void complete_copies(dbar_session* s, SClass& c, bool wait) {
   if (any) s->cv_done.notify_all();
 }
 
+// The end of a class whose worker cannot go on: its requests, in slots and queued, end with the error, later ones of its
+// grid get a new class, and it gives its reservation back.
+static void fail_class(dbar_session* s, SClass& c, int rc, const std::string& why) {
+  destroy_streams(c);  // (waits: result copies under way still write the requests' blocks)
+  {
+    std::lock_guard<std::mutex> lock(s->mu);
+    c.error = rc;
+    for (int b = 0; b < (int)c.slots.size(); ++b)
+      if (c.slots[b]) finish_slot(s, c, b, rc, why.c_str());
+    for (auto& r : c.queue) {
+      r->state = 2;
+      r->info.status = rc;
+      r->err_msg = why;
+      r->t_done = Clock::now();
+      s->st.queued -= 1;
+    }
+    c.queue.clear();
+    detach_class(s, c);
+  }
+  release_class(s, c);
+}
+
 static void worker(dbar_session* s, SClass* cp) {
   SClass& c = *cp;
   (void)hipSetDevice(s->device);
-  int rc = class_init(c);
+  if (const int rc = class_init(c)) {
+    fail_class(s, c, rc, "the serving worker for this grid could not set up: " + g_last_error);
+    return;
+  }
   {
     std::lock_guard<std::mutex> lock(s->mu);
-    c.ready = rc == DBAR_OK;
-    c.error = rc;
-    if (rc) {  // the requests routed to this class end with the error; the class gives its reservation back
-      for (auto& r : c.queue) {
-        r->state = 2;
-        r->info.status = rc;
-        r->err_msg = "the serving worker for this grid could not set up: " + g_last_error;
-        r->t_done = Clock::now();
-        s->st.queued -= 1;
-      }
-      c.queue.clear();
-      detach_class(s, c);
-    }
-  }
-  if (rc) {
-    release_class(s, c);
-    return;
+    c.ready = true;
   }
   Work& w = c.w;
   const size_t n = w.n;
@@ -404,8 +413,11 @@ static void worker(dbar_session* s, SClass* cp) {
       rhs_span.stride = c.P.rhs_blocks();
       launch_ctl_check(w, rhs_span, 0.0, 1, nm, static_cast<const double*>(c.tolv.p), c.stream);
       launch_zero_done(w, nm, false, c.stream);  // admitted requests with b = 0: S = m = 0
-      // (cap boxes: those of the other slots in flight are still there; a failure shows at the cycle's own wait)
-      if (c.P.box) (void)w.report({{static_cast<const int*>(w.box.p), w.host_box.data(), c.cap * 4}}, c.stream);
+      // (cap boxes: those of the other slots in flight are still there)
+      if (c.P.box && w.report({{static_cast<const int*>(w.box.p), w.host_box.data(), c.cap * 4}}, c.stream)) {
+        fail_class(s, c, DBAR_EDEVICE, "the serving worker's stream failed: " + g_last_error);
+        return;
+      }
     }
     bool computing = false;
     for (int b = 0; b < c.cap; ++b) computing |= c.h_live[b] != 0;
@@ -438,29 +450,19 @@ static void worker(dbar_session* s, SClass* cp) {
     }
     launch_ctl_start(w, mixed ? 0.3 : 0.5, mixed ? cfg.inner_tol : 0.0, static_cast<const double*>(c.tolv.p),
                      c.stream);
-    int ran;
-    TileSpan span;
-    if (mixed) {
-      ran = krylov_cycle<float>(c.P, w, cfg, c.restart, c.stream);
-      outputs |= ran == 0;
-      span = end_cycle<float>(c.P, w, ran, w.r64.p, c.stream, 0, true, outputs);
-    } else {
-      ran = krylov_cycle<double>(c.P, w, cfg, c.restart, c.stream);
-      span = end_cycle<double>(c.P, w, ran, w.V.p, c.stream, 0, true, outputs);
+    const int ran = mixed ? krylov_cycle<float>(c.P, w, cfg, c.restart, c.stream)
+                          : krylov_cycle<double>(c.P, w, cfg, c.restart, c.stream);
+    outputs |= ran == 0;
+    bool lost = ran < 0;
+    if (!lost) {
+      const TileSpan span = mixed ? end_cycle<float>(c.P, w, ran, w.r64.p, c.stream, 0, true, outputs)
+                                  : end_cycle<double>(c.P, w, ran, w.V.p, c.stream, 0, true, outputs);
+      launch_ctl_check(w, span, 0.0, 0, nullptr, check, c.stream);
+      // (x-space: the residual evaluation wrote the next cycle's FP32 basis vector itself)
+      lost = w.report({}, c.stream) != DBAR_OK;
     }
-    launch_ctl_check(w, span, 0.0, 0, nullptr, check, c.stream);
-    // (x-space: the residual evaluation wrote the next cycle's FP32 basis vector itself)
-    if (w.report({}, c.stream) != DBAR_OK) {
-      std::lock_guard<std::mutex> lock(s->mu);
-      c.error = DBAR_EDEVICE;
-      for (auto& r : c.slots)
-        if (r) {
-          r->state = 2;
-          r->info.status = DBAR_EDEVICE;
-          r->err_msg = std::string("the serving worker's stream failed: ") + hipGetErrorString(hipGetLastError());
-          r->t_done = Clock::now();
-        }
-      s->cv_done.notify_all();
+    if (lost) {
+      fail_class(s, c, DBAR_EDEVICE, "the serving worker's stream failed: " + g_last_error);
       return;
     }
     // ---- finish converged (or exhausted) requests

@@ -396,7 +396,8 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, EntryRes
 // not live (and in mask, if given): those no residual evaluation writes
 void launch_zero_done(Work& w, const int* mask, bool iterated, hipStream_t s);
 int ctl_blocks(int B);
-// one lockstep Krylov cycle over the entries flagged in w.act; returns the iterations run
+// one lockstep Krylov cycle over the entries flagged in w.act; returns the iterations run, or -1 (dbar_last_error's message
+// set) if the host could not read the flags
 template <typename T>
 int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget, hipStream_t s);
 // solution update from the cycle and the FP64 residual r = b - A(x) into r_out (returns the span of its squared norms'

@@ -1332,7 +1332,8 @@ static bool own_coef_ok(const Pipeline& P, int B, int nval, bool fp64) {
   return P.N >= 64 && P.N <= kOwnCoefMaxN && nval <= 4 && B <= used && used * B <= kOwnCoefBlocks;
 }
 
-// One Krylov cycle in lockstep; returns the number of iterations run (max over entries).
+// One Krylov cycle in lockstep; returns the number of iterations run (max over entries), or -1 if a read of the flags
+// failed (the host's copy is then an earlier step's: nothing may go by it).
 // With cfg.use_graph each group of iterations between two convergence reads is captured once into a HIP graph (per
 // element size, method, space, group, passes and batch) and replayed on later cycles and calls; nothing in a
 // captured group is a memset or a host transfer.
@@ -1473,7 +1474,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
   if (fused && !cfg.each_step && small_cycle_ok(P.N, P.L)) {
     launch_small_cycle<T>(P, w, cfg.method, window, mlim, s);
     const size_t flags = (size_t)3 * w.flag_stride + 1;  // act, restart, full, then the steps of the longest cycle
-    (void)w.report({{act, w.host_act.data(), (int)flags}}, s);
+    if (w.report({{act, w.host_act.data(), (int)flags}}, s)) return -1;
     for (int b = 0; b < B; ++b)
       if (w.host_act[w.flag_stride + b] != 0) w.full_host[b] = 1;
     return w.host_act[flags - 1];
@@ -1523,7 +1524,7 @@ int krylov_cycle(const Pipeline& P, Work& w, const BatchCfg& cfg, int it_budget,
     if (!done)
       for (int jj = j; jj < j1; ++jj) enqueue(jj);
     j = j1;
-    (void)w.report({{act, w.host_act.data(), w.flag_stride + B}}, s);
+    if (w.report({{act, w.host_act.data(), w.flag_stride + B}}, s)) return -1;
     int active = 0;
     for (int b = 0; b < B; ++b) {
       active += w.host_act[b] != 0;
@@ -1716,10 +1717,12 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, EntryRes
     // the condition estimate is taken from the first cycle (from x = 0: the longest, every entry in it)
     if (mixed) {
       ran = krylov_cycle<float>(P, w, cfg, cfg.max_iter - total, s);
+      if (ran < 0) return DBAR_EDEVICE;
       outputs = !early || ran == 0 || ran >= cfg.max_iter;
       span = end_cycle<float>(P, w, ran, w.r64.p, s, cfg.method, total == 0, outputs);
     } else {
       ran = krylov_cycle<double>(P, w, cfg, cfg.max_iter - total, s);
+      if (ran < 0) return DBAR_EDEVICE;
       span = end_cycle<double>(P, w, ran, w.V.p, s, cfg.method, total == 0);
     }
     total += ran;

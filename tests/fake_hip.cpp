@@ -185,6 +185,18 @@ int apply(int N, double L) {
   return CALL(dbar_apply, &g, in.data(), k, in.data(), out.data(), DBAR_FP64);
 }
 
+// one request to a session, its status
+int serve(dbar_session* s, int N, bool nan = false) {
+  const size_t n = (size_t)N * N;
+  std::vector<double> Q(2 * n, 0.25);
+  if (nan) Q[2 * n - 1] = std::numeric_limits<double>::quiet_NaN();
+  const double k[2] = {0.5, 0.25};
+  const dbar_grid g{N, 11, 3.0};
+  uint64_t ticket = 0;
+  if (const int rc = CALL(dbar_submit, s, &g, Q.data(), k, 1e-12, &ticket)) return rc;
+  return CALL(dbar_wait, s, ticket, nullptr, nullptr, nullptr, nullptr);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
     // an error that the caller's own calls left behind does not refuse a call; a launch that fails does
     {"left_error", [] {
@@ -203,6 +215,30 @@ const std::map<std::string, std::function<void()>> scenarios = {
          fail_kernel.clear();
          say("after", transform(64));
        }
+     }},
+    // the host's reads of the flags: the n-th of a solve of at most 8 steps is lost, n = 1, 2, .. (0: none)
+    {"lost_report", [] {
+       for (int N : {64, 128})
+         for (int n = 0; n < 4; ++n) {
+           lose_report = n ? reports + n : 0;
+           say("solve", solve(N, 3.0, 1, 8, 1));
+           say("left", hipGetLastError() != kOk);
+         }
+     }},
+    {"lost_report_serving", [] {
+       dbar_session* s = nullptr;
+       const dbar_session_opts o{size_t(1) << 30, 1, DBAR_MIXED, 20, 0};
+       if (CALL(dbar_session_create, &o, &s)) return;
+       for (int n = 0; n < 4; ++n) {
+         lose_report = n ? reports + n : 0;
+         say("lost", serve(s, 128));
+         lose_report = 0;
+         say("next", serve(s, 128));
+       }
+       dbar_session_stats st;
+       CALL(dbar_session_get_stats, s, &st);
+       say("in_flight", st.in_flight + st.queued + st.bytes_in_use);
+       CALL(dbar_session_destroy, s);
      }},
 };
 }  // namespace

@@ -35,3 +35,18 @@ def test_an_error_left_by_the_caller_does_not_refuse_a_call(run):
 def test_a_launch_that_fails_is_an_error(run):
     assert run("failed_launch") == [("k_stage_copy", EDEVICE), ("after", 0), ("k_lines", EDEVICE), ("after", 0),
                                     ("k_tail_table", EDEVICE), ("after", 0)]
+
+
+def test_a_lost_read_of_the_flags_ends_the_solve(run):
+    """The flags the host holds are then an earlier step's.  (Reads of a solve of 8 steps at N = 128: the start, every four
+    steps, the cycle's end; at N = 64: the start, the cycle, its end.)"""
+    solves = [b for a, b in run("lost_report") if a == "solve"]
+    assert solves == 2 * [ENOCONV, EDEVICE, EDEVICE, EDEVICE]
+
+
+def test_a_lost_read_of_the_flags_ends_the_requests_and_not_the_session(run):
+    """The boxes, a cycle's flags, a cycle's end: the request ends with an error, the next one of its grid is served."""
+    seen = run("lost_report_serving")
+    assert [b for a, b in seen if a == "lost"] == [ENOCONV, EDEVICE, EDEVICE, EDEVICE]
+    assert [b for a, b in seen if a == "next"] == 4 * [ENOCONV]
+    assert seen[-1] == ("in_flight", 0)
