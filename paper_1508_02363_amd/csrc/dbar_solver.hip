@@ -710,7 +710,7 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   if (N_ != N || B_ != B || m_ != m || prec_ != prec || (shared_q ? 0 : (size_t)N_ * N_) != Q_bs) drop_graphs();
   const void* before[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
                           nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
-                          dmom32.p, unit32.p, tail64.p, tail32.p};
+                          dmom32.p, unit32.p};
   N = N_;
   B = B_;
   flag_stride = B_;
@@ -771,7 +771,7 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   }
   const void* after[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
                          nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
-                          dmom32.p, unit32.p, tail64.p, tail32.p};
+                          dmom32.p, unit32.p};
   if (std::memcmp(before, after, sizeof(before)) != 0) drop_graphs();
   return DBAR_OK;
 }
@@ -782,9 +782,14 @@ int Work::setup_tail(double L, int M, hipStream_t s) {
   if (tail64.p && tail_N == N && tail_L == L && tail_M == M) return DBAR_OK;
   int rc;
   tail_N = 0;
-  drop_graphs();  // captured launches read the table
-  if ((rc = tail64.ensure(tail_table_size(N) * sizeof(c64)))) return rc;
-  if ((rc = tail32.ensure(tail_table_size(N) * sizeof(c32)))) return rc;
+  const void* const before[] = {tail64.p, tail32.p};
+  if ((rc = tail64.ensure(tail_table_size(N) * sizeof(c64))) || (rc = tail32.ensure(tail_table_size(N) * sizeof(c32)))) {
+    drop_graphs();
+    return rc;
+  }
+  // captured launches read the table where it is: another grid's values there do not matter to them (each solve of a grid
+  // sets its table up first), another place does
+  if (before[0] != tail64.p || before[1] != tail32.p) drop_graphs();
   if (!launch_tail_table(N, L, M, static_cast<c64*>(tail64.p), static_cast<c32*>(tail32.p), s))
     return fail(DBAR_EDEVICE, "the tail table could not be computed");
   // (the workspace may be used on another stream next: the table is complete when this returns)

@@ -240,6 +240,16 @@ const std::map<std::string, std::function<void()>> scenarios = {
        say("in_flight", st.in_flight + st.queued + st.bytes_in_use);
        CALL(dbar_session_destroy, s);
      }},
+    // captures of solves that alternate between two grids of one size, then a larger one between them
+    {"captures", [] {
+       for (double L : {3.0, 4.0, 3.0, 4.0}) {
+         (void)solve(128, L, 1, 8, 1);
+         say("captures", captures);
+       }
+       (void)solve(256, 3.0, 1, 8, 1);
+       (void)solve(128, 3.0, 1, 8, 1);
+       say("captures", captures);
+     }},
 };
 }  // namespace
 

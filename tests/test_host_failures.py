@@ -1,4 +1,5 @@
-"""The host code where calls of the runtime fail, on a stand-in for the runtime (fake_hip.cpp: no GPU, kernels do nothing)."""
+"""The host code on a stand-in for the runtime (fake_hip.cpp: no GPU, kernels do nothing): calls that fail, and what is kept from
+one call to the next."""
 import os
 import shutil
 import subprocess
@@ -50,3 +51,8 @@ def test_a_lost_read_of_the_flags_ends_the_requests_and_not_the_session(run):
     assert [b for a, b in seen if a == "lost"] == [ENOCONV, EDEVICE, EDEVICE, EDEVICE]
     assert [b for a, b in seen if a == "next"] == 4 * [ENOCONV]
     assert seen[-1] == ("in_flight", 0)
+
+
+def test_graphs_of_two_grids_of_one_size_are_kept(run):
+    """Eight steps are two groups: two captures for each L, none when it comes back; a larger grid drops them (new buffers)."""
+    assert [b for _, b in run("captures")] == [2, 4, 4, 4, 8]
