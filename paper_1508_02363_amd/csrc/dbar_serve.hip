@@ -636,8 +636,9 @@ int dbar_submit(dbar_session* s, const dbar_grid* grid, const double* Q, const d
   r->tol = tol;
   r->pool = &s->pool;
   r->Q = static_cast<c64*>(s->pool.get(r->q_bytes()));
-  if (!r->Q) return fail(DBAR_ENOMEM, "pinned host memory for the request's potential could not be allocated");
-  if (!copy_finite(reinterpret_cast<double*>(r->Q), Q, 2 * n)) return fail(DBAR_EINVAL, "Q contains NaN or Inf");
+  if (!r->Q && all_finite(Q, 2 * n))
+    return fail(DBAR_ENOMEM, "pinned host memory for the request's potential could not be allocated");
+  if (!r->Q || !copy_finite(reinterpret_cast<double*>(r->Q), Q, 2 * n)) return fail(DBAR_EINVAL, "Q contains NaN or Inf");
   r->footprint = footprint_of(grid->n, s->o.precision, s->o.restart, 1);
   r->t_submit = Clock::now();
   std::lock_guard<std::mutex> lock(s->mu);

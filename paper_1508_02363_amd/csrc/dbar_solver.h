@@ -213,6 +213,7 @@ struct Work {
   int report(std::initializer_list<WordRange> ranges, hipStream_t s);
   PinnedInts host_io;  // per batch: k values, grid shifts and results on their way between host and device
   int setup(int N_, int B_, int m_, int prec_, bool shared_q);
+  int setup_q(int N_);
   size_t vec_bytes(int prec) const;
 };
 

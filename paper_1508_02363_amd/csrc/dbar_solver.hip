@@ -776,6 +776,14 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   return DBAR_OK;
 }
 
+// The shared potential's buffer alone, ahead of the rest of a workspace (setup then finds it in place).
+int Work::setup_q(int N_) {
+  const void* const before = Q64.p;
+  const int rc = Q64.ensure((size_t)N_ * N_ * sizeof(c64));
+  if (Q64.p != before) drop_graphs();
+  return rc;
+}
+
 // The grid's tail table, computed on s when the grid is another than the last (an entry's value depends on nothing else).
 int Work::setup_tail(double L, int M, hipStream_t s) {
   if (N > kTailTabMaxN) return DBAR_OK;
@@ -1958,6 +1966,12 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
     Work& w = lane_work(l);
     ln[l].w = &w;
     const hipStream_t s = ln[l].s;
+    // a host potential goes up first, checked on its way: one with NaN or Inf is refused before a workspace is allocated
+    // for it (which could fail for want of memory, and the last one's graphs would go)
+    if (!q_on_device && l == 0 &&
+        ((rc = w.setup_q(N)) ||
+         (rc = g_stage[0].upload(w.Q64.p, Q, n * sizeof(c64), s, true, "Q contains NaN or Inf"))))
+      return rc;
     if ((rc = w.setup(N, Bl, o.restart, o.precision, true))) return rc;
     if ((rc = w.setup_tail(grid->L, grid->M, s))) return rc;
     if ((rc = make_pipeline(grid, w, &ln[l].P))) return rc;
@@ -1968,9 +1982,8 @@ int solve_impl(const dbar_grid* grid, const void* Q, bool q_on_device, int64_t n
         launch_convert<double, double>(Q, 0, w.Q64.p, 0, n, 1, nullptr, 1.0, s);
       else if (hipMemcpyAsync(w.Q64.p, Q, n * sizeof(c64), hipMemcpyDeviceToDevice, s) != hipSuccess)
         return fail(DBAR_EDEVICE, "Q copy failed");
-    } else {
-      // (checked on its first way up)
-      if ((rc = g_stage[l].upload(w.Q64.p, Q, n * sizeof(c64), s, l == 0, "Q contains NaN or Inf"))) return rc;
+    } else if (l > 0 && (rc = g_stage[l].upload(w.Q64.p, Q, n * sizeof(c64), s, false, ""))) {
+      return rc;
     }
     if (o.precision == DBAR_MIXED) launch_convert<float, double>(w.Q64.p, 0, w.Q32.p, 0, n, 1, nullptr, 1.0, s);
     if (cfg.xspace && cfg.reorth == 1 && N >= kBoxMinN) {

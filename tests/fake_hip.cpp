@@ -250,6 +250,25 @@ const std::map<std::string, std::function<void()>> scenarios = {
        (void)solve(128, 3.0, 1, 8, 1);
        say("captures", captures);
      }},
+    // a potential with NaN where the workspace would not fit; then a solve that replays what an earlier one captured
+    {"nan_first", [] {
+       device_limit = size_t(64) << 20;
+       for (int lanes : {1, 2}) say("nan", solve(1024, 3.0, 4, 8, lanes, true));
+       say("most", (long long)device_most);
+       say("memory", solve(1024, 3.0, 4, 8, 1));
+       device_limit = std::numeric_limits<size_t>::max();
+       (void)solve(128, 3.0, 1, 8, 1);
+       say("nan", solve(128, 3.0, 1, 8, 1, true));
+       say("nan", solve(128, 4.0, 2, 8, 2, true));
+       const int before = captures;
+       (void)solve(128, 3.0, 1, 8, 1);
+       say("captures", captures - before);
+       dbar_session* s = nullptr;
+       if (CALL(dbar_session_create, nullptr, &s)) return;
+       pinned_limit = 0;
+       say("nan", serve(s, 64, true));
+       say("memory", serve(s, 64));
+     }},
 };
 }  // namespace
 

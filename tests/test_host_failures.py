@@ -56,3 +56,13 @@ def test_a_lost_read_of_the_flags_ends_the_requests_and_not_the_session(run):
 def test_graphs_of_two_grids_of_one_size_are_kept(run):
     """Eight steps are two groups: two captures for each L, none when it comes back; a larger grid drops them (new buffers)."""
     assert [b for _, b in run("captures")] == [2, 4, 4, 4, 8]
+
+
+def test_a_potential_with_nan_is_refused_as_such_and_first(run):
+    """Also where there is no memory for its solve; nothing but the potential's own buffer is allocated before, and what an
+    earlier solve captured is still there after."""
+    seen = run("nan_first")
+    assert [b for a, b in seen if a == "nan"] == 5 * [EINVAL]
+    assert [b for a, b in seen if a == "memory"] == 2 * [ENOMEM]
+    assert dict(seen)["most"] <= 16 * 1024 ** 2
+    assert dict(seen)["captures"] == 0
