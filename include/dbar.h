@@ -299,7 +299,7 @@ int dbar_poll(dbar_session* s, uint64_t ticket, double* S_out, double* m_out, db
 /* As dbar_poll but blocks until the result is ready. */
 int dbar_wait(dbar_session* s, uint64_t ticket, double* S_out, double* m_out, dbar_info* info, double* latency_s);
 int dbar_session_get_stats(dbar_session* s, dbar_session_stats* st);
-/* Bytes of device memory a request of this grid would hold while in flight. */
+/* Bytes of device memory a request of this grid would hold while in flight, alone in its class (its tables included). */
 size_t dbar_request_footprint(const dbar_grid* grid, int32_t precision, int32_t restart);
 /* Stop the worker (pending requests are abandoned) and free everything. */
 void dbar_session_destroy(dbar_session* s);

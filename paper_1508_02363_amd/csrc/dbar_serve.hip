@@ -161,6 +161,8 @@ static size_t footprint_of(int N, int prec, int restart, int cap_hint) {
   per += mixed ? n * sizeof(c32) * 2 : 0;                                          // T32, Q32
   per += 2 * (size_t)N * sizeof(c64) + sizeof(Ctl) + 2 * kNMom * sizeof(c64);
   per += (size_t)2 * kNMom * 1024 * sizeof(double) + (size_t)(kMaxRestart + 3) * vec_blocks(n) * sizeof(double);
+  // the class's tail table, counted with each request: a class may hold a single one
+  if (N <= kTailTabMaxN) per += tail_table_size(N) * (sizeof(c64) + sizeof(c32));
   (void)cap_hint;
   return per;
 }
