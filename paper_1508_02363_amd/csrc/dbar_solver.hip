@@ -2185,6 +2185,7 @@ void dbar_default_opts(dbar_opts* o) {
   o->space = DBAR_SPACE_X;
   o->inner_tol = 0.0;
   o->orth_window = kDefaultOrthWindow;
+  o->lanes = 0;
 }
 
 const char* dbar_last_error(void) { return g_last_error.c_str(); }
