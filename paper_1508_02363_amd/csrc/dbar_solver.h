@@ -95,8 +95,12 @@ class HostStage {
   HostStage& operator=(const HostStage&) = delete;
   // host -> device on s; returns once src has been read.  check: DBAR_EINVAL with `what` if src holds NaN or Inf.
   int upload(void* dst, const void* src, size_t bytes, hipStream_t s, bool check, const char* what);
-  // device -> host after the work queued on s; returns once dst is written
-  int download(void* dst, const void* src, size_t bytes, hipStream_t s);
+  // device -> host after the work queued on s; returns once dst is written.  finish: a result of one chunk waits for the
+  // stream, not for an event on it.  After a wait for an event behind five launches or more, the next synchronisation of
+  // the device (the caller's, or dbar_apply's own) takes 35 us.  Event -> stream, N = 64: an FP32 transform 37 -> 39 us
+  // alone, 68 -> 43 with a synchronisation after each (54 by hipMemcpy); an application 105 -> 83 us.  The regularised
+  // inverse keeps the event: 55 -> 62 us alone, 79 -> 64 with one (94 and 97 by hipMemcpy).
+  int download(void* dst, const void* src, size_t bytes, hipStream_t s, bool finish = false);
   void release();
 
  private:

@@ -605,11 +605,17 @@ int HostStage::upload(void* dst, const void* src, size_t bytes, hipStream_t s, b
   }
   return DBAR_OK;
 }
-int HostStage::download(void* dst, const void* src, size_t bytes, hipStream_t s) {
+int HostStage::download(void* dst, const void* src, size_t bytes, hipStream_t s, bool finish) {
   if (int rc = ensure()) return rc;
   const size_t chunk = stage_chunk(bytes, kChunk), count = (bytes + chunk - 1) / chunk;
   for (int i = 0; i < kSlots; ++i)
     if (int rc = wait(i)) return rc;
+  if (finish && count == 1) {  // nothing to overlap
+    if (!stage_copy(buf_, src, bytes, s)) return fail(DBAR_EDEVICE, "a host transfer could not be queued");
+    if (hipStreamSynchronize(s) != hipSuccess) return fail(DBAR_EDEVICE, "a host transfer failed");
+    std::memcpy(dst, buf_, bytes);
+    return DBAR_OK;
+  }
   for (size_t c = 0; c < count + kSlots - 1; ++c) {
     if (c < count) {
       const int i = (int)(c % kSlots);
@@ -2383,7 +2389,7 @@ int dbar_apply(const dbar_grid* grid, const double* Q, const double* k, const do
     launch_convert<double, float>(V1, 0, w->bvec.p, 0, n, 1, nullptr, 1.0, s);
   }
   if ((rc = watch.check())) return rc;
-  if ((rc = st.download(AS_out, w->bvec.p, n * sizeof(c64), s))) return rc;
+  if ((rc = st.download(AS_out, w->bvec.p, n * sizeof(c64), s, true))) return rc;
   if (hipDeviceSynchronize() != hipSuccess) return fail(DBAR_EDEVICE, "kernel failure");
   return DBAR_OK;
 }
@@ -2407,7 +2413,7 @@ int dbar_transform(const dbar_grid* grid, int32_t inverse, const double* in, dou
     launch_convert<double, float>(V1, 0, w->bvec.p, 0, n, 1, nullptr, 1.0, nullptr);
   }
   if ((rc = watch.check())) return rc;
-  return g_stage[0].download(out, w->bvec.p, n * sizeof(c64), nullptr);
+  return g_stage[0].download(out, w->bvec.p, n * sizeof(c64), nullptr, true);
 }
 
 int dbar_dbar_inverse(const dbar_grid* grid, const double* S_in, double* h_out, int32_t precision) {

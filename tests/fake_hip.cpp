@@ -29,7 +29,7 @@ std::map<const void*, std::string> kernels;
 std::map<void*, size_t> device;  // live device allocations
 size_t device_bytes = 0, device_most = 0, device_limit = std::numeric_limits<size_t>::max();
 std::atomic<size_t> pinned_limit{std::numeric_limits<size_t>::max()};
-std::atomic<int> captures{0}, reports{0}, lose_report{0};  // lose_report: the ticketed k_words launch that fails (1, 2, ..)
+std::atomic<int> captures{0}, stream_waits{0}, reports{0}, lose_report{0};  // lose_report: the ticketed k_words launch that fails (1, 2, ..)
 std::string fail_kernel;                                   // launches of kernels whose name holds this fail
 thread_local int last_error = kOk;
 
@@ -96,7 +96,7 @@ API int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) { return st
 API int hipMemsetAsync(void*, int, size_t, void*) { return kOk; }
 API int hipStreamCreateWithFlags(void** s, unsigned) { return *s = std::malloc(1), kOk; }
 API int hipStreamDestroy(void* s) { return std::free(s), kOk; }
-API int hipStreamSynchronize(void*) { return kOk; }
+API int hipStreamSynchronize(void*) { return ++stream_waits, kOk; }
 API int hipStreamWaitEvent(void*, void*, unsigned) { return kOk; }
 API int hipEventCreate(void** e) { return *e = std::malloc(1), kOk; }
 API int hipEventCreateWithFlags(void** e, unsigned) { return *e = std::malloc(1), kOk; }
@@ -268,6 +268,14 @@ const std::map<std::string, std::function<void()>> scenarios = {
        pinned_limit = 0;
        say("nan", serve(s, 64, true));
        say("memory", serve(s, 64));
+     }},
+    // how transforms of one and of several chunks wait for their results
+    {"transform_waits", [] {
+       for (int N : {64, 512}) {
+         const int before = stream_waits;
+         say("transform", transform(N));
+         say("stream_waits", stream_waits - before);
+       }
      }},
 };
 }  // namespace

@@ -66,3 +66,8 @@ def test_a_potential_with_nan_is_refused_as_such_and_first(run):
     assert [b for a, b in seen if a == "memory"] == 2 * [ENOMEM]
     assert dict(seen)["most"] <= 16 * 1024 ** 2
     assert dict(seen)["captures"] == 0
+
+
+def test_a_small_transform_waits_for_its_stream(run):
+    """(one chunk; a wait for an event leaves the caller's next synchronisation of the device a slow one)"""
+    assert run("transform_waits") == [("transform", 0), ("stream_waits", 1), ("transform", 0), ("stream_waits", 0)]
