@@ -348,7 +348,10 @@ int Work::report(std::initializer_list<WordRange> ranges, hipStream_t s) {
   Words a = words_of(ranges);
   a.ticket = host_ticket.data();
   a.value = (int)++ticket_no;
-  hipLaunchKernelGGL(k_words, dim3(1), dim3(256), 0, s, a);
+  {
+    TimerScope ts(kStageControl, 0.0, 1, nullptr, s);
+    hipLaunchKernelGGL(k_words, dim3(1), dim3(256), 0, s, a);
+  }
   // The ticket for as long as short work takes, then the runtime's wait (which also shows a stream that failed).
   using Clock = std::chrono::steady_clock;
   const Clock::time_point until = Clock::now() + std::chrono::microseconds(500);
@@ -527,6 +530,7 @@ __global__ void __launch_bounds__(256) k_stage_copy(uint4* __restrict__ dst, con
 // Whole 16-byte elements.  False if the launch itself failed: hipGetLastError would also return an error that an earlier
 // call of the caller's own left.
 static bool stage_copy(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  TimerScope ts(kStageConvert, (double)bytes, 1, nullptr, s);
   unsigned n = (unsigned)(bytes / 16);
   void* args[] = {&dst, &src, &n};
   if (hipLaunchKernel(reinterpret_cast<const void*>(k_stage_copy), dim3(std::min(256u, (n + 255) / 256)), dim3(256), args, 0,
@@ -1667,6 +1671,7 @@ __global__ void k_zero_done(c64* a0, c64* a1, c64* a2, c64* a3, const int* live,
 void launch_zero_done(Work& w, const int* mask, bool iterated, hipStream_t s) {
   // plain: S and m where they are left; iterated: h (Sx), f (Fx), the shifted inverse (Ax) and m, from which S is
   // formed
+  TimerScope ts(kStageConvert, 0.0, w.B, nullptr, s);
   hipLaunchKernelGGL(k_zero_done, dim3((unsigned)std::min<size_t>(1024, (w.n + 255) / 256), w.B), dim3(256), 0, s,
                      static_cast<c64*>(iterated ? w.Sx.p : w.S_dst(0)), static_cast<c64*>(w.m_dst()),
                      iterated ? static_cast<c64*>(w.Fx.p) : nullptr, iterated ? static_cast<c64*>(w.Ax.p) : nullptr,
@@ -1721,8 +1726,7 @@ int run_batch(Pipeline& P, Work& w, const BatchCfg& cfg, hipStream_t s, EntryRes
     if (!any || total >= cfg.max_iter) break;
     const double rel = mixed ? cfg.inner_tol : 0.0;
     const double abs_tol = mixed ? 0.3 * cfg.tol : 0.5 * cfg.tol;
-    hipLaunchKernelGGL(k_ctl_start, dim3(ctl_blocks(B)), dim3(64), 0, s, ctl, nred, live, act, w.flag_stride, abs_tol,
-                       rel, nullptr, B);
+    launch_ctl_start(w, abs_tol, rel, nullptr, s);
     int ran;
     TileSpan span;
     // The first cycle of a mixed-precision x-space solve starts from |r| = |b| and asks its FP32 inner solve for

@@ -283,8 +283,11 @@ __global__ void __launch_bounds__(1024) k_box_cut(const double* tmp, int N, int 
 size_t box_scratch(int N, int B) { return (size_t)B * 2 * ((N + kBoxTile - 1) / kBoxTile) * N; }
 void launch_box(const c64* Q, size_t Q_bs, int N, double* tmp, int* box, int B, const int* act, hipStream_t s) {
   const int nt = (N + kBoxTile - 1) / kBoxTile;
-  TimerScope ts(kStageConvert, (double)N * N * sizeof(c64), B, act, s);
-  hipLaunchKernelGGL(k_box_sums, dim3(nt * nt, B), dim3(256), 0, s, Q, Q_bs, N, tmp, act);
+  {
+    TimerScope ts(kStageConvert, (double)N * N * sizeof(c64), B, act, s);
+    hipLaunchKernelGGL(k_box_sums, dim3(nt * nt, B), dim3(256), 0, s, Q, Q_bs, N, tmp, act);
+  }
+  TimerScope ts(kStageControl, 0.0, B, act, s);
   hipLaunchKernelGGL(k_box_cut, dim3(2, B), dim3(1024), 0, s, tmp, N, box_row_align(N), box, act);
 }
 

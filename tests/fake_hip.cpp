@@ -29,7 +29,7 @@ std::map<const void*, std::string> kernels;
 std::map<void*, size_t> device;  // live device allocations
 size_t device_bytes = 0, device_most = 0, device_limit = std::numeric_limits<size_t>::max();
 std::atomic<size_t> pinned_limit{std::numeric_limits<size_t>::max()};
-std::atomic<int> captures{0}, stream_waits{0}, reports{0}, lose_report{0};  // lose_report: the ticketed k_words launch that fails (1, 2, ..)
+std::atomic<int> captures{0}, stream_waits{0}, launches{0}, reports{0}, lose_report{0};  // lose_report: the ticketed k_words launch that fails (1, 2, ..)
 std::string fail_kernel;                                   // launches of kernels whose name holds this fail
 thread_local int last_error = kOk;
 
@@ -135,6 +135,7 @@ API int hipLaunchKernel(const void* f, Dim3, Dim3, void** args, size_t, void*) {
   const auto it = kernels.find(f);
   const std::string name = it == kernels.end() ? "" : it->second;
   if (!fail_kernel.empty() && name.find(fail_kernel) != std::string::npos) return set(kLaunchFailure);
+  launches += name.find("k_count_active") == std::string::npos;  // (the timer's own)
   if (name.find("k_words") == std::string::npos) return kOk;
   const Words& w = *static_cast<const Words*>(args[0]);
   if (w.ticket && ++reports == lose_report) return set(kLaunchFailure);
@@ -276,6 +277,25 @@ const std::map<std::string, std::function<void()>> scenarios = {
          say("transform", transform(N));
          say("stream_waits", stream_waits - before);
        }
+     }},
+    // launches of a few calls, and those that the timer saw
+    {"timer", [] {
+       say("on", CALL(dbar_timer_enable, 1));
+       launches = 0;
+       for (int precision : {DBAR_FP64, DBAR_MIXED})
+         for (int N : {8, 64, 128}) (void)solve(N, 3.0, 2, 8, 1, false, precision);
+       (void)transform(512);
+       (void)apply(128, 4.0);
+       const int made = launches;
+       say("off", CALL(dbar_timer_enable, 0));
+       long long seen = 0;
+       for (int i = 0; i < CALL(dbar_timer_num_stages); ++i) {
+         int64_t n = 0;
+         (void)CALL(dbar_timer_stage, i, nullptr, 0, nullptr, &n, nullptr);
+         seen += n;
+       }
+       say("made", made);
+       say("seen", seen);
      }},
 };
 }  // namespace

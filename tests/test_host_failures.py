@@ -71,3 +71,8 @@ def test_a_potential_with_nan_is_refused_as_such_and_first(run):
 def test_a_small_transform_waits_for_its_stream(run):
     """(one chunk; a wait for an event leaves the caller's next synchronisation of the device a slow one)"""
     assert run("transform_waits") == [("transform", 0), ("stream_waits", 1), ("transform", 0), ("stream_waits", 0)]
+
+
+def test_the_timer_sees_every_launch(run):
+    seen = dict(run("timer"))
+    assert seen["made"] > 100 and seen["seen"] == seen["made"]
