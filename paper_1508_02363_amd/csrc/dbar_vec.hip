@@ -245,7 +245,7 @@ __global__ void __launch_bounds__(1024) k_box_cut(const double* tmp, int N, int 
   }
   fw[t] = own;
   bw[t] = own;
-  if (t == 0) lo = 0, hi = N;
+  if (t == 0) lo = N, hi = 0;
   __syncthreads();
   for (int off = 1; off < NT; off <<= 1) {
     const double x = t >= off ? fw[t - off] : 0.0, y = t + off < NT ? bw[t + off] : 0.0;
@@ -256,24 +256,26 @@ __global__ void __launch_bounds__(1024) k_box_cut(const double* tmp, int N, int 
   }
   const double total = fw[NT - 1], cut = kBoxCut * total;
   if (total > 0x1p-900 && total < 0x1p900) {
-    // the thread that holds the first line beyond the cut, from either side
+    // the thread that holds the first line beyond the cut, from either side (the sums of neighbouring threads are rounded
+    // in different orders: where they straddle the cut more than one thread can be such, and the outermost counts)
     if (fw[t] > cut && (t == 0 || !(fw[t - 1] > cut))) {
       double s = t == 0 ? 0.0 : fw[t - 1];
       int i = 0;
       while (i < per - 1 && s + e[i] <= cut) s += e[i++];
-      lo = t * per + i;
+      atomicMin(&lo, t * per + i);
     }
     if (bw[t] > cut && (t == NT - 1 || !(bw[t + 1] > cut))) {
       double s = t == NT - 1 ? 0.0 : bw[t + 1];
       int i = per - 1;
       while (i > 0 && s + e[i] <= cut) s += e[i--];
-      hi = t * per + i + 1;
+      atomicMax(&hi, t * per + i + 1);
     }
   }
   __syncthreads();
   if (t == 0) {
     const int al = cols ? kBoxCols : align;
-    const int a = lo / al * al, z = hi < a + 1 ? a + 1 : hi;
+    const bool cut_at = hi > 0;  // (else the whole grid)
+    const int a = cut_at ? lo / al * al : 0, z = !cut_at ? N : hi < a + 1 ? a + 1 : hi;
     int* dst = box + (size_t)b * 4 + (cols ? 2 : 0);
     dst[0] = a;
     dst[1] = (z + al - 1) / al * al < N ? (z + al - 1) / al * al : N;
