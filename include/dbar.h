@@ -171,7 +171,7 @@ int dbar_apply(const dbar_grid* grid, const double* Q, const double* k, const do
  * forbid hipMalloc): dbar_apply on device buffers, allocating nothing.  Q_dev and S_dev: N*N complex128 device
  * arrays (read only), AS_dev: N*N complex128 device array (written; must not overlap S_dev); k: one (re, im) pair on
  * the host; precision DBAR_FP64 or DBAR_FP32 (as dbar_apply); stream: a hipStream_t (NULL = the default stream).
- * Every intermediate array lives in one static device array of 34 MiB per GPU (held until the process ends), which
+ * Every intermediate array lives in one static device array of 37 MiB per GPU (held until the process ends), which
  * limits the grid to N <= 1024 (larger N: DBAR_EINVAL); the twiddle tables are a second static array, filled when
  * the library is loaded.  The first call on a device looks up the two arrays' device addresses; every call only
  * queues kernels on `stream` and returns without waiting (no host copies: the calls can be captured into a HIP
@@ -207,7 +207,8 @@ int dbar_dbar_inverse(const dbar_grid* grid, const double* S_in, double* h_out, 
 typedef struct {
   int32_t n_variants[2];    /* [0]: FP64 operator, [1]: FP32 operator; 0 if that operator was not tuned */
   int32_t chosen[2];        /* the variant kept */
-  int32_t columns[2][4];    /* columns per tile of each variant */
+  int32_t columns[2][4];    /* columns per tile of each variant; a stage whose block would have more than 1024 threads,
+                               and the one that leaves moments, takes fewer */
   double ms[2][4];          /* one operator application over `batch` entries, per variant (milliseconds) */
   int32_t batch;            /* entries per launch kept for solves with opts->batch = 0 */
   int32_t batch_candidates[4];

@@ -5,7 +5,8 @@
 
 namespace dbar {
 
-static __constant__ double kInvFactC[kMaxM + 2] = {
+// 1/n!, n <= kMaxM + 1
+static __constant__ double kInvFact[kMaxM + 2] = {
     1.0, 1.0, 5.0e-1, 1.6666666666666666e-1, 4.1666666666666664e-2, 8.3333333333333332e-3,
     1.3888888888888889e-3, 1.9841269841269841e-4, 2.4801587301587302e-5, 2.7557319223985893e-6,
     2.7557319223985888e-7, 2.5052108385441720e-8, 2.0876756987868100e-9, 1.6059043836821613e-10,
@@ -34,7 +35,7 @@ DBAR_D c64 taylor_power(int n, c64 d) {  // (-i/2)^n d
   const c64 p = s * d;
   return (n & 3) == 0 ? p : (n & 3) == 1 ? mul_mi(p) : (n & 3) == 2 ? -p : mul_i(p);
 }
-DBAR_D c64 taylor_coef(int n, c64 d) { return kInvFactC[n] * taylor_power(n, d); }
+DBAR_D c64 taylor_coef(int n, c64 d) { return kInvFact[n] * taylor_power(n, d); }
 
 // sum of p[0 .. nblk) over one wave (every lane gets it), in an order fixed by nblk.  Eight independent partial sums
 // per lane: the loads of a chunk are in flight together.

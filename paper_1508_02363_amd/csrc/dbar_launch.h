@@ -135,8 +135,10 @@ int line_tiles_variant(int N, bool cols, bool fp64, int variant);
 int moment_tiles(int N, bool fp64);  // tiles of ColsInvMoments (the stride of its partials) with the current choice
 int line_tiles_max(int N, bool cols, bool fp64);  // the most tiles over the variants (sizes partial buffers)
 // Column-tile width choice per (N, precision): the number of valid variants (0: the default width; then up to two
-// wider tiles, 2x and 4x, while the block has at most 1024 threads and its LDS fits; then half the default width),
-// the current choice, and the columns of a variant.
+// wider tiles, 2x and 4x, while a block of 16 elements per thread has at most 1024 threads and its LDS fits; then half the
+// default width), the current choice, and the columns of a variant.  A stage takes fewer columns than its variant where its
+// own elements per thread would make more than 1024 threads of them, the stage that leaves moments at most 16 and from
+// N = 64 on 512 / N, but at least 4 (Tiling::cols_of): wide variants can then launch alike in some stages.
 constexpr int kMaxTileVariants = 4;
 int tile_variants(int N, bool fp64);
 int tile_variant(int N, bool fp64);
@@ -184,8 +186,6 @@ template <typename TO, typename TI> void launch_convert(const void* in, size_t i
                                                        size_t n, int B, const int* act, double scale, hipStream_t s);
 int vec_blocks(size_t n);
 
-// Deterministic reduction of partial sums: out[b][v] = scale * sum_blk part[b][v][blk]
-
 // The box of each potential Q (B of them, stride Q_bs) on an N x N grid: the rows and columns outside hold at most
 // 2^-56 of its 2-norm.  tmp: box_scratch(N, B) doubles.  box: 4 B ints.
 size_t box_scratch(int N, int B);
@@ -199,8 +199,7 @@ enum Stage : int {
   kStageLines = 0,                 // + 2 * LineOp + (float ? 1 : 0)
   kStageDots = 32,                 // + (float ? 1 : 0)
   kStageUpdate = 34,
-  kStageAxpy = 36,                 // f64 += f64 / f64 += f32 / f32 += f32: 36, 37, 38
-  kStageReduce = 39,
+  kStageAxpy = 36,                 // f64 += f64 / f64 += f32 / f32 += f32: 36, 37, 38 (39: unused)
   kStageConvert = 40,
   kStageMoments = 41,
   kStageControl = 42,

@@ -33,18 +33,6 @@
 
 namespace dbar {
 
-static __constant__ double kInvFact[40] = {
-    1.0, 1.0, 5.0e-1, 1.6666666666666666e-1, 4.1666666666666664e-2, 8.3333333333333332e-3,
-    1.3888888888888889e-3, 1.9841269841269841e-4, 2.4801587301587302e-5, 2.7557319223985893e-6,
-    2.7557319223985888e-7, 2.5052108385441720e-8, 2.0876756987868100e-9, 1.6059043836821613e-10,
-    1.1470745597729725e-11, 7.6471637318198164e-13, 4.7794773323873853e-14, 2.8114572543455206e-15,
-    1.5619206968586225e-16, 8.2206352466243295e-18, 4.1103176233121648e-19, 1.9572941063391263e-20,
-    8.8967913924505741e-22, 3.8681701706306835e-23, 1.6117375710961184e-24, 6.4469502843844736e-26,
-    2.4795962632247972e-27, 9.1836898637955460e-29, 3.2798892370698378e-30, 1.1309962886447717e-31,
-    3.7699876288159054e-33, 1.2161250415535179e-34, 3.8003907548547434e-36, 1.1516335620771951e-37,
-    3.3871575355211620e-39, 9.6775929586318906e-41, 2.6882202662866363e-42, 7.2654601791530714e-44,
-    1.9119632050402819e-45, 4.9024697565135435e-47};
-
 // Smallest u beyond which e^{-u} sum_{k<=M} u^k/k! (times a safety factor 10) is below the rounding unit, so that
 // P(n+1, u) = 1 exactly for every n <= M and omega_n = i / z^{n+1} (index M = 0..15).
 static __constant__ float kTailOneF32[16] = {19.0f,  22.75f, 26.0f,  28.75f, 31.25f, 33.5f,  36.0f,  38.0f,
@@ -501,9 +489,9 @@ struct MomentsBase : OpBase<T, N, E> {
   static constexpr bool MOMENTS = true;
   static constexpr int NV = 2 * kNMom;
   static constexpr int NMU = 2 * (kMaxM + 1);  // mu_0 .. mu_kMaxM (re, im)
-  // Per-thread moments are accumulated in the transform's precision (16 elements per thread; the FP32 operator's s
-  // carries FP32 rounding anyway, and the regularisation is exact for any G coefficients); every reduction beyond
-  // the thread and the binomial combination run in FP64.
+  // Moments are accumulated over a thread's elements (4 to 16) and its group's lanes in the transform's precision (the FP32
+  // operator's s carries FP32 rounding anyway, and the regularisation is exact for any G coefficients); the sums over
+  // groups and tiles and the binomial combination run in FP64.
   struct Acc {
     T v[NMU];  // mu_k = sum t^k s over this thread's elements
   };

@@ -352,7 +352,7 @@ __global__ void __launch_bounds__((SmallGeom<T, N>::NT), (SmallGeom<T, N>::NW >=
     sh.g[0] = c.g[0];
   }
   for (int t = threadIdx.x; t < kMaxM1 * kMaxM1; t += S::NT) sh.binom[t] = kBinom.v[t / kMaxM1][t % kMaxM1];
-  if (threadIdx.x < kMaxM1) sh.invfact[threadIdx.x] = kInvFactC[threadIdx.x];
+  if (threadIdx.x < kMaxM1) sh.invfact[threadIdx.x] = kInvFact[threadIdx.x];
   for (int t = threadIdx.x; t < N; t += S::NT) {
     const double y = xgrid<N>(t, sa.first.L);
     double p = 1.0;

@@ -60,7 +60,8 @@ struct DevBuf {
   int ensure(size_t nbytes);
 };
 
-// Pinned host allocation (device-to-host flag reads are DMA transfers, not staging kernels).
+// Pinned, coherent host allocation: kernels read k values there and write flags and results, which the host sees as they
+// arrive.
 struct PinnedInts {
   int* p = nullptr;
   size_t count = 0;
@@ -181,7 +182,7 @@ struct Work {
   size_t n = 0;
   size_t Q_bs = 0;
   DevBuf x, bvec, T64, r64, T32, V, Q64, Q32, ex, ey, ex32, ey32, coefG, dmom, dmom32, part_mom, part_vec, part_norm,
-      dred, nred, ctl, act, live, kvals, shv, unit, unit32, Hbuf;
+      nred, ctl, act, live, kvals, shv, unit, unit32, Hbuf;
   DevBuf Sx, mx;  // x-space solves: S = F x and m = h(S) of the last residual evaluation (FP64)
   DevBuf Fx, Ax;  // x-space iterated solves: f = H(h) and the shifted inverse of h of the last residual evaluation
   // Where an x-space solve leaves S and m: the caller's device arrays when it passes them (set per batch), else null

@@ -697,7 +697,7 @@ Work& Work::operator=(Work&& o) noexcept {
   ex = std::move(o.ex); ey = std::move(o.ey); coefG = std::move(o.coefG); dmom = std::move(o.dmom);
   ex32 = std::move(o.ex32); ey32 = std::move(o.ey32); dmom32 = std::move(o.dmom32); unit32 = std::move(o.unit32);
   part_mom = std::move(o.part_mom); part_vec = std::move(o.part_vec); part_norm = std::move(o.part_norm);
-  dred = std::move(o.dred); nred = std::move(o.nred); ctl = std::move(o.ctl); act = std::move(o.act);
+  nred = std::move(o.nred); ctl = std::move(o.ctl); act = std::move(o.act);
   live = std::move(o.live); kvals = std::move(o.kvals);
   shv = std::move(o.shv); unit = std::move(o.unit); Hbuf = std::move(o.Hbuf);
   Sx = std::move(o.Sx); mx = std::move(o.mx); Fx = std::move(o.Fx); Ax = std::move(o.Ax);
@@ -718,7 +718,7 @@ size_t Work::vec_bytes(int prec) const { return (size_t)n * (prec == DBAR_FP64 ?
 int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   // captured graphs hold raw pointers and sizes of this workspace: drop them if anything can change
   if (N_ != N || B_ != B || m_ != m || prec_ != prec || (shared_q ? 0 : (size_t)N_ * N_) != Q_bs) drop_graphs();
-  const void* before[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
+  const void* before[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p,
                           nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
                           dmom32.p, unit32.p};
   N = N_;
@@ -754,7 +754,6 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
   if ((rc = part_vec.ensure((size_t)B * (kMaxRestart + 2) * std::max(vec_blocks(n), rtiles) * sizeof(double))))
     return rc;
   if ((rc = part_norm.ensure((size_t)B * std::max(vec_blocks(n), rtiles) * sizeof(double)))) return rc;
-  if ((rc = dred.ensure((size_t)B * (kMaxRestart + 2) * sizeof(double)))) return rc;
   if ((rc = nred.ensure((size_t)B * sizeof(double)))) return rc;
   if ((rc = ctl.ensure((size_t)B * sizeof(Ctl)))) return rc;
   if ((rc = kvals.ensure((size_t)B * sizeof(c64)))) return rc;
@@ -779,7 +778,7 @@ int Work::setup(int N_, int B_, int m_, int prec_, bool shared_q) {
     if ((rc = host_ticket.ensure(1))) return rc;
     host_ticket[0] = (int)ticket_no;
   }
-  const void* after[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p, dred.p,
+  const void* after[] = {x.p, V.p, T64.p, T32.p, ctl.p, act.p, part_vec.p, part_norm.p, part_mom.p,
                          nred.p, Q32.p, Q64.p, ex.p, ey.p, coefG.p, dmom.p, shv.p, unit.p, Hbuf.p, ex32.p, ey32.p,
                           dmom32.p, unit32.p};
   if (std::memcmp(before, after, sizeof(before)) != 0) drop_graphs();

@@ -63,11 +63,11 @@ const char* stage_name(int stage) {
       names[stage] = stage == kStageDots ? "krylov.dots.f64" : "krylov.dots.f32";
     } else if (stage < kStageAxpy) {
       names[stage] = stage == kStageUpdate ? "krylov.update.f64" : "krylov.update.f32";
-    } else if (stage < kStageReduce) {
+    } else if (stage < kStageAxpy + 3) {
       static const char* ax[] = {"krylov.axpy.f64_f64", "krylov.axpy.f64_f32", "krylov.axpy.f32_f32"};
       names[stage] = ax[stage - kStageAxpy];
-    } else if (stage == kStageReduce) {
-      names[stage] = "reduce";
+    } else if (stage < kStageConvert) {
+      names[stage] = "?";
     } else if (stage == kStageConvert) {
       names[stage] = "convert";
     } else if (stage == kStageMoments) {

@@ -188,12 +188,12 @@ void launch_convert(const void* in, size_t in_bs, void* out, size_t out_bs, size
 // The index box of a potential
 // ------------------------------------------------------------------------------------------------------------
 // Energies |Q|^2 of 64 x 64 tiles, per row and per column of the tile: rowp[b][tile column][row],
-// colp[b][tile row][column] (grids below N = 64: one tile, its rows and columns beyond N empty).
+// colp[b][tile row][column] (whole tiles: N >= kBoxMinN).
 constexpr int kBoxTile = 64;
 __global__ void __launch_bounds__(256) k_box_sums(const c64* Q, size_t Q_bs, int N, double* tmp, const int* act) {
   const int b = blockIdx.y;
   if (act && !act[b]) return;
-  const int nt = (N + kBoxTile - 1) / kBoxTile;
+  const int nt = N / kBoxTile;
   const int tx = blockIdx.x % nt, ty = blockIdx.x / nt;
   double* rowp = tmp + (size_t)b * 2 * nt * N;
   double* colp = rowp + (size_t)nt * N;
@@ -204,18 +204,18 @@ __global__ void __launch_bounds__(256) k_box_sums(const c64* Q, size_t Q_bs, int
 #pragma unroll
   for (int i = 0; i < kBoxTile / 4; ++i) {
     const int row = ty * kBoxTile + wave + 4 * i;
-    e[i] = col < N && row < N ? norm2(Q[(size_t)b * Q_bs + (size_t)row * N + col]) : 0.0;
+    e[i] = norm2(Q[(size_t)b * Q_bs + (size_t)row * N + col]);
   }
 #pragma unroll
   for (int i = 0; i < kBoxTile / 4; ++i) {
     const int row = ty * kBoxTile + wave + 4 * i;
     ce += e[i];
     const double r = wsum(e[i]);
-    if (lane == 0 && row < N) rowp[(size_t)tx * N + row] = r;
+    if (lane == 0) rowp[(size_t)tx * N + row] = r;
   }
   cs[wave][lane] = ce;
   __syncthreads();
-  if (wave == 0 && col < N)
+  if (wave == 0)
     colp[(size_t)ty * N + col] = (cs[0][lane] + cs[1][lane]) + (cs[2][lane] + cs[3][lane]);
 }
 
@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(1024) k_box_cut(const double* tmp, int N, int 
   const int b = blockIdx.y;
   if (act && !act[b]) return;
   const bool cols = blockIdx.x == 1;
-  const int nt = (N + kBoxTile - 1) / kBoxTile;
+  const int nt = N / kBoxTile;
   const double* p = tmp + (size_t)b * 2 * nt * N + (cols ? (size_t)nt * N : 0);
   // thread t: lines t * per .. ; inclusive sums over the threads from both ends, then the lines of the thread where
   // the sum passes the limit
@@ -282,9 +282,10 @@ __global__ void __launch_bounds__(1024) k_box_cut(const double* tmp, int N, int 
   }
 }
 
-size_t box_scratch(int N, int B) { return (size_t)B * 2 * ((N + kBoxTile - 1) / kBoxTile) * N; }
+size_t box_scratch(int N, int B) { return (size_t)B * 2 * (N / kBoxTile) * N; }
 void launch_box(const c64* Q, size_t Q_bs, int N, double* tmp, int* box, int B, const int* act, hipStream_t s) {
-  const int nt = (N + kBoxTile - 1) / kBoxTile;
+  static_assert(kBoxMinN % kBoxTile == 0, "whole tiles");
+  const int nt = N / kBoxTile;
   {
     TimerScope ts(kStageConvert, (double)N * N * sizeof(c64), B, act, s);
     hipLaunchKernelGGL(k_box_sums, dim3(nt * nt, B), dim3(256), 0, s, Q, Q_bs, N, tmp, act);
