@@ -305,10 +305,12 @@ struct Ept {
   static constexpr int FWD_MOMENTS = D ? by_n(N, 4, 16, 8, 4, 8, 8, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 8, 8, 16);
   static constexpr int TAIL_ROWS = D ? by_n(N, 4, 4, 4, 4, 4, 4, 16, 16) : by_n(N, 4, 4, 4, 4, 4, 16, 16, 16);
   static constexpr int REG_COLS = D ? by_n(N, 4, 8, 8, 8, 8, 8, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 16, 16, 16);
-  // the stages of the operator on S itself (one application, N = 64: 70 -> 38 us; N = 1024: 99 -> 87 us)
+  // the stages of the operator on S itself (one application, N = 64: 70 -> 38 us; N = 1024: 99 -> 87 us).  FP32 at N = 512
+  // and 1024 takes eight for its batches: 64 mixed solves on S at N = 512 18.2 -> 16.8 -> 18.5 ms, 32 at N = 1024
+  // 37.3 -> 36.0 -> 38.0 ms, one application at N = 1024 94 -> 75 -> 70 us.
   static constexpr int MOMENT_COLS = by_n(N, 4, 4, 4, 8, 8, 8, 16, 16);
-  static constexpr int TAIL_COLS = by_n(N, 4, 4, 4, 4, 4, 4, 16, 16);
-  static constexpr int ROWS = by_n(N, 4, 4, 4, 4, 4, 8, 16, 16);  // the row stages with light work per element
+  static constexpr int TAIL_COLS = D ? by_n(N, 4, 4, 4, 4, 4, 4, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 8, 16, 16);
+  static constexpr int ROWS = D ? by_n(N, 4, 4, 4, 4, 4, 8, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 8, 16, 16);  // the row stages with light work per element
   static constexpr int COLS = by_n(N, 4, 4, 4, 8, 8, 8, 16, 16);  // the column stages with light work per element
 };
 
