@@ -78,17 +78,20 @@ def kernel_source_hash() -> str:
     return h.hexdigest()
 
 
-def stored_traffic(kernel: str, workload: str = "plain_n1024"):
-    """HBM bytes per launch of `kernel` from the PMC runs recorded in profiles/traffic_<workload>.json, or None if
-    none was recorded for it or the kernels changed since."""
+def stored_traffic(kernel: str, workload: str = "plain_n1024", entries: int = 0) -> dict:
+    """Of `kernel`, from the PMC runs recorded in profiles/traffic_<workload>.json: `traffic`, the HBM bytes per launch
+    scaled from the entries per launch of those runs (`traffic_entries`) to `entries`; None if none was recorded for it
+    or the kernels changed since."""
+    none = {"traffic": None, "traffic_entries": None}
     path = traffic_path(workload)
     if not os.path.exists(path):
-        return None
+        return none
     rec = json.load(open(path))
-    if rec.get("source_sha256") != kernel_source_hash():
-        return None
     ent = rec.get("kernels", {}).get(kernel)
-    return None if ent is None else ent["bytes_per_launch"]
+    measured = rec.get("entries_per_launch")
+    if rec.get("source_sha256") != kernel_source_hash() or ent is None or not measured:
+        return none
+    return {"traffic": ent["bytes_per_launch"] * (entries or measured) / measured, "traffic_entries": measured}
 
 
 def stage_of_kernel(name: str):
@@ -114,7 +117,7 @@ def traffic_path(workload: str) -> str:
     return os.path.join(HERE, "profiles", f"traffic_{workload}.json")
 
 
-def traffic_from(fetch_dir: str, write_dir: str, workload: str) -> dict:
+def traffic_from(fetch_dir: str, write_dir: str, workload: str, entries: int) -> dict:
     import csv
     import glob
 
@@ -149,8 +152,8 @@ def traffic_from(fetch_dir: str, write_dir: str, workload: str) -> dict:
             continue
         kernels[st] = {"bytes_per_launch": f + wv, "fetch_bytes_per_launch": f, "write_bytes_per_launch": wv,
                        "launches": len(vals)}
-    rec = {"source_sha256": kernel_source_hash(), "workload": workload, "fetch_scale": ff, "write_scale": fw,
-           "calibration_check": check, "kernels": kernels}
+    rec = {"source_sha256": kernel_source_hash(), "workload": workload, "entries_per_launch": entries,
+           "fetch_scale": ff, "write_scale": fw, "calibration_check": check, "kernels": kernels}
     json.dump(rec, open(traffic_path(workload), "w"), indent=1)
     return rec
 
@@ -351,7 +354,9 @@ def iterated_leg(D, Qd, L: float, M: int, tol: float) -> dict:
 def stage_summary(stages: list) -> dict:
     """Roofline of the dominant stage of one timed pass (the stage with the largest total time: its algorithmic bytes
     per launch over its average launch duration, HIP events on the stream the kernels run on), the per-stage GB/s,
-    and the stages whose algorithmic rate would exceed the HBM peak (a byte-model error, reported, never hidden)."""
+    and the stages whose algorithmic rate would exceed the HBM peak (a byte-model error, reported, never hidden).
+    `bound` is what limits that stage: vector issue for the column stage of the x-space operator in FP32 (0.72 of its time
+    and more by the SQ counters), else memory; achieved and peak are HBM rates either way."""
     dom = max(stages, key=lambda s: s["total_ms"])
     achieved = dom["bytes"] / (dom["total_ms"] * 1e-3) / 1e9
     fft = [s for s in stages if s["name"].startswith("lines.")]
@@ -359,7 +364,8 @@ def stage_summary(stages: list) -> dict:
     per = {s["name"]: {"ms": round(s["total_ms"], 4), "launches": s["launches"],
                        "GB/s": round(s["bytes"] / max(s["total_ms"], 1e-9) / 1e6, 1)} for s in stages}
     return {
-        "roofline": {"bound": "hbm", "kernel": dom["name"], "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "roofline": {"bound": "valu" if dom["name"] == "lines.ColsFwdRegularInv.f32" else "hbm",
+                     "kernel": dom["name"], "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "launches": dom["launches"],
                      "avg_launch_us": dom["total_ms"] * 1e3 / dom["launches"],
                      "bytes_per_launch": dom["bytes"] / dom["launches"]},
@@ -418,8 +424,8 @@ def configs_leg(D, W) -> dict:
                           "max_err_estimate": max(i.err_estimate for i in info),
                           "max_cond_estimate": max(i.cond_estimate for i in info),
                           "err_S_vs_fp64_sampled": err, "sampled_k": sample,
-                          "roofline": dict(summ["roofline"], traffic=stored_traffic(summ["roofline"]["kernel"],
-                                                                                     "mixed_n4096")),
+                          "roofline": dict(summ["roofline"], **stored_traffic(summ["roofline"]["kernel"], "mixed_n4096",
+                                                                              tune4096["batch"])),
                           "stages": summ["stages"],
                           "fft_matvec_GBs": summ["fft_matvec_GBs"], "stages_above_peak": summ["stages_above_peak"],
                           "tuning": tune4096}
@@ -448,10 +454,19 @@ def ds2_leg(D, W, N: int = 128, L: float = 3.2) -> dict:
     }
 
 
+def entries_per_launch(batch: int) -> tuple[int, int]:
+    """(lanes, entries per launch of each): the library splits a batch of 16 or more into two concurrent lanes of half the
+    entries each."""
+    lanes = 2 if batch >= 16 else 1
+    return lanes, -(-batch // lanes)
+
+
 def main():
     args = parse()
     if args.traffic_from:
-        rec = traffic_from(*args.traffic_from, args.workload)
+        import dbar_workloads as W
+        rec = traffic_from(*args.traffic_from, args.workload,
+                           entries_per_launch(args.batch if args.batch > 0 else len(W.workload(args.workload).ks))[1])
         print(json.dumps({"traffic_stages": len(rec["kernels"]), "fetch_scale": rec["fetch_scale"],
                           "write_scale": rec["write_scale"], "calibration_check": rec["calibration_check"]}))
         return
@@ -474,9 +489,7 @@ def main():
     torch.cuda.synchronize()
 
     batch = args.batch if args.batch > 0 else nk
-    # the library splits a batch of 16 or more into two concurrent lanes of half the entries each
-    lanes = 2 if batch >= 16 else 1
-    lane_batch = -(-batch // lanes)
+    lanes, lane_batch = entries_per_launch(batch)
 
     def step(**kw):
         kw.setdefault("batch", batch)
@@ -557,7 +570,7 @@ def main():
     D.timer_enable(False)
     summ = stage_summary(D.timer_stages())
     roof = summ["roofline"]
-    roof["traffic"] = stored_traffic(roof["kernel"])
+    roof.update(stored_traffic(roof["kernel"], w.name, lane_batch))
 
     context = {}
     if not args.no_context:
