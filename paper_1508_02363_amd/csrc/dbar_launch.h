@@ -48,7 +48,9 @@ struct CoefReq {
   int* act = nullptr;
   Ctl* ctl = nullptr;
 };
-// Largest grid whose RowsFwdMoments can do so (on larger ones the launches are long beside one of a few microseconds).
+// Largest grid whose RowsFwdMoments can do so: on larger ones the launches are long beside one of a few microseconds.
+// Own launch -> inside: N = 1024, one mixed problem 1291 -> 1267 us, four FP64 ones 2238 -> 2287; N = 2048, one FP64
+// 7.02 -> 7.25 ms, two mixed 2.77 -> 2.89 ms.
 constexpr int kOwnCoefMaxN = 512;
 
 struct LineArgs {

@@ -289,16 +289,40 @@ constexpr int by_n(int N, int e32, int e64, int e128, int e256, int e512, int e1
   return N <= 32 ? e32 : N <= 64 ? e64 : N <= 128 ? e128 : N <= 256 ? e256 : N <= 512 ? e512 : N <= 1024 ? e1024
          : N <= 2048 ? e2048 : e4096;
 }
-// Measured (one entry / a full batch, launch times in us; 16 -> 8 -> 4 elements per thread):
-//   tails, FP64:   N = 128 25 -> 17 -> 13 / 1024 entries 179 -> 179 -> 180;  N = 512 27 -> 17 -> 13 / 45 entries
-//                  82 -> 80 -> 73;  N = 1024 28 -> 20 -> 17 / 8 entries 61 -> 60 -> 53;  N = 2048 35 -> 41 -> 53
-//   tails, FP32:   N = 256 14 -> 11 -> 10 / 16 entries 15 -> 12 -> 11;  N = 512 15 -> 12 -> 9 / 9 entries
-//                  17 -> 14 -> 13;  N = 1024 15 -> 13 -> 10 / 8 entries 24.5 -> 26 -> 28
-//   moments, FP64: N = 64 19 -> 15 / 4096 entries 270 -> 317;  N = 128 17 -> 12 / 151 -> 136 -> 211 (the wave reduction of the moments costs the same whatever a
-//                  thread holds);  N = 256 15 -> 13 -> 12 / 63 entries 27 -> 35 -> 30;  N = 512 16 -> 13 / 54 -> 51
-//   moments, FP32: N = 256 15 -> 12 -> 10;  N = 512 14 -> 11 / 9 entries 17 -> 13.5;  N = 2048 19 -> 17 / 40 -> 37
-//   division, FP64: N = 256 15 -> 12.5 / 44 -> 39;  N = 512 15 -> 12.5 -> 13 / 88 -> 77 -> 109;  N = 1024 19 -> 17.5
-//   division, FP32: N = 128 12.5 -> 10.5 -> 9;  N = 512 13 -> 10 / 17.4 -> 16;  N = 1024 15 -> 14 / 33 -> 41
+// Measured with the row tiles below, boxes of a sum of three Gaussians at L = 5 (one entry / a batch of 2^22 .. 2^25 points;
+// launch times in us; 16 -> 8 -> 4 elements per thread; between figures within a few percent the whole solve decided):
+//   tails, FP64: N = 256 17 -> 13 -> 11 / 41 -> 35 -> 37; N = 512 18 -> 14 -> 12 / 41 -> 37 -> 38;
+//     N = 1024 22 -> 18 -> 16 / 68 -> 64 -> 69; N = 2048 59 -> 55 -> 68 / 158 -> 175 -> 240;
+//     N = 4096 174 -> 221 -> 235 / 318 -> 416 -> 443
+//   tails, FP32: N = 256 14 -> 11 -> 9 / 20 -> 21 -> 21; N = 512 15 -> 11 -> 10 / 21 -> 21 -> 21;
+//     N = 1024 17 -> 14 -> 14 / 35 -> 35 -> 39; N = 2048 24 -> 26 -> 31 / 55 -> 61 -> 82;
+//     N = 4096 74 -> 89 -> 131 / 138 -> 177 -> 257
+//   moments, FP64: N = 256 14 -> 13 -> 12 / 36 -> 37 -> 40; N = 512 16 -> 15 -> 15 / 38 -> 38 -> 41;
+//     N = 1024 18 -> 18 -> 18 / 65 -> 68 -> 76; N = 2048 39 -> 40 -> 47 / 118 -> 122 -> 150;
+//     N = 4096 125 -> 169 -> 196 / 227 -> 316 -> 366
+//   moments, FP32: N = 256 16 -> 12 -> 12 / 24 -> 19 -> 22; N = 512 17 -> 14 -> 13 / 24 -> 19 -> 22;
+//     N = 1024 18 -> 15 -> 15 / 40 -> 33 -> 41; N = 2048 26 -> 22 -> 28 / 66 -> 58 -> 68;
+//     N = 4096 82 -> 76 -> 123 / 160 -> 136 -> 219
+//   division, FP64: N = 256 15 -> 12 -> 11 / 53 -> 48 -> 50; N = 512 16 -> 13 -> 13 / 47 -> 41 -> 53;
+//     N = 1024 19 -> 19 -> 19 / 75 -> 75 -> 96; N = 2048 46 -> 47 -> 64 / 149 -> 152 -> 232;
+//     N = 4096 187 -> 193 -> 340 / 369 -> 377 -> 682
+//   division, FP32: N = 256 14 -> 11 -> 10 / 21 -> 21 -> 22; N = 512 14 -> 11 -> 12 / 21 -> 21 -> 25;
+//     N = 1024 18 -> 17 -> 14 / 37 -> 46 -> 44; N = 2048 24 -> 30 -> 43 / 67 -> 81 -> 124;
+//     N = 4096 73 -> 111 -> 152 / 135 -> 212 -> 290
+// and of the stages on S itself (whole grids):
+//   ColsInvMoments, FP64: N = 64 21 -> 14 -> 11 / 75 -> 41 -> 48; N = 256 12 -> 10 -> 10 / 36 -> 30 -> 36;
+//     N = 1024 16 -> 15 -> 16 / 54 -> 52 -> 87; N = 2048 37 -> 37 -> 52 / 152 -> 159 -> 225
+//   ColsInvTailFwd, FP64: N = 64 17 -> 11 -> 9 / 64 -> 49 -> 46; N = 256 19 -> 13 -> 11 / 71 -> 49 -> 49;
+//     N = 512 23 -> 16 -> 14 / 74 -> 51 -> 59; N = 1024 29 -> 25 -> 23 / 126 -> 112 -> 136;
+//     N = 2048 99 -> 93 -> 124 / 340 -> 366 -> 470
+//   ColsInvTailFwd, FP32: N = 256 16 -> 12 -> 10 / 32 -> 30 -> 29; N = 512 20 -> 14 -> 14 / 35 -> 32 -> 42;
+//     N = 1024 25 -> 21 -> 17 / 66 -> 74 -> 86; N = 2048 44 -> 45 -> 64 / 156 -> 161 -> 233
+//   RowsInvRegular, FP64: N = 64 12 -> 9 -> 8 / 38 -> 32 -> 30; N = 512 13 -> 10 -> 9 / 34 -> 30 -> 30;
+//     N = 1024 19 -> 17 -> 16 / 60 -> 53 -> 57; FP32: N = 512 11 -> 9 -> 8 / 20 -> 17 -> 25
+//   RowsFwdEpilogue, FP64: N = 64 11 -> 10 -> 9 / 145 -> 141 -> 139; N = 512 16 -> 14 -> 14 / 137 -> 135 -> 135;
+//     N = 2048 152 -> 141 -> 149 / 565 -> 542 -> 565
+//   ColsFwdPlain, FP64: N = 512 9 -> 8 -> 9; N = 1024 13 -> 13 -> 14; N = 2048 32 -> 34 -> 39;
+//     N = 4096 252 -> 235 -> 428
 template <typename T, int N>
 struct Ept {
   static constexpr bool D = sizeof(T) == 8;
@@ -310,8 +334,9 @@ struct Ept {
   // 37.3 -> 36.0 -> 38.0 ms, one application at N = 1024 94 -> 75 -> 70 us.
   static constexpr int MOMENT_COLS = by_n(N, 4, 4, 4, 8, 8, 8, 16, 16);
   static constexpr int TAIL_COLS = D ? by_n(N, 4, 4, 4, 4, 4, 4, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 8, 16, 16);
-  static constexpr int ROWS = D ? by_n(N, 4, 4, 4, 4, 4, 8, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 8, 16, 16);  // the row stages with light work per element
-  static constexpr int COLS = by_n(N, 4, 4, 4, 8, 8, 8, 16, 16);  // the column stages with light work per element
+  // the row stages and the column stages with light work per element
+  static constexpr int ROWS = D ? by_n(N, 4, 4, 4, 4, 4, 8, 16, 16) : by_n(N, 4, 4, 4, 4, 8, 8, 16, 16);
+  static constexpr int COLS = by_n(N, 4, 4, 4, 8, 8, 8, 16, 16);
 };
 
 template <typename T, int N>
