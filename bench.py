@@ -355,8 +355,9 @@ def stage_summary(stages: list) -> dict:
     """Roofline of the dominant stage of one timed pass (the stage with the largest total time: its algorithmic bytes
     per launch over its average launch duration, HIP events on the stream the kernels run on), the per-stage GB/s,
     and the stages whose algorithmic rate would exceed the HBM peak (a byte-model error, reported, never hidden).
-    `bound` is what limits that stage: vector issue for the column stage of the x-space operator in FP32 (0.72 of its time
-    and more by the SQ counters), else memory; achieved and peak are HBM rates either way."""
+    `bound` is what limits that stage: vector issue for the column stage of the x-space operator in FP32 (0.59 to 0.74 of
+    its time by the SQ counters, where its bytes take 0.2 to 0.4 of it), else memory; achieved and peak are HBM rates
+    either way."""
     dom = max(stages, key=lambda s: s["total_ms"])
     achieved = dom["bytes"] / (dom["total_ms"] * 1e-3) / 1e9
     fft = [s for s in stages if s["name"].startswith("lines.")]
